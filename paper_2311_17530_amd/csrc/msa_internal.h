@@ -100,7 +100,11 @@ struct Ctrl {
                       // (batched launches report it)
   int64_t wait_limit;  // batched launches: dependency-wait time-out in 100 MHz
                        // ticks (0: 2 s)
-  int32_t pad[26];
+  int32_t sweeps;   // streaming k = 4 fills finished on this workspace: their
+                    // exchange values carry the tag sweeps % 15 + 1
+  int32_t swept;    // 1 once the current fill is a streaming k = 4 one; the
+                    // kernel that ends the alignment then counts it
+  int32_t pad[24];
 };
 static_assert(sizeof(Ctrl) == 256, "control block is one 256-byte slot");
 constexpr int64_t kBatchWaitTicks = 25000000;  // 250 ms: batched launches' time-out
@@ -194,6 +198,30 @@ constexpr int kSwRows = kSwNW * kSwRPW;  // rows per workgroup
 constexpr int kSwLanes = 64;       // lanes (dimension-1 cells) per wave
 constexpr int kSwSeqMax = 16384;   // longest third sequence (kept in LDS)
 constexpr int kSwSubMax = 32;      // largest alphabet (matrix kept in LDS)
+
+// Streaming fill of k = 4 (msa_sweep4.hip): a workgroup owns rows (dimension
+// 0; 4 or 8 of them) x 16 x 16 lines along dimension 3.
+constexpr int kS4Lanes = 16;       // lanes along dimensions 1 and 2
+constexpr int kS4SeqMax = 2048;    // longest fourth sequence (kept in LDS)
+constexpr int kS4SubMax = 32;      // largest alphabet (matrix kept in LDS)
+constexpr int64_t kS4SmallX = (int64_t)64 << 20;  // exchange regions larger than the face planes
+                                   // are kept up to this size (bytes)
+constexpr int kS4FewBlocks = 256;  // up to this many blocks of 8 rows: 4 rows instead
+
+// Device descriptor of a streaming k = 4 fill.
+struct Sweep4Dev {
+  int32_t n[4];
+  int32_t nb[3];              // blocks along dimensions 0..2
+  int32_t S;                  // steps a block's slice of an exchange region holds
+  int32_t ts[3];              // tile strides of dimensions 0..2 (dimension 3: 1)
+  int32_t alpha, gap;         // batched launches (the plain path reads the control block)
+  const uint8_t *seqs;
+  const int8_t *sub;
+  int32_t *x0, *x1, *x2;      // exchange regions, [block][step][256 or 16 * rows]
+  uint8_t *dir;               // tile-major direction blocks
+  int64_t *score_out;
+  const int32_t *order;       // blocks in the order workgroups take them
+};
 
 // Parameters of one batched launch, written into the launch's arena with its
 // inputs.  The launch sequence then takes only fixed arguments (this

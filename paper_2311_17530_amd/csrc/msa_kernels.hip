@@ -978,6 +978,18 @@ __global__ __launch_bounds__(NT) void fill_kernel(JobDev jd, Ctrl *ctrl,
   }
 }
 
+// Readies the control block for the next launch on this workspace (one lane
+// of the kernel that ends an alignment).
+__device__ __forceinline__ void finish_launch(Ctrl *ctrl) {
+  ctrl->head = 0;
+  ctrl->status = ST_OK;
+  ctrl->best = INT64_MIN;
+  ctrl->epoch = ctrl->epoch + 1;
+  // a streaming k = 4 fill's tag is not used again until every other one was
+  ctrl->sweeps = ctrl->sweeps + ctrl->swept;
+  ctrl->swept = 0;
+}
+
 // ---------------------------------------------------------------------------
 // Traceback: one workgroup of one wave.
 // ---------------------------------------------------------------------------
@@ -1249,11 +1261,7 @@ __global__ __launch_bounds__(64) void traceback_kernel(JobDev jd, Ctrl *ctrl) {
     traceback_job<K, false, false>(jd, st, dirb);
   __syncthreads();
   if (threadIdx.x == 0) {
-    // ready the control block for the next launch on this workspace
-    ctrl->head = 0;
-    ctrl->status = ST_OK;
-    ctrl->best = INT64_MIN;
-    ctrl->epoch = ctrl->epoch + 1;
+    finish_launch(ctrl);
   }
 }
 
@@ -1416,11 +1424,7 @@ __global__ __launch_bounds__(64) void coopt_kernel(JobDev jd, Ctrl *ctrl, int32_
     *npaths_out = status == ST_OK ? np : 0;
     *jd.status_out = status;
     if (status != ST_OK) *jd.score_out = 0;
-    // ready the control block for the next launch on this workspace
-    ctrl->head = 0;
-    ctrl->status = ST_OK;
-    ctrl->best = INT64_MIN;
-    ctrl->epoch = ctrl->epoch + 1;
+    finish_launch(ctrl);
   }
 }
 
@@ -1656,11 +1660,7 @@ __global__ __launch_bounds__(64) void nearopt_kernel(JobDev jd, Ctrl *ctrl, int6
     *npaths_out = status == ST_OK ? np : 0;
     *jd.status_out = status;
     if (status != ST_OK) *jd.score_out = 0;
-    // ready the control block for the next launch on this workspace
-    ctrl->head = 0;
-    ctrl->status = ST_OK;
-    ctrl->best = INT64_MIN;
-    ctrl->epoch = ctrl->epoch + 1;
+    finish_launch(ctrl);
   }
 }
 

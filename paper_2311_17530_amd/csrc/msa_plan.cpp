@@ -126,9 +126,79 @@ int make_plan(const int32_t *lens, int32_t k, Plan *p) {
     o = align256(o + std::max<int64_t>((q.sw_nb1 - 1) * q.x1_plane * 4, 256));
     q.x_bytes = o - q.off_x0;
   }
+  q.tile_bytes = o;
+  if (k == 4 && q.n[3] <= kS4SeqMax) {
+    // Rows per block: 8 do the least exchange and per-step work per cell;
+    // 4 halve a block's step, which is what a tensor with no more blocks than
+    // compute units waits on.
+    for (int rows = 8; rows >= 4; rows -= 4) {
+      q.s4_rows = rows;
+      q.s4_nb[0] = (q.n[0] + rows) / rows;
+      for (int i = 1; i < 3; ++i) q.s4_nb[i] = (q.n[i] + kS4Lanes) / kS4Lanes;
+      if ((int64_t)q.s4_nb[0] * q.s4_nb[1] * q.s4_nb[2] > kS4FewBlocks) break;
+    }
+    const int64_t nb0 = q.s4_nb[0], nb1 = q.s4_nb[1], nb2 = q.s4_nb[2];
+    q.s4_steps = ((q.n[3] + 7) / 8 * 8 + 1 + 2 * (kS4Lanes - 1) + 7) / 8 * 8;
+    const int64_t S = q.s4_steps;
+    // (fewer blocks than tiles, so nothing here overflows)
+    q.s4_x0 = (nb0 - 1) * nb1 * nb2 * S * 256;
+    q.s4_x1 = nb0 * (nb1 - 1) * nb2 * S * 16 * q.s4_rows;
+    q.s4_x2 = nb0 * nb1 * (nb2 - 1) * S * 16 * q.s4_rows;
+    const int64_t xb = sweep4_x_words(q) * 4;
+    // (the kernel forms a line's offset in the direction blocks of one tile
+    // row along dimension 0 in 32 bits)
+    if (xb <= std::max<int64_t>(q.face_elems * 4, kS4SmallX) &&
+        (int64_t)q.tstride[0] * q.dbs < ((int64_t)1 << 32)) {
+      q.off_s4order = o;
+      o = align256(o + nb0 * nb1 * nb2 * 4);
+      if (xb <= q.face_elems * 4) {
+        q.off_s4x = q.off_faces;
+      } else {
+        q.off_s4x = o;
+        o = align256(o + xb);
+      }
+    } else {
+      q.s4_rows = 0;  // the tile fill only
+    }
+  }
   q.bytes = o;
   *p = q;
   return MSA_OK;
+}
+
+int64_t sweep4_x_words(const Plan &p) {
+  return std::max<int64_t>(p.s4_x0 + p.s4_x1 + p.s4_x2, 256);
+}
+
+bool sweep4_eligible(const Plan &p, int alpha, int32_t flags) {
+  return p.k == 4 && p.s4_rows > 0 && flags == 0 && alpha >= 1 && alpha <= kS4SubMax;
+}
+
+void fill_sweep4dev(const Plan &p, Sweep4Dev *sd) {
+  memset(sd, 0, sizeof(*sd));
+  for (int i = 0; i < 4; ++i) sd->n[i] = p.n[i];
+  for (int i = 0; i < 3; ++i) {
+    sd->nb[i] = p.s4_nb[i];
+    sd->ts[i] = p.tstride[i];
+  }
+  sd->S = p.s4_steps;
+}
+
+void make_sweep4_order(const Plan &p, std::vector<int32_t> *order) {
+  // by earliest start: a block along dimension 0 follows its predecessor by a
+  // few steps, one along dimension 1 or 2 by its 16 lanes more
+  const int nb0 = p.s4_nb[0], nb1 = p.s4_nb[1], nb2 = p.s4_nb[2];
+  auto key = [](int b0, int b1, int b2) { return b0 + 4 * (b1 + b2); };
+  std::vector<int32_t> count(key(nb0, nb1, nb2) + 2, 0);
+  for (int b0 = 0; b0 < nb0; ++b0)
+    for (int b1 = 0; b1 < nb1; ++b1)
+      for (int b2 = 0; b2 < nb2; ++b2) ++count[key(b0, b1, b2) + 1];
+  for (size_t i = 1; i < count.size(); ++i) count[i] += count[i - 1];
+  order->assign((size_t)nb0 * nb1 * nb2, 0);
+  int32_t b = 0;
+  for (int b0 = 0; b0 < nb0; ++b0)
+    for (int b1 = 0; b1 < nb1; ++b1)
+      for (int b2 = 0; b2 < nb2; ++b2) (*order)[count[key(b0, b1, b2)]++] = b++;
 }
 
 // The streaming k = 3 fill covers the plain and the end-gap-free modes.

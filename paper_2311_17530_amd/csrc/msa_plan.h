@@ -44,7 +44,23 @@ struct Plan {
   int32_t sw_nb0 = 0, sw_nb1 = 0;
   int64_t x0_plane = 0, x1_plane = 0;  // int32 elements per boundary
   int64_t off_x0 = 0, off_x1 = 0, x_bytes = 0;
+  // streaming fill of k = 4: rows per block, block grid, steps and words of
+  // the exchange regions; the regions share the face planes' memory where
+  // they fit there (a tile fill writes no valid tag), else follow the layout
+  int32_t s4_rows = 0, s4_nb[3] = {}, s4_steps = 0;
+  int64_t s4_x0 = 0, s4_x1 = 0, s4_x2 = 0;  // int32 elements
+  int64_t off_s4x = 0, off_s4order = 0;
+  int64_t tile_bytes = 0;    // workspace without the streaming k = 4 fill's regions
 };
+
+// The streaming k = 4 fill runs the plain mode of k = 4 plans whose alphabet
+// and fourth sequence fit its LDS tables.
+bool sweep4_eligible(const Plan &p, int alpha, int32_t flags);
+int64_t sweep4_x_words(const Plan &p);
+// Sizes of a streaming k = 4 fill (no pointers).
+void fill_sweep4dev(const Plan &p, Sweep4Dev *sd);
+// Its blocks in an order in which each follows its lower neighbours.
+void make_sweep4_order(const Plan &p, std::vector<int32_t> *order);
 
 // The streaming k = 3 fill runs the plain mode (flags 0) of a k = 3 plan
 // whose alphabet and third sequence fit its LDS tables.

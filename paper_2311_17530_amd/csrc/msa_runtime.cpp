@@ -112,6 +112,13 @@ int prepare_workspace(const Plan &p, char *ws, const int8_t *submat, int alpha, 
   // the streaming k = 3 fill's exchange regions: tag 0, never a launch's tag
   if (p.k == 3)
     ok = ok && hipMemsetAsync(ws + p.off_x0, 0, (size_t)p.x_bytes, s) == hipSuccess;
+  std::vector<int32_t> s4order;
+  if (sweep4_eligible(p, alpha, flags)) {  // the same for k = 4, and its block order
+    make_sweep4_order(p, &s4order);
+    ok = ok && hipMemcpyAsync(ws + p.off_s4order, s4order.data(), s4order.size() * 4,
+                              hipMemcpyHostToDevice, s) == hipSuccess;
+    ok = ok && hipMemsetAsync(ws + p.off_s4x, 0, (size_t)sweep4_x_words(p) * 4, s) == hipSuccess;
+  }
   ok = ok && hipStreamSynchronize(s) == hipSuccess;
   std::lock_guard<std::mutex> lk(g_mu);
   if (ok) {
@@ -159,6 +166,8 @@ static int run_fill(const Plan &p, char *ws, JobDev &jd, hipStream_t s, int alph
   tune_get(kTunePlain, p.k, length_bucket(p.n, p.k), &tc);
   if (tc.variant != 2 && sweep3_eligible(p, alpha, workspace_flags(ws)))
     return launch_sweep3(p, ws, jd, ctrl, workspace_flags(ws), s);
+  if (tc.variant != 2 && sweep4_eligible(p, alpha, workspace_flags(ws)))
+    return launch_sweep4(p, ws, jd, ctrl, s);
   const int32_t *order = reinterpret_cast<const int32_t *>(ws + p.off_order);
   int grid = fill_grid(p, tc.variant == 2 ? tc.wpc : 0);
   if (jd.ncols > 0 && grid > jd.ncols) grid = jd.ncols;

@@ -33,6 +33,8 @@ int batch_occupancy(int kclass);
 // streaming k = 3 fill (msa_sweep3.hip), for plans with sweep3_eligible
 int launch_sweep3(const Plan &p, char *ws, const JobDev &jd, Ctrl *ctrl, int32_t flags,
                   hipStream_t s);
+// streaming k = 4 fill (msa_sweep4.hip), for plans with sweep4_eligible
+int launch_sweep4(const Plan &p, char *ws, const JobDev &jd, Ctrl *ctrl, hipStream_t s);
 
 // runtime (msa_runtime.cpp)
 int device_cu_count();
