@@ -199,14 +199,17 @@ constexpr int kSwLanes = 64;       // lanes (dimension-1 cells) per wave
 constexpr int kSwSeqMax = 16384;   // longest third sequence (kept in LDS)
 constexpr int kSwSubMax = 32;      // largest alphabet (matrix kept in LDS)
 
-// Streaming fill of k = 4 (msa_sweep4.hip): a workgroup owns rows (dimension
-// 0; 4 or 8 of them) x 16 x 16 lines along dimension 3.
+// Streaming fill of k = 4 (msa_sweep4.hip): a workgroup owns 4 rows (dimension
+// 0) x 16 x 16 lines along dimension 3.
+constexpr int kS4Rows = 4;
 constexpr int kS4Lanes = 16;       // lanes along dimensions 1 and 2
 constexpr int kS4SeqMax = 2048;    // longest fourth sequence (kept in LDS)
 constexpr int kS4SubMax = 32;      // largest alphabet (matrix kept in LDS)
 constexpr int64_t kS4SmallX = (int64_t)64 << 20;  // exchange regions larger than the face planes
                                    // are kept up to this size (bytes)
-constexpr int kS4FewBlocks = 256;  // up to this many blocks of 8 rows: 4 rows instead
+// words before and after the exchange regions that the loader may read (up to
+// 2 steps before a slice and 38 after it)
+constexpr int kS4PadFront = 512, kS4PadBack = 40 * 256;
 
 // Device descriptor of a streaming k = 4 fill.
 struct Sweep4Dev {
@@ -217,7 +220,7 @@ struct Sweep4Dev {
   int32_t alpha, gap;         // batched launches (the plain path reads the control block)
   const uint8_t *seqs;
   const int8_t *sub;
-  int32_t *x0, *x1, *x2;      // exchange regions, [block][step][256 or 16 * rows]
+  int32_t *x0, *x1, *x2;      // exchange regions, [block][step][256 or 64]
   uint8_t *dir;               // tile-major direction blocks
   int64_t *score_out;
   const int32_t *order;       // blocks in the order workgroups take them

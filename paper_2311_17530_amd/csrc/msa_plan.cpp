@@ -13,7 +13,7 @@ static int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 
 static bool mul_ok(int64_t a, int64_t b, int64_t lim) { return a == 0 || b <= lim / a; }
 
-int make_plan(const int32_t *lens, int32_t k, Plan *p) {
+int make_plan(const int32_t *lens, int32_t k, Plan *p, bool streams) {
   if (!lens || !p || k < 2 || k > kMaxK) return MSA_EINVAL;
   Plan q;
   q.k = k;
@@ -78,6 +78,24 @@ int make_plan(const int32_t *lens, int32_t k, Plan *p) {
     if (!mul_ok(plane, (int64_t)q.P[i] - 1, lim)) return MSA_ENOMEM;
     q.face_elems += plane * (q.P[i] - 1);
   }
+  if (streams && k == 4 && q.n[3] <= kS4SeqMax) {
+    q.s4_nb[0] = (q.n[0] + kS4Rows) / kS4Rows;
+    for (int i = 1; i < 3; ++i) q.s4_nb[i] = (q.n[i] + kS4Lanes) / kS4Lanes;
+    const int64_t nb0 = q.s4_nb[0], nb1 = q.s4_nb[1], nb2 = q.s4_nb[2];
+    // the most steps a block runs, and one more of X0
+    q.s4_steps = ((q.n[3] + 3) / 4 * 4 + 1 + 2 * (kS4Lanes - 1) + 7) / 8 * 8 + 1;
+    const int64_t S = q.s4_steps;
+    // (at most twice as many blocks as tiles, so nothing here overflows)
+    q.s4_x0 = (nb0 - 1) * nb1 * nb2 * S * 256;
+    q.s4_x1 = nb0 * (nb1 - 1) * nb2 * S * 16 * kS4Rows;
+    q.s4_x2 = nb0 * nb1 * (nb2 - 1) * S * 16 * kS4Rows;
+    // Shapes whose exchange regions would be far larger than the face planes
+    // (short second and third sequences leave most lanes of a block idle) keep
+    // the tile fill; the kernel forms a line's offset in the direction blocks
+    // of one tile row along dimension 0 in 32 bits.
+    q.s4 = sweep4_x_words(q) * 4 <= std::max<int64_t>(2 * q.face_elems * 4, kS4SmallX) &&
+           (int64_t)q.tstride[0] * q.dbs < ((int64_t)1 << 32);
+  }
   // workspace layout
   int64_t o = 0;
   q.off_ctrl = o;   o = align256(o + (int64_t)sizeof(Ctrl));
@@ -89,8 +107,11 @@ int make_plan(const int32_t *lens, int32_t k, Plan *p) {
   q.off_path = o;   o = align256(o + std::max<int64_t>(q.total_len, 1));
   q.off_faces = o;
   if (!mul_ok(q.face_elems, 4, lim)) return MSA_ENOMEM;
-  // at least one block, so a clamped (unconditional) read at offset 0 is in range
-  o = align256(o + std::max<int64_t>(q.face_elems * 4, 256));
+  // at least one block, so a clamped (unconditional) read at offset 0 is in
+  // range; the streaming k = 4 fill's exchange regions share the planes' memory
+  // (the words of a tile fill carry no valid tag, and it reads none of theirs)
+  o = align256(o + std::max<int64_t>(
+                       {q.face_elems * 4, q.s4 ? sweep4_x_words(q) * 4 : 0, (int64_t)256}));
   q.off_dir = o;
   if (!mul_ok(q.ntiles, q.dbs, lim)) return MSA_ENOMEM;
   o = align256(o + q.ntiles * q.dbs);
@@ -126,40 +147,9 @@ int make_plan(const int32_t *lens, int32_t k, Plan *p) {
     o = align256(o + std::max<int64_t>((q.sw_nb1 - 1) * q.x1_plane * 4, 256));
     q.x_bytes = o - q.off_x0;
   }
-  q.tile_bytes = o;
-  if (k == 4 && q.n[3] <= kS4SeqMax) {
-    // Rows per block: 8 do the least exchange and per-step work per cell;
-    // 4 halve a block's step, which is what a tensor with no more blocks than
-    // compute units waits on.
-    for (int rows = 8; rows >= 4; rows -= 4) {
-      q.s4_rows = rows;
-      q.s4_nb[0] = (q.n[0] + rows) / rows;
-      for (int i = 1; i < 3; ++i) q.s4_nb[i] = (q.n[i] + kS4Lanes) / kS4Lanes;
-      if ((int64_t)q.s4_nb[0] * q.s4_nb[1] * q.s4_nb[2] > kS4FewBlocks) break;
-    }
-    const int64_t nb0 = q.s4_nb[0], nb1 = q.s4_nb[1], nb2 = q.s4_nb[2];
-    q.s4_steps = ((q.n[3] + 7) / 8 * 8 + 1 + 2 * (kS4Lanes - 1) + 7) / 8 * 8;
-    const int64_t S = q.s4_steps;
-    // (fewer blocks than tiles, so nothing here overflows)
-    q.s4_x0 = (nb0 - 1) * nb1 * nb2 * S * 256;
-    q.s4_x1 = nb0 * (nb1 - 1) * nb2 * S * 16 * q.s4_rows;
-    q.s4_x2 = nb0 * nb1 * (nb2 - 1) * S * 16 * q.s4_rows;
-    const int64_t xb = sweep4_x_words(q) * 4;
-    // (the kernel forms a line's offset in the direction blocks of one tile
-    // row along dimension 0 in 32 bits)
-    if (xb <= std::max<int64_t>(q.face_elems * 4, kS4SmallX) &&
-        (int64_t)q.tstride[0] * q.dbs < ((int64_t)1 << 32)) {
-      q.off_s4order = o;
-      o = align256(o + nb0 * nb1 * nb2 * 4);
-      if (xb <= q.face_elems * 4) {
-        q.off_s4x = q.off_faces;
-      } else {
-        q.off_s4x = o;
-        o = align256(o + xb);
-      }
-    } else {
-      q.s4_rows = 0;  // the tile fill only
-    }
+  if (q.s4) {
+    q.off_s4order = o;
+    o = align256(o + (int64_t)q.s4_nb[0] * q.s4_nb[1] * q.s4_nb[2] * 4);
   }
   q.bytes = o;
   *p = q;
@@ -167,11 +157,11 @@ int make_plan(const int32_t *lens, int32_t k, Plan *p) {
 }
 
 int64_t sweep4_x_words(const Plan &p) {
-  return std::max<int64_t>(p.s4_x0 + p.s4_x1 + p.s4_x2, 256);
+  return kS4PadFront + p.s4_x0 + p.s4_x1 + p.s4_x2 + kS4PadBack;
 }
 
 bool sweep4_eligible(const Plan &p, int alpha, int32_t flags) {
-  return p.k == 4 && p.s4_rows > 0 && flags == 0 && alpha >= 1 && alpha <= kS4SubMax;
+  return p.s4 && flags == 0 && alpha >= 1 && alpha <= kS4SubMax;
 }
 
 void fill_sweep4dev(const Plan &p, Sweep4Dev *sd) {

@@ -44,13 +44,12 @@ struct Plan {
   int32_t sw_nb0 = 0, sw_nb1 = 0;
   int64_t x0_plane = 0, x1_plane = 0;  // int32 elements per boundary
   int64_t off_x0 = 0, off_x1 = 0, x_bytes = 0;
-  // streaming fill of k = 4: rows per block, block grid, steps and words of
-  // the exchange regions; the regions share the face planes' memory where
-  // they fit there (a tile fill writes no valid tag), else follow the layout
-  int32_t s4_rows = 0, s4_nb[3] = {}, s4_steps = 0;
+  // streaming fill of k = 4: block grid, steps and words of the exchange
+  // regions (at off_faces), and the block order
+  bool s4 = false;
+  int32_t s4_nb[3] = {}, s4_steps = 0;
   int64_t s4_x0 = 0, s4_x1 = 0, s4_x2 = 0;  // int32 elements
-  int64_t off_s4x = 0, off_s4order = 0;
-  int64_t tile_bytes = 0;    // workspace without the streaming k = 4 fill's regions
+  int64_t off_s4order = 0;
 };
 
 // The streaming k = 4 fill runs the plain mode of k = 4 plans whose alphabet
@@ -69,8 +68,9 @@ bool sweep3_eligible(const Plan &p, int alpha, int32_t flags);
 constexpr int64_t kSubBytes = 255 * 255;
 constexpr int64_t kMaxTiles = (int64_t)1 << 30;
 
-// Fills geometry and layout; returns 0 or a negative status.
-int make_plan(const int32_t *lens, int32_t k, Plan *p);
+// Fills geometry and layout; returns 0 or a negative status.  Without
+// `streams`, the layout of the tile fill alone (k = 4).
+int make_plan(const int32_t *lens, int32_t k, Plan *p, bool streams = true);
 
 // Tiles ordered by computation wave (sum of tile coordinates).
 void make_tile_order(const Plan &p, std::vector<int32_t> *order);

@@ -117,7 +117,7 @@ int prepare_workspace(const Plan &p, char *ws, const int8_t *submat, int alpha, 
     make_sweep4_order(p, &s4order);
     ok = ok && hipMemcpyAsync(ws + p.off_s4order, s4order.data(), s4order.size() * 4,
                               hipMemcpyHostToDevice, s) == hipSuccess;
-    ok = ok && hipMemsetAsync(ws + p.off_s4x, 0, (size_t)sweep4_x_words(p) * 4, s) == hipSuccess;
+    ok = ok && hipMemsetAsync(ws + p.off_faces, 0, (size_t)sweep4_x_words(p) * 4, s) == hipSuccess;
   }
   ok = ok && hipStreamSynchronize(s) == hipSuccess;
   std::lock_guard<std::mutex> lk(g_mu);

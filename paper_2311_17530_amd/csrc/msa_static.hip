@@ -139,10 +139,8 @@ extern "C" int msa_dp_align_static(const uint8_t *d_seqs, const int32_t *lens, i
     if (lens[i] < 0) return MSA_EINVAL;
   if (alpha < 1 || alpha > kStaticSubMax) return MSA_EINVAL;
   Plan p;
-  int rc = make_plan(lens, k, &p);
+  int rc = make_plan(lens, k, &p, false);  // (k = 4: the tile fill)
   if (rc) return rc;
-  p.s4_rows = 0;  // k = 4: the tile fill, which needs no exchange regions
-  p.bytes = p.tile_bytes;
   if (aln_cap < p.total_len || (p.total_len > 0 && (!d_aln || !d_seqs))) return MSA_EINVAL;
   rc = check_scoring_mode(lens, k, submat, alpha, gap, 0u);
   if (rc) return rc;

@@ -1,8 +1,8 @@
 """GPU parity of the streaming four-sequence fill at the sizes where its blocks
-can go wrong: lengths at the edges of its 16-lane and 4- or 8-row blocks, runs
-of the fourth dimension at the edges of its 4-cell direction words, empty and
-one-residue sequences, both block heights.  Score, rows and the full decision
-tensor equal the oracle's exactly (integer arithmetic: no tolerance).
+can go wrong: lengths at the edges of its 4 x 16 x 16 blocks, runs of the
+fourth dimension at the edges of its 4-cell direction words, empty and
+one-residue sequences, more blocks than fit the chip.  Score, rows and the full
+decision tensor equal the oracle's exactly (integer arithmetic: no tolerance).
 """
 import sys
 
@@ -39,8 +39,8 @@ SHAPES = [
     [0, 0, 0, 0], [1, 0, 0, 1], [0, 1, 17, 4], [3, 15, 16, 3], [4, 16, 15, 5],
     [7, 17, 31, 8], [8, 31, 32, 9], [9, 32, 14, 12], [25, 33, 33, 1], [2, 47, 48, 31],
     [33, 5, 6, 40], [12, 15, 15, 0],
-    # more than 256 blocks of 8 rows: the high blocks
-    [71, 95, 95, 6], [64, 96, 111, 7], [135, 65, 63, 5],
+    # more blocks than fit the chip at once
+    [135, 111, 95, 5], [64, 160, 143, 6], [303, 65, 63, 3],
 ]
 
 
