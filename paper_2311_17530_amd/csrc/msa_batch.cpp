@@ -86,7 +86,7 @@ extern "C" int msa_dp_align_batch(const msa_job *jobs, int32_t njobs, msa_result
     while (pos < valid.size()) {
       const msa_job &j = jobs[valid[pos]];
       if (kclass_of(j.k) != kc) break;
-      const int64_t b = job_arena_bytes(j);
+      const int64_t b = job_arena_bytes(j, cap);
       Plan p;
       make_plan(j.lens, j.k, &p);
       const int64_t need = used + b + Launch::overhead_bytes((int)grp.size() + 1, tiles + p.ntiles);

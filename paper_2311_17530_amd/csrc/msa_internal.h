@@ -102,9 +102,10 @@ struct Ctrl {
                        // ticks (0: 2 s)
   int32_t sweeps;   // streaming k = 4 fills finished on this workspace: their
                     // exchange values carry the tag sweeps % 15 + 1
+  int32_t s4head;   // next slot of a batched launch's k = 4 block queue
   int32_t swept;    // 1 once the current fill is a streaming k = 4 one; the
                     // kernel that ends the alignment then counts it
-  int32_t pad[24];
+  int32_t pad[23];
 };
 static_assert(sizeof(Ctrl) == 256, "control block is one 256-byte slot");
 constexpr int64_t kBatchWaitTicks = 25000000;  // 250 ms: batched launches' time-out
@@ -223,8 +224,18 @@ struct Sweep4Dev {
   int32_t *x0, *x1, *x2;      // exchange regions, [block][step][256 or 64]
   uint8_t *dir;               // tile-major direction blocks
   int64_t *score_out;
-  const int32_t *order;       // blocks in the order workgroups take them
+  const int32_t *order;       // blocks in the order workgroups take them (plain path)
+  // batched launches: the job's status word, and the launch's queue slot of
+  // the job's first block of each key (sweep4_key)
+  int32_t *status;
+  const int32_t *kbase;
 };
+static_assert(sizeof(Sweep4Dev) % 4 == 0, "copied by words");
+
+// Blocks are taken in ascending order of this key, by earliest start: a block
+// along dimension 0 follows its predecessor by a few steps, one along dimension
+// 1 or 2 by its 16 lanes more.
+__host__ __device__ inline int sweep4_key(int b0, int b1, int b2) { return b0 + 4 * (b1 + b2); }
 
 // Parameters of one batched launch, written into the launch's arena with its
 // inputs.  The launch sequence then takes only fixed arguments (this
@@ -242,7 +253,18 @@ struct BatchArgs {
   int64_t tiles;              // tiles of all jobs
   int64_t cols;               // columns of all jobs (queue length)
   int32_t njobs;
-  int32_t pad;
+  // streaming k = 4 jobs: descriptors, blocks before each of them, the block
+  // queue ((job, block) pairs), their number, the queue's length and the tag
+  // of the launch's exchange values
+  int32_t s4n;
+  const Sweep4Dev *s4jobs;
+  const int32_t *s4pre;
+  int32_t *s4q;
+  int32_t s4total, s4tag;
+  // exchange words that may hold anything but another launch's tags, cleared
+  // before the fill (16-byte units)
+  void *xzero;
+  int64_t xzero16;
 };
 
 // One entry of the batched tile queue: (job index, tile linear index).

@@ -21,6 +21,7 @@
 #include <stdlib.h>
 
 #include "msa_internal.h"
+#include "msa_runtime.h"
 
 namespace msa {
 
@@ -1868,14 +1869,18 @@ __global__ __launch_bounds__(64) void batch_traceback_kernel(const BatchArgs *__
   }
 }
 
-// Clears the completion flags of a launch (a kernel, not a memset, so that the
+// Clears the completion flags of a launch, and the exchange words that are not
+// known to hold tagged words of other launches (a kernel, not a memset, so that the
 // launch sequence can be captured in a graph).
 __global__ void batch_zero_kernel(const BatchArgs *__restrict__ a) {
   int32_t *flags = a->flags;
   const int64_t n = a->tiles;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    flags[i] = 0;
+  const int64_t first = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t step = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = first; i < n; i += step) flags[i] = 0;
+  u32x4 *x = static_cast<u32x4 *>(a->xzero);
+  const int64_t nx = a->xzero16;
+  for (int64_t i = first; i < nx; i += step) x[i] = u32x4{0, 0, 0, 0};
 }
 
 // Reports the launch-wide status (MSA_EDEVICE after a dependency wait timed
@@ -2003,6 +2008,7 @@ static int launch_batch_k(const BatchArgs *d_args, const JobDev *d_jobs, Ctrl *c
   hipLaunchKernelGGL(batch_queue_kernel, dim3(kBatchAuxGrid), dim3(256), 0, s, d_args, d_jobs);
   hipLaunchKernelGGL((batch_fill_kernel<KLO, KHI, kBatchThreads>), dim3(grid),
                      dim3(kBatchThreads), 0, s, d_args, d_jobs, ctrl);
+  if (KLO <= 4 && 4 <= KHI) launch_batch_sweep4(d_args, ctrl, s);
   hipLaunchKernelGGL((batch_traceback_kernel<KLO, KHI>), dim3(kBatchTraceGrid), dim3(64), 0, s,
                      d_args, d_jobs, ctrl);
   hipLaunchKernelGGL(batch_finish_kernel, dim3(1), dim3(64), 0, s, d_args, ctrl);

@@ -44,9 +44,19 @@ struct JobSizes {
   int64_t small = 0;     // host-initialised bytes
   int64_t big = 0;       // device-only bytes (path, faces, dir)
   int64_t out = 0;       // output rows
+  bool s4 = false;       // streaming k = 4 fill
+  std::vector<int32_t> keys;  // its blocks per key
+  int64_t x = 0;         // its exchange regions (bytes)
+  int64_t total(int64_t ntiles) const {
+    return small + big + x + out + 12 * ntiles + (int64_t)sizeof(JobDev) + 64 +
+           (s4 ? (int64_t)sizeof(Sweep4Dev) + 8 : 0);
+  }
 };
 
-int sizes_of(const msa_job &j, JobSizes *s) {
+// cap: bytes of the arena the job has to fit.  A k = 4 job takes the streaming
+// fill where that is possible; where only the tile fill's smaller layout fits
+// the arena, it keeps that.
+int sizes_of(const msa_job &j, int64_t cap, JobSizes *s) {
   int rc = make_plan(j.lens, j.k, &s->p);
   if (rc) return rc;
   const Plan &p = s->p;
@@ -60,14 +70,23 @@ int sizes_of(const msa_job &j, JobSizes *s) {
            a256(std::max<int64_t>(p.face_elems * 4, 256)) +   // face planes
            a256(p.ntiles * p.dbs);                            // direction blocks
   s->out = a256((int64_t)j.k * s->cap);
+  if (sweep4_eligible(p, j.alpha, 0)) {
+    JobSizes t = *s;
+    t.s4 = true;
+    t.keys = sweep4_key_counts(p);
+    t.x = a256(sweep4_x_words(p) * 4);
+    t.small = a256(std::max<int64_t>(p.total_len, 1)) + a256((int64_t)t.keys.size() * 4) + 256;
+    t.big = a256(std::max<int64_t>(p.total_len, 1)) + a256(p.ntiles * p.dbs);
+    if (t.total(p.ntiles) + Launch::overhead_bytes(1, p.ntiles) <= cap) *s = t;
+  }
   return MSA_OK;
 }
 }  // namespace
 
-int64_t job_arena_bytes(const msa_job &j) {
+int64_t job_arena_bytes(const msa_job &j, int64_t cap) {
   JobSizes s;
-  if (sizes_of(j, &s)) return -1;
-  return s.small + s.big + s.out + 12 * s.p.ntiles + (int64_t)sizeof(JobDev) + 64;
+  if (sizes_of(j, cap, &s)) return -1;
+  return s.total(s.p.ntiles);
 }
 
 int64_t Launch::overhead_bytes(int njobs, int64_t ntiles_total) {
@@ -113,6 +132,7 @@ int Launch::init(int64_t bytes, hipStream_t shared) {
       return MSA_ENOMEM;
     }
     cap_ = bytes;
+    x_clean_ = cap_;  // nothing known of the new arena
   }
   // Pinned staging and the four k classes' launch graphs are made here, once
   // per arena, so that launches under load (a server's slots) allocate and
@@ -209,8 +229,8 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
   int64_t tiles = 0, small = 0, big = 0, outb = 0;
   for (int i = 0; i < nj; ++i) {
     if (kclass_of(jobs[i]->k) != kc) return MSA_EINVAL;
-    if (sizes_of(*jobs[i], &sz[i])) return MSA_EINVAL;
-    tiles += sz[i].p.ntiles;
+    if (sizes_of(*jobs[i], cap_, &sz[i])) return MSA_EINVAL;
+    if (!sz[i].s4) tiles += sz[i].p.ntiles;
     small += sz[i].small;
     big += sz[i].big;
     outb += sz[i].out;
@@ -225,6 +245,18 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
   if (off_args != kArgsOff || off_jobs != kJobsOff) return MSA_EINVAL;
   const int64_t off_jt = o;    o = a256(o + (int64_t)(nj + 1) * 8);
   const int64_t off_jc = o;    o = a256(o + (int64_t)(nj + 1) * 8);
+  int n4 = 0;               // streaming k = 4 jobs, their blocks and exchange bytes
+  int64_t blocks4 = 0, x4 = 0;
+  for (int i = 0; i < nj; ++i)
+    if (sz[i].s4) {
+      ++n4;
+      const int32_t *nb = sz[i].p.s4_nb;
+      blocks4 += (int64_t)nb[0] * nb[1] * nb[2];
+      x4 += sz[i].x;
+    }
+  if (blocks4 >= ((int64_t)1 << 30)) return MSA_ENOMEM;
+  const int64_t off_s4jobs = o; o = a256(o + (int64_t)n4 * sizeof(Sweep4Dev));
+  const int64_t off_s4pre = o;  o = a256(o + (int64_t)(n4 + 1) * 4);
   // substitution matrices, deduplicated by content
   std::map<std::string, int64_t> subs;
   std::vector<int64_t> sub_off(nj);
@@ -261,14 +293,29 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
   const int64_t off_qjob = o;  o = a256(o + tiles * 4);
   const int64_t off_qtile = o; o = a256(o + tiles * 4);
   const int64_t off_flags = o; o = a256(o + tiles * 4);
+  const int64_t off_s4q = o;   o = a256(o + blocks4 * 8);
   std::vector<int64_t> job_big(nj);
   for (int i = 0; i < nj; ++i) {
     job_big[i] = o;
     o += sz[i].big;
   }
-  if (o > cap_) return MSA_ENOMEM;
+  // The exchange regions of the streaming jobs lie at the arena's end, so that
+  // from launch to launch most of them hold words of earlier launches, whose
+  // tags are not this launch's.  [x_clean_, cap) holds nothing else; what lies
+  // before it, and everything once the tags start again, is cleared.
+  const int64_t xlo = (cap_ - x4) / 256 * 256;
+  if (o > xlo) return MSA_ENOMEM;
   int rc = ensure_host(in_bytes, out_bytes);
   if (rc) return rc;
+  if (x_clean_ < o) x_clean_ = o;
+  const int s4tag = sweeps_ % 15 + 1;
+  int64_t xzero = 0;
+  if (n4 > 0) {
+    if (s4tag == 1) x_clean_ = cap_ / 256 * 256;
+    xzero = std::max<int64_t>(0, x_clean_ - xlo);
+    x_clean_ = std::min(x_clean_, xlo);
+    ++sweeps_;
+  }
 
   // ---- host image of the input region ----
   char *h = h_in_;
@@ -276,6 +323,7 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
   Ctrl ctrl;
   memset(&ctrl, 0, sizeof(ctrl));
   ctrl.epoch = 1;
+  ctrl.wd[0] = -1;  // no job
   // A batched dependency wait is bounded by one job's tile chain (a few ms
   // even for large jobs), so a launch gives up after 250 ms instead of the
   // plain fill's 2 s: a launch that times out is re-run sooner.
@@ -291,11 +339,17 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
   std::vector<const int32_t *> wave_cnt(nj);
   std::vector<int64_t *> wave_base(nj);
   JobDev *jd_all = reinterpret_cast<JobDev *>(h + off_jobs);
+  Sweep4Dev *s4_all = reinterpret_cast<Sweep4Dev *>(h + off_s4jobs);
+  int32_t *s4pre = reinterpret_cast<int32_t *>(h + off_s4pre);
+  std::vector<int32_t *> s4base;        // queue slots per key, of each streaming job
+  std::vector<const JobSizes *> s4size;
+  int64_t xo = xlo;
   for (int i = 0; i < nj; ++i) {
     const msa_job &j = *jobs[i];
     const Plan &p = sz[i].p;
-    jt[i + 1] = jt[i] + p.ntiles;
-    jc[i + 1] = jc[i] + p.ncols;
+    const bool s4 = sz[i].s4;
+    jt[i + 1] = jt[i] + (s4 ? 0 : p.ntiles);
+    jc[i + 1] = jc[i] + (s4 ? 0 : p.ncols);
     JobDev jd;
     fill_jobdev(p, nullptr, j.alpha, j.gap, &jd);
     // small region of this job
@@ -309,21 +363,28 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
     const int64_t o_seq = so;
     so += a256(std::max<int64_t>(p.total_len, 1));
     const int64_t o_wcnt = so;
-    int32_t *wc = reinterpret_cast<int32_t *>(h + so);
+    int64_t o_wst = so;
     const int nw = p.nwaves;
-    // wc[d][s]: coordinate tuples (c_d..c_{k-1}) with sum s
-    for (int s = 0; s < nw; ++s) wc[j.k * nw + s] = (s == 0);
-    for (int d = j.k - 1; d >= 0; --d)
-      for (int s = 0; s < nw; ++s) {
-        int64_t acc = 0;
-        for (int c = 0; c < p.P[d] && c <= s; ++c) acc += wc[(d + 1) * nw + (s - c)];
-        wc[d * nw + s] = (int32_t)acc;
-      }
-    so += a256((int64_t)(j.k + 1) * nw * 4);
-    const int64_t o_wst = so;
-    wave_cnt[i] = wc + nw;  // row 1: columns by the wave of their first tile
-    wave_base[i] = reinterpret_cast<int64_t *>(h + so);
-    so += a256((int64_t)nw * 8);
+    if (s4) {
+      s4base.push_back(reinterpret_cast<int32_t *>(h + so));
+      s4size.push_back(&sz[i]);
+      so += a256((int64_t)sz[i].keys.size() * 4);
+    } else {
+      int32_t *wc = reinterpret_cast<int32_t *>(h + so);
+      // wc[d][s]: coordinate tuples (c_d..c_{k-1}) with sum s
+      for (int s = 0; s < nw; ++s) wc[j.k * nw + s] = (s == 0);
+      for (int d = j.k - 1; d >= 0; --d)
+        for (int s = 0; s < nw; ++s) {
+          int64_t acc = 0;
+          for (int c = 0; c < p.P[d] && c <= s; ++c) acc += wc[(d + 1) * nw + (s - c)];
+          wc[d * nw + s] = (int32_t)acc;
+        }
+      so += a256((int64_t)(j.k + 1) * nw * 4);
+      o_wst = so;
+      wave_cnt[i] = wc + nw;  // row 1: columns by the wave of their first tile
+      wave_base[i] = reinterpret_cast<int64_t *>(h + so);
+      so += a256((int64_t)nw * 8);
+    }
     const int64_t o_jst = so;
     // device pointers
     jd.seqs = reinterpret_cast<const uint8_t *>(d_ + o_seq);
@@ -336,8 +397,8 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
     int64_t bo = job_big[i];
     jd.path = reinterpret_cast<uint8_t *>(d_ + bo);
     bo += a256(std::max<int64_t>(p.total_len, 1));
-    jd.faces = reinterpret_cast<int32_t *>(d_ + bo);
-    bo += a256(std::max<int64_t>(p.face_elems * 4, 256));
+    jd.faces = s4 ? nullptr : reinterpret_cast<int32_t *>(d_ + bo);
+    if (!s4) bo += a256(std::max<int64_t>(p.face_elems * 4, 256));
     jd.dir = reinterpret_cast<uint8_t *>(d_ + bo);
     jd.score_out = reinterpret_cast<int64_t *>(d_ + off_score) + i;
     jd.aln_len_out = reinterpret_cast<int64_t *>(d_ + off_len) + i;
@@ -346,10 +407,30 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
     jd.aln_cap = sz[i].cap;
     jd.trace = nullptr;
     memcpy(&jd_all[i], &jd, sizeof(JobDev));
+    if (s4) {
+      const int n = (int)s4base.size() - 1;
+      Sweep4Dev sd;
+      fill_sweep4dev(p, &sd);
+      sd.alpha = j.alpha;
+      sd.gap = j.gap;
+      sd.seqs = jd.seqs;
+      sd.sub = jd.sub;
+      sd.x0 = reinterpret_cast<int32_t *>(d_ + xo) + kS4PadFront;
+      sd.x1 = sd.x0 + p.s4_x0;
+      sd.x2 = sd.x1 + p.s4_x1;
+      xo += sz[i].x;
+      sd.dir = jd.dir;
+      sd.score_out = jd.score_out;
+      sd.status = jd.jstatus;
+      sd.kbase = reinterpret_cast<const int32_t *>(d_ + o_wcnt);
+      memcpy(&s4_all[n], &sd, sizeof(sd));
+      if (n == 0) s4pre[0] = 0;
+      s4pre[n + 1] = s4pre[n] + p.s4_nb[0] * p.s4_nb[1] * p.s4_nb[2];
+    }
     meta_[i].k = j.k;
     meta_[i].cap = sz[i].cap;
     meta_[i].aln_off = job_out[i] - off_out;
-    meta_[i].qbase = jt[i];
+    meta_[i].qbase = s4 ? -2 : jt[i];
   }
 
   // The queue holds tile columns along dimension 0 (a workgroup computes a
@@ -361,20 +442,48 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
   // so the order is topological.
   {
     int wmax = 0;
-    for (int i = 0; i < nj; ++i) wmax = std::max(wmax, sz[i].p.nwaves);
+    for (int i = 0; i < nj; ++i)
+      if (!sz[i].s4) wmax = std::max(wmax, sz[i].p.nwaves);
     std::vector<int64_t> slot(wmax, 0);  // next free slot of wave w
     std::vector<int64_t> tot(wmax, 0);
     for (int i = 0; i < nj; ++i)
-      for (int w = 0; w < sz[i].p.nwaves; ++w) tot[w] += wave_cnt[i][w];
+      for (int w = 0; !sz[i].s4 && w < sz[i].p.nwaves; ++w) tot[w] += wave_cnt[i][w];
     int64_t acc = 0;
     for (int w = 0; w < wmax; ++w) {
       slot[w] = acc;
       acc += tot[w];
     }
     for (int i = 0; i < nj; ++i)
-      for (int w = 0; w < sz[i].p.nwaves; ++w) {
+      for (int w = 0; !sz[i].s4 && w < sz[i].p.nwaves; ++w) {
         wave_base[i][w] = slot[w];
         slot[w] += wave_cnt[i][w];
+      }
+  }
+
+  // The queue of the streaming jobs' blocks: all jobs' blocks in descending
+  // order of the steps their job still needs after them (about five per key,
+  // and a block's own), so that the longest chains start first and no job is
+  // left to run alone at the end; within a job the keys ascend.
+  {
+    auto bin = [&](int n, int key) {
+      return (int)s4size[n]->keys.size() - 1 - key + s4size[n]->p.s4_steps / 5;
+    };
+    int top = -1;
+    for (int n = 0; n < n4; ++n) top = std::max(top, bin(n, 0));
+    std::vector<int32_t> slot(top + 2, 0);  // next free slot of a bin
+    for (int n = 0; n < n4; ++n)
+      for (int key = 0; key < (int)s4size[n]->keys.size(); ++key)
+        slot[bin(n, key)] += s4size[n]->keys[key];
+    int32_t acc = 0;
+    for (int b = top; b >= 0; --b) {
+      const int32_t c = slot[b];
+      slot[b] = acc;
+      acc += c;
+    }
+    for (int n = 0; n < n4; ++n)
+      for (int key = 0; key < (int)s4size[n]->keys.size(); ++key) {
+        s4base[n][key] = slot[bin(n, key)];
+        slot[bin(n, key)] += s4size[n]->keys[key];
       }
   }
 
@@ -389,6 +498,14 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
   args.tiles = tiles;
   args.cols = jc[nj];
   args.njobs = nj;
+  args.s4n = n4;
+  args.s4jobs = reinterpret_cast<const Sweep4Dev *>(d_ + off_s4jobs);
+  args.s4pre = reinterpret_cast<const int32_t *>(d_ + off_s4pre);
+  args.s4q = reinterpret_cast<int32_t *>(d_ + off_s4q);
+  args.s4total = (int32_t)blocks4;
+  args.s4tag = s4tag;
+  args.xzero = d_ + xlo;
+  args.xzero16 = xzero / 16;
   memcpy(h + off_args, &args, sizeof(args));
 
   // ---- enqueue: inputs, the launch sequence (a graph replay), outputs ----
@@ -412,6 +529,7 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
   (void)off_score;
   busy_ = true;
   launch_status_ = ok ? MSA_OK : MSA_EDEVICE;
+  if (!ok) x_clean_ = cap_;  // the clearing may not have run
   return launch_status_;
 }
 

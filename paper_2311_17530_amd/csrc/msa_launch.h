@@ -22,8 +22,8 @@ int validate_job(const msa_job &j, int64_t aln_cap_needed_check = -1);
 // instead of 1 beside k = 8).
 inline int kclass_of(int k) { return k <= 4 ? 0 : k == 5 ? 1 : k == 6 ? 2 : 3; }
 
-// Device bytes one job needs inside a launch arena.
-int64_t job_arena_bytes(const msa_job &j);
+// Device bytes one job needs inside a launch arena of `cap` bytes.
+int64_t job_arena_bytes(const msa_job &j, int64_t cap);
 
 struct LaunchResult {
   int32_t status = MSA_OK;
@@ -115,6 +115,11 @@ class Launch {
   bool busy_ = false;
   int launch_status_ = MSA_OK;
   int64_t wait_limit_ = 0;
+  // streaming k = 4 jobs: launches with such jobs so far (their tags), and the
+  // arena offset from which everything is zero or a word of one of the last
+  // launches with a tag
+  int32_t sweeps_ = 0;
+  int64_t x_clean_ = 0;
   // The launch sequence of each k class, captured once on this arena (its
   // arguments are the arena's fixed batch descriptor and control block) and
   // replayed for every batch; dropped when the arena is reallocated.

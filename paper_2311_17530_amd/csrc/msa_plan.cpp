@@ -174,11 +174,24 @@ void fill_sweep4dev(const Plan &p, Sweep4Dev *sd) {
   sd->S = p.s4_steps;
 }
 
-void make_sweep4_order(const Plan &p, std::vector<int32_t> *order) {
-  // by earliest start: a block along dimension 0 follows its predecessor by a
-  // few steps, one along dimension 1 or 2 by its 16 lanes more
+std::vector<int32_t> sweep4_key_counts(const Plan &p) {
   const int nb0 = p.s4_nb[0], nb1 = p.s4_nb[1], nb2 = p.s4_nb[2];
-  auto key = [](int b0, int b1, int b2) { return b0 + 4 * (b1 + b2); };
+  // blocks with b1 + b2 = m cover the keys 4 m .. 4 m + nb0 - 1, each as often
+  // as there are such (b1, b2)
+  std::vector<int32_t> d(sweep4_key(nb0 - 1, nb1 - 1, nb2 - 1) + 2, 0);
+  for (int m = 0; m <= nb1 + nb2 - 2; ++m) {
+    const int cnt = std::min(m, nb1 - 1) - std::max(0, m - (nb2 - 1)) + 1;
+    d[sweep4_key(0, m, 0)] += cnt;
+    d[sweep4_key(nb0, m, 0)] -= cnt;
+  }
+  for (size_t i = 1; i < d.size(); ++i) d[i] += d[i - 1];
+  d.pop_back();
+  return d;
+}
+
+void make_sweep4_order(const Plan &p, std::vector<int32_t> *order) {
+  const int nb0 = p.s4_nb[0], nb1 = p.s4_nb[1], nb2 = p.s4_nb[2];
+  const auto key = sweep4_key;
   std::vector<int32_t> count(key(nb0, nb1, nb2) + 2, 0);
   for (int b0 = 0; b0 < nb0; ++b0)
     for (int b1 = 0; b1 < nb1; ++b1)

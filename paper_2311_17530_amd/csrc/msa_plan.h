@@ -58,6 +58,8 @@ bool sweep4_eligible(const Plan &p, int alpha, int32_t flags);
 int64_t sweep4_x_words(const Plan &p);
 // Sizes of a streaming k = 4 fill (no pointers).
 void fill_sweep4dev(const Plan &p, Sweep4Dev *sd);
+// Blocks per key (sweep4_key), from key 0 to the last block's.
+std::vector<int32_t> sweep4_key_counts(const Plan &p);
 // Its blocks in an order in which each follows its lower neighbours.
 void make_sweep4_order(const Plan &p, std::vector<int32_t> *order);
 

@@ -35,6 +35,9 @@ int launch_sweep3(const Plan &p, char *ws, const JobDev &jd, Ctrl *ctrl, int32_t
                   hipStream_t s);
 // streaming k = 4 fill (msa_sweep4.hip), for plans with sweep4_eligible
 int launch_sweep4(const Plan &p, char *ws, const JobDev &jd, Ctrl *ctrl, hipStream_t s);
+// the same for the k = 4 jobs of a batched launch: block queue and persistent
+// fill (fixed arguments, for launch_batch)
+void launch_batch_sweep4(const BatchArgs *d_args, Ctrl *ctrl, hipStream_t s);
 
 // runtime (msa_runtime.cpp)
 int device_cu_count();

@@ -322,7 +322,7 @@ extern "C" int msa_server_submit(msa_server *srv, const msa_job *job, uint64_t *
     off += job->lens[d];
   }
   p->job.submat = p->sub.data();
-  p->bytes = job_arena_bytes(p->job);
+  p->bytes = job_arena_bytes(p->job, srv->slot_bytes);
   Plan pl;
   make_plan(job->lens, job->k, &pl);
   p->ntiles = pl.ntiles;

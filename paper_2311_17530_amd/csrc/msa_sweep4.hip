@@ -54,6 +54,7 @@
 
 #include "msa_internal.h"
 #include "msa_plan.h"
+#include "msa_runtime.h"
 
 namespace msa {
 
@@ -578,7 +579,10 @@ __device__ __forceinline__ void s4_block(const Sweep4Dev &sd, S4Smem &sm, int it
                                          int alpha, int gap, int tag, int32_t *status, Ctrl *ctrl,
                                          int64_t wlim) {
   constexpr int R = kS4Rows, NT = kS4Threads;
-  const int tid = threadIdx.x;
+  // (opaque, so that nothing derived from it is kept across a batched launch's
+  // blocks)
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
   const int wave = __builtin_amdgcn_readfirstlane(tid) >> 6;
   int rem = item;
   const int B2 = rem % sd.nb[2];
@@ -662,6 +666,88 @@ void sweep4_kernel(Sweep4Dev sd, Ctrl *ctrl) {
   if (ticket == 0 && threadIdx.x == 0) ctrl->swept = 1;
   s4_block(sd, sm, __builtin_amdgcn_readfirstlane(sd.order[ticket]), alpha, gap, tag,
                  &ctrl->status, ctrl, kS4WaitTicks);
+}
+
+// ---------------------------------------------------------------------------
+// Batched launches: the blocks of all k = 4 jobs from one queue.
+// ---------------------------------------------------------------------------
+
+// Block b of job j goes to slot kbase_j[key] (where the host placed job j's
+// blocks of that key) + its rank among them in the order of (b1 + b2, b1).
+__global__ __launch_bounds__(256) void batch_s4queue_kernel(const BatchArgs *__restrict__ a) {
+  const int total = a->s4total;
+  const int32_t *__restrict__ pre = a->s4pre;
+  int32_t *q = a->s4q;
+  for (int g = blockIdx.x * (int)blockDim.x + threadIdx.x; g < total;
+       g += (int)(gridDim.x * blockDim.x)) {
+    int lo = 0, hi = a->s4n;  // pre[lo] <= g < pre[hi]
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (pre[mid] <= g) lo = mid; else hi = mid;
+    }
+    const Sweep4Dev &sd = a->s4jobs[lo];
+    const int nb0 = sd.nb[0], nb1 = sd.nb[1], nb2 = sd.nb[2];
+    const int b = g - pre[lo];
+    const int b2 = b % nb2, b1 = b / nb2 % nb1, b0 = b / nb2 / nb1;
+    const int key = sweep4_key(b0, b1, b2);
+    int rank = b1 - max(0, b1 + b2 - (nb2 - 1));
+    for (int m = 0; m < b1 + b2; ++m) {
+      const int c0 = key - sweep4_key(0, m, 0);  // the b0 of a block with this m and key
+      if (c0 >= 0 && c0 < nb0) rank += min(m, nb1 - 1) - max(0, m - (nb2 - 1)) + 1;
+    }
+    const int slot = sd.kbase[key] + rank;
+    q[2 * slot] = lo;
+    q[2 * slot + 1] = b;
+  }
+}
+
+// Persistent workgroups take the queue's blocks in order; every block follows
+// its job's lower neighbours there.
+__global__ __launch_bounds__(kS4Threads) __attribute__((amdgpu_waves_per_eu(4)))
+void batch_sweep4_kernel(const BatchArgs *__restrict__ a, Ctrl *ctrl) {
+  __shared__ S4Smem sm;
+  const int total = __builtin_amdgcn_readfirstlane(a->s4total);
+  const int tag = __builtin_amdgcn_readfirstlane(a->s4tag);
+  const int32_t *const q = a->s4q;
+  const Sweep4Dev *const jobs = a->s4jobs;
+  const int64_t wl =
+      __hip_atomic_load(&ctrl->wait_limit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int64_t wlim = wl > 0 ? wl : kS4WaitTicks;
+  for (;;) {
+    // every lane of the workgroup takes the same way: no divergent pop next to
+    // the loop's back edge
+    if (__builtin_amdgcn_readfirstlane((int)threadIdx.x) == 0) {
+      const int got = atomicAdd(&ctrl->s4head, threadIdx.x == 0 ? 1 : 0);
+      sm.item = __builtin_amdgcn_readfirstlane(got);
+    }
+    s4_barrier();  // also: every wave is done with the last block's LDS
+    const int it = __builtin_amdgcn_readfirstlane(sm.item);
+    if (it >= total) break;
+    const int job = __builtin_amdgcn_readfirstlane(q[2 * it]);
+    const int blk = __builtin_amdgcn_readfirstlane(q[2 * it + 1]);
+    // the job's descriptor, kept in scalar registers
+    Sweep4Dev sd;
+    {
+      const uint32_t *const src = reinterpret_cast<const uint32_t *>(jobs + job);
+      uint32_t w[sizeof(Sweep4Dev) / 4];
+#pragma unroll
+      for (int i = 0; i < (int)(sizeof(Sweep4Dev) / 4); ++i)
+        w[i] = __builtin_amdgcn_readfirstlane(src[i]);
+      __builtin_memcpy(&sd, w, sizeof(sd));
+    }
+    s4_block(sd, sm, blk, sd.alpha, sd.gap, tag, sd.status, ctrl, wlim);
+  }
+}
+
+void launch_batch_sweep4(const BatchArgs *d_args, Ctrl *ctrl, hipStream_t s) {
+  int nb = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, batch_sweep4_kernel, kS4Threads, 0) !=
+          hipSuccess ||
+      nb < 1)
+    nb = 1;
+  hipLaunchKernelGGL(batch_s4queue_kernel, dim3(256), dim3(256), 0, s, d_args);
+  hipLaunchKernelGGL(batch_sweep4_kernel, dim3((unsigned)(device_cu_count() * nb)),
+                     dim3(kS4Threads), 0, s, d_args, ctrl);
 }
 
 int launch_sweep4(const Plan &p, char *ws, const JobDev &jd, Ctrl *ctrl, hipStream_t s) {
