@@ -48,6 +48,7 @@
 // the same tile-major blocks (edge 8) as the tile kernel's, so the traceback
 // and the decision export read them unchanged.
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include <type_traits>
@@ -84,14 +85,20 @@ constexpr int kS4Threads = 8 * 64;
 // Words of one step in a block's slice of X0, and of X1 or X2.
 constexpr int kS4X0 = 256;
 constexpr int kS4X1 = 16 * kS4Rows;
+constexpr int kS4UpRow = 48, kS4UpOff = 4, kS4Up = kS4E * kS4UpRow;
+constexpr int kS4SubRow = 33;  // (an odd stride spreads the rows over the banks)
 
 struct S4Smem {
-  static constexpr int Slot = 2 * kS4Pos;  // vectors per slot
-  // Position (q1 + 1) * kS4E + q2 + 1 of slot s % 4: [1] holds the four rows at
-  // t = s - q1 - q2, the last element of [0] the row above the block at t + 1.
-  i32x4 ring[kS4Ring][2][kS4Pos];
-  i32x4 p03[kS4SubMax];                  // sub(r0 of each row, c) << 4 by code c
-  int32_t sub16[kS4SubMax * kS4SubMax];  // substitution matrix << 4
+  // Position (q1 + 1) * kS4E + q2 + 1 of slot s % 4: the four rows at t = s - q1
+  // - q2.
+  i32x4 ring[kS4Ring][kS4Pos];
+  // The row above the block, at t = s - q1 - q2 + 1: position (q1 + 1) * kS4UpRow
+  // + kS4UpOff + q2.  A wave's four runs of 16 words fall in distinct quarters
+  // of the 64 banks, and the loader writes 16 bytes a lane.
+  alignas(16) int32_t up[kS4Ring][kS4Up];
+  alignas(16) int32_t last[kS4Ring][kS4X0];  // the lanes' last rows, for the storer
+  i32x4 p03[kS4SubMax];                      // sub(r0 of each row, c) << 4 by code c
+  int32_t sub16[kS4SubMax * kS4SubRow];      // substitution matrix << 4
   uint8_t s3[kS4Front + kS4SeqMax + 64];
   int32_t late, pause;  // the loader's watchdog fired; longest pause it saw (ticks)
   int32_t item;
@@ -166,6 +173,8 @@ struct S4Loader {
   uint32_t chk[E], keep[E];
   int32_t neg[E];
   int32_t dst[E];         // LDS words from the ring's first, slot 0
+  int32_t slot1;          // words per slot there, of the single words
+  static constexpr int kUp = (int)(offsetof(Sm, up) - offsetof(Sm, ring)) / 4;
 
   __device__ __forceinline__ void set(int x, const int32_t *p, int words, int off, int steps) {
     ptr[x] = p + (int64_t)off * words;
@@ -189,15 +198,15 @@ struct S4Loader {
     if constexpr (W == 0) {
       // (X0: here + 1 steps are stored, the last for the check alone)
       if (B0 > 0) set(0, x0 + s4_x0(sd, B0 - 1, B1, B2) + lane * 4, kS4X0, 1, here + 1);
-      dst[0] = ((lane / 4 + 1) * kS4E + lane % 4 * 4 + 1) * 4 + 3;
+      dst[0] = kUp + (lane / 4 + 1) * kS4UpRow + kS4UpOff + lane % 4 * 4;
     } else if constexpr (W == 2) {
       if (B2 > 0) set(0, x2 + s4_x2(sd, B0, B1, B2 - 1) + lv, kS4X1, 16, left2);
-      dst[0] = (kS4Pos + (q + 1) * kS4E) * 4;
+      dst[0] = (q + 1) * kS4E * 4;
     } else {
       if (B1 > 0) set(0, x1 + s4_x1(sd, B0, B1 - 1, B2) + lv, kS4X1, 16, left1);
-      dst[0] = (kS4Pos + q + 1) * 4;
+      dst[0] = (q + 1) * 4;
       const int l = min(lane, kS4Rows + 32);
-      int pos = 0;  // position of the row above
+      int pos = kS4UpOff - 1;  // in the row above
       if (l < kS4Rows) {
         if (B1 > 0 && B2 > 0)
           set(1, x1 + s4_x1(sd, B0, B1 - 1, B2 - 1) + 15 * kS4Rows + l, kS4X1, 32, left12);
@@ -205,17 +214,18 @@ struct S4Loader {
         const int q2 = l - kS4Rows;
         if (B0 > 0 && B1 > 0)
           set(1, x0 + s4_x0(sd, B0 - 1, B1 - 1, B2) + 15 * 16 + q2, kS4X0, 17, left1 + 1);
-        pos = q2 + 1;
+        pos += q2 + 1;
       } else if (l < kS4Rows + 32) {
         const int q1 = l - kS4Rows - 16;
         if (B0 > 0 && B2 > 0)
           set(1, x0 + s4_x0(sd, B0 - 1, B1, B2 - 1) + q1 * 16 + 15, kS4X0, 17, left2 + 1);
-        pos = (q1 + 1) * kS4E;
+        pos += (q1 + 1) * kS4UpRow;
       } else {
         if (B0 > 0 && B1 > 0 && B2 > 0)
           set(1, x0 + s4_x0(sd, B0 - 1, B1 - 1, B2 - 1) + 255, kS4X0, 33, left12 + 1);
       }
-      dst[1] = l < kS4Rows ? kS4Pos * 4 + l : pos * 4 + 3;
+      dst[1] = l < kS4Rows ? l : kUp + pos;
+      slot1 = l < kS4Rows ? kS4Pos * 4 : kS4Up;
     }
   }
 
@@ -299,17 +309,12 @@ struct S4Loader {
                                          Ctrl *ctrl, int64_t wlim) {
     if (stale(v, tag)) respin(back, v, tag, sm, ctrl, wlim);
     auto key = [&](int x, uint32_t w) { return (int32_t)(w & keep[x]) | neg[x]; };
-    int32_t *const rb = reinterpret_cast<int32_t *>(&sm.ring[0][0][0]) +
-                        (s & (kS4Ring - 1)) * Sm::Slot * 4;
+    int32_t *const rb = reinterpret_cast<int32_t *>(&sm.ring[0][0]);
+    const int k = s & (kS4Ring - 1);
     const i32x4 r = {key(0, (uint32_t)v.w[0]), key(0, (uint32_t)(v.w[0] >> 32)),
                      key(0, (uint32_t)v.w[1]), key(0, (uint32_t)(v.w[1] >> 32))};
-    if constexpr (W == 0) {  // four positions' last elements
-#pragma unroll
-      for (int e = 0; e < 4; ++e) rb[dst[0] + 4 * e] = r[e];
-    } else {
-      *reinterpret_cast<i32x4 *>(rb + dst[0]) = r;
-    }
-    if constexpr (E > 1) rb[dst[E - 1]] = key(E - 1, (uint32_t)v.c);
+    *reinterpret_cast<i32x4 *>(rb + (dst[0] + k * (W == 0 ? kS4Up : kS4Pos * 4))) = r;
+    if constexpr (E > 1) rb[dst[E - 1] + k * slot1] = key(E - 1, (uint32_t)v.c);
   }
   // The whole block.
   __device__ __forceinline__ void run(int total, uint32_t tag, Sm &sm, Ctrl *ctrl, int64_t wlim) {
@@ -346,7 +351,7 @@ struct S4Storer {
   using Sm = S4Smem;
   int32_t *x0, *x1, *x2;      // this step's words (wave-uniform)
   bool wx0, wx1, wx2;
-  int src0, src1, src2;       // ring vectors (x0: the first of four positions)
+  int src1, src2;             // ring vectors
   uint32_t o0, o1;
   bool edge;  // the 16 lanes that store X1 and X2
   __device__ __forceinline__ S4Storer(const Sweep4Dev &sd, int B0, int B1, int B2, int lane) {
@@ -356,21 +361,18 @@ struct S4Storer {
     x0 = sd.x0 + s4_x0(sd, B0, B1, B2);
     x1 = sd.x1 + s4_x1(sd, B0, B1, B2);
     x2 = sd.x2 + s4_x2(sd, B0, B1, B2);
-    src0 = kS4Pos + (lane / 4 + 1) * kS4E + lane % 4 * 4 + 1;
     o0 = (uint32_t)lane * 4;
     const int q = lane % 16;
-    src1 = kS4Pos + 16 * kS4E + q + 1;
-    src2 = kS4Pos + (q + 1) * kS4E + 16;
+    src1 = 16 * kS4E + q + 1;
+    src2 = (q + 1) * kS4E + 16;
     o1 = (uint32_t)q * 4;
     edge = lane < 16;
   }
   __device__ __forceinline__ void step(int s, int tag, const Sm &sm) {
-    const i32x4 *const rb = &sm.ring[s & (kS4Ring - 1)][0][0];
-    if (wx0) {
-      const i32x4 v = {rb[src0].w | tag, rb[src0 + 1].w | tag, rb[src0 + 2].w | tag,
-                       rb[src0 + 3].w | tag};
-      s4_store4(x0, o0, v);
-    }
+    const i32x4 *const rb = &sm.ring[s & (kS4Ring - 1)][0];
+    if (wx0)
+      s4_store4(x0, o0,
+                *reinterpret_cast<const i32x4 *>(&sm.last[s & (kS4Ring - 1)][o0]) | tag);
     if (edge) {
       if (wx1) s4_store4(x1, o1, rb[src1] | tag);
       if (wx2) s4_store4(x2, o1, rb[src2] | tag);
@@ -403,7 +405,7 @@ __device__ __forceinline__ void s4_sweep(const Sweep4Dev &sd, S4Smem &sm, int B0
   const int g3 = gap * 48, g4 = gap * 64;
   const int32_t K1 = g3 + 14, K2 = g3 + 13, K4 = g3 + 11, K8 = g3 + 7, K9 = g4 + 6;
   int32_t K3 = g4 + 12, K5 = g4 + 10;
-  const int32_t p12 = sm.sub16[r1 * kS4SubMax + r2];
+  const int32_t p12 = sm.sub16[r1 * kS4SubRow + r2];
   const int32_t K10 = g4 + 5, K11 = g3 + 4, K12 = g4 + 3, K13 = g3 + 2;  // (mask 15: 0)
   const int32_t P7 = p12 + g3 + 8;
   int32_t K6 = g4 + 9;
@@ -413,14 +415,14 @@ __device__ __forceinline__ void s4_sweep(const Sweep4Dev &sd, S4Smem &sm, int B0
     p01[u] = sm.p03[r1][u];  // sub(r0 of row u, r1) << 4
     p02[u] = sm.p03[r2][u];
   }
-  const int32_t *const sub1 = sm.sub16 + r1 * kS4SubMax;
-  const int32_t *const sub2 = sm.sub16 + r2 * kS4SubMax;
+  const int32_t *const sub1 = sm.sub16 + r1 * kS4SubRow;
+  const int32_t *const sub2 = sm.sub16 + r2 * kS4SubRow;
   // The lane's ring vectors at position (q1 - 1, q2 - 1): + 1 is (q1 - 1, q2),
-  // + kS4E (q1, q2 - 1), + kS4E + 1 the lane's own.  The row above is the last
-  // element of the vectors before them, a step older.
-  i32x4 *const rp = &sm.ring[0][1][q1 * kS4E + q2];
-  const int32_t *const up = reinterpret_cast<const int32_t *>(rp - kS4Pos) + 3;
-  constexpr int RS = Sm::Slot;
+  // + kS4E (q1, q2 - 1), + kS4E + 1 the lane's own (the row above's rows:
+  // kS4UpRow).
+  i32x4 *const rp = &sm.ring[0][q1 * kS4E + q2];
+  const int32_t *const up = &sm.up[0][q1 * kS4UpRow + kS4UpOff - 1 + q2];
+  constexpr int RS = kS4Pos;
   // direction lines: tile (c0, c1, c2, c3), bytes ((q0*8 + q1)*8 + q2)*8 + q3
   auto tc = [](int v) { return v == 0 ? 0 : (v - 1) / kS4T + 1; };
   auto tq = [](int v) { return v == 0 ? 0 : (v - 1) % kS4T; };
@@ -466,8 +468,8 @@ __device__ __forceinline__ void s4_sweep(const Sweep4Dev &sd, S4Smem &sm, int B0
   }
   i32x4 c = rp[(-2 & RM) * RS];  // (v1 - 1, v2 - 1)
   // the row above at (v1 - 1), (v2 - 1) and both
-  int32_t na = up[((-2 & RM) * RS + 1) * 4], nb = up[((-2 & RM) * RS + kS4E) * 4],
-          nc = up[(-3 & RM) * RS * 4];
+  int32_t na = up[(-2 & RM) * kS4Up + 1], nb = up[(-2 & RM) * kS4Up + kS4UpRow],
+          nc = up[(-3 & RM) * kS4Up];
   const uint8_t *s3p = sm.s3 + kS4Front - 1 - sk;  // s3p[s]: residue of cell t of step s
   int r3 = s3p[1];
 
@@ -479,15 +481,15 @@ __device__ __forceinline__ void s4_sweep(const Sweep4Dev &sd, S4Smem &sm, int B0
       const int t = s - sk;
       const i32x4 a = rp[((i - 1) & RM) * RS + 1];     // (v1 - 1)
       const i32x4 b = rp[((i - 1) & RM) * RS + kS4E];  // (v2 - 1)
-      const int32_t no = up[(((i - 1) & RM) * RS + kS4E + 1) * 4];
+      const int32_t no = up[((i - 1) & RM) * kS4Up + kS4UpRow + 1];
       __builtin_amdgcn_sched_barrier(0);  // (LDS returns in order: these first)
       // ---- for step s + 1 ----
       const i32x4 p03 = sm.p03[r3], cn = rp[((i - 1) & RM) * RS];
       const int32_t p13 = sub1[r3], p23 = sub2[r3];
       r3 = s3p[s + 2];
-      const int32_t na1 = up[(((i - 1) & RM) * RS + 1) * 4];
-      const int32_t nb1 = up[(((i - 1) & RM) * RS + kS4E) * 4];
-      const int32_t nc1 = up[((i - 2) & RM) * RS * 4];
+      const int32_t na1 = up[((i - 1) & RM) * kS4Up + 1];
+      const int32_t nb1 = up[((i - 1) & RM) * kS4Up + kS4UpRow];
+      const int32_t nc1 = up[((i - 2) & RM) * kS4Up];
       // Opaque at every step: the compiler would otherwise keep sums with them
       // in registers across the steps.
       asm volatile("" : "+s"(K3), "+s"(K5), "+s"(K6));
@@ -522,6 +524,7 @@ __device__ __forceinline__ void s4_sweep(const Sweep4Dev &sd, S4Smem &sm, int B0
         }
       }
       rp[(i & RM) * RS + kS4E + 1] = out;
+      sm.last[i & RM][tid] = out[R - 1];
       {
         // ---- masks 8 .. 15 of step s + 1 ----
         int32_t so = no;
@@ -591,7 +594,7 @@ __device__ __forceinline__ void s4_block(const Sweep4Dev &sd, S4Smem &sm, int it
   const int B0 = rem / sd.nb[1];
   bool bad = false;
   for (int e = tid; e < alpha * alpha; e += NT)
-    sm.sub16[(e / alpha) * kS4SubMax + e % alpha] = (int32_t)sd.sub[e] * 16;
+    sm.sub16[(e / alpha) * kS4SubRow + e % alpha] = (int32_t)sd.sub[e] * 16;
   for (int e = tid; e < alpha * R; e += NT) {
     const int cc = e / R, u = e % R;
     const int v0 = B0 * R + u;
@@ -614,8 +617,9 @@ __device__ __forceinline__ void s4_block(const Sweep4Dev &sd, S4Smem &sm, int it
   }
   if (bad) atomicCAS(status, 0, -1);
   // before step 0 the rings hold cells t < 0: -infinity
-  for (int e = tid; e < kS4Ring * S4Smem::Slot; e += NT)
-    (&sm.ring[0][0][0])[e] = i32x4{kNegKey, kNegKey, kNegKey, kNegKey};
+  for (int e = tid; e < kS4Ring * kS4Pos; e += NT)
+    (&sm.ring[0][0])[e] = i32x4{kNegKey, kNegKey, kNegKey, kNegKey};
+  for (int e = tid; e < kS4Ring * kS4Up; e += NT) (&sm.up[0][0])[e] = kNegKey;
   if (tid == 0) sm.late = sm.pause = 0;
   s4_barrier();
   const int total = s4_steps(sd, B1, B2);
