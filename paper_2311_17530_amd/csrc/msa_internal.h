@@ -140,6 +140,18 @@ struct WaitClock {
   }
 };
 
+// Readies the control block for the next launch on this workspace (one lane
+// of the kernel that ends an alignment).
+__device__ __forceinline__ void finish_launch(Ctrl *ctrl) {
+  ctrl->head = 0;
+  ctrl->status = 0;
+  ctrl->best = INT64_MIN;
+  ctrl->epoch = ctrl->epoch + 1;
+  // a streaming k = 4 fill's tag is not used again until every other one was
+  ctrl->sweeps = ctrl->sweeps + ctrl->swept;
+  ctrl->swept = 0;
+}
+
 // Alignment mode bits (same values as MSA_END_GAPS_FREE / MSA_COOPTIMAL in
 // the C ABI).
 constexpr int32_t kEndGapsFree = 1;
@@ -188,6 +200,11 @@ constexpr int kNoMaxTotal = 4096;
 // its stack of masks (one per column, at most sum n_i) in LDS.
 constexpr int kCoMaxK = 3;
 constexpr int kCoMaxTotal = 32768;
+
+// Traceback by several walkers (msa_trace.hip): k <= kTrMaxK, and the sum of
+// the lengths bounded by its LDS records.
+constexpr int kTrMaxK = 5;
+constexpr int kTrMaxTotal = 8191;
 
 // Streaming fill of k = 3 (msa_sweep3.hip): a workgroup owns kSwRows rows
 // (dimension 0) x 64 lanes (dimension 1) of lines along dimension 2 and

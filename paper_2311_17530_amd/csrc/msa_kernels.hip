@@ -979,18 +979,6 @@ __global__ __launch_bounds__(NT) void fill_kernel(JobDev jd, Ctrl *ctrl,
   }
 }
 
-// Readies the control block for the next launch on this workspace (one lane
-// of the kernel that ends an alignment).
-__device__ __forceinline__ void finish_launch(Ctrl *ctrl) {
-  ctrl->head = 0;
-  ctrl->status = ST_OK;
-  ctrl->best = INT64_MIN;
-  ctrl->epoch = ctrl->epoch + 1;
-  // a streaming k = 4 fill's tag is not used again until every other one was
-  ctrl->sweeps = ctrl->sweeps + ctrl->swept;
-  ctrl->swept = 0;
-}
-
 // ---------------------------------------------------------------------------
 // Traceback: one workgroup of one wave.
 // ---------------------------------------------------------------------------
@@ -1963,6 +1951,7 @@ int launch_fill(const JobDev &jd, Ctrl *ctrl, const int32_t *order, int grid, in
 }
 
 int launch_traceback(const JobDev &jd, Ctrl *ctrl, hipStream_t s) {
+  if (jd.k <= kTrMaxK && jd.total_len <= kTrMaxTotal) return launch_trace(jd, ctrl, s);
   MSA_DISPATCH_K(jd.k, launch_traceback_k, jd, ctrl, s);
 }
 

@@ -204,12 +204,15 @@ void make_sweep4_order(const Plan &p, std::vector<int32_t> *order) {
       for (int b2 = 0; b2 < nb2; ++b2) (*order)[count[key(b0, b1, b2)]++] = b++;
 }
 
-// The streaming k = 3 fill covers the plain and the end-gap-free modes.
+// The streaming k = 3 fill covers the plain mode and one of the end-gap-free,
+// co-optimal and near-optimal ones.
 bool sweep3_eligible(const Plan &p, int alpha, int32_t flags) {
   // the loader keeps each exchange element's offset within its window of
   // n2 + 1 steps as 32 bits: n2 steps of n1 + 1 (X0) or n0 + 1 (X1) words
   const int64_t wmax = (int64_t)p.n[2] * ((int64_t)std::max(p.n[0], p.n[1]) + 1);
-  return p.k == 3 && (flags & ~kEndGapsFree) == 0 && alpha >= 1 && alpha <= kSwSubMax &&
+  const bool mode =
+      flags == 0 || flags == kEndGapsFree || flags == kCoOptimal || flags == kNearOpt;
+  return p.k == 3 && mode && alpha >= 1 && alpha <= kSwSubMax &&
          p.n[2] <= kSwSeqMax && wmax < ((int64_t)1 << 31);
 }
 

@@ -63,8 +63,8 @@ std::vector<int32_t> sweep4_key_counts(const Plan &p);
 // Its blocks in an order in which each follows its lower neighbours.
 void make_sweep4_order(const Plan &p, std::vector<int32_t> *order);
 
-// The streaming k = 3 fill runs the plain mode (flags 0) of a k = 3 plan
-// whose alphabet and third sequence fit its LDS tables.
+// The streaming k = 3 fill runs k = 3 plans whose alphabet and third sequence
+// fit its LDS tables, in every mode but the pruned one.
 bool sweep3_eligible(const Plan &p, int alpha, int32_t flags);
 
 constexpr int64_t kSubBytes = 255 * 255;

@@ -12,6 +12,8 @@ namespace msa {
 int launch_fill(const JobDev &jd, Ctrl *ctrl, const int32_t *order, int grid, int pass,
                 hipStream_t s);
 int launch_traceback(const JobDev &jd, Ctrl *ctrl, hipStream_t s);
+// the same by several walkers (msa_trace.hip): k <= kTrMaxK, sum n_i <= kTrMaxTotal
+int launch_trace(const JobDev &jd, Ctrl *ctrl, hipStream_t s);
 int launch_export(const JobDev &jd, const Ctrl *ctrl, uint8_t *out, int64_t ncell,
                   hipStream_t s);
 int launch_nearopt(const JobDev &jd, Ctrl *ctrl, int64_t delta, int32_t max_paths,

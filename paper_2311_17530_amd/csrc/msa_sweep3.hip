@@ -85,7 +85,7 @@ struct Sweep3Dev {
   int32_t ts0, ts1;           // tile strides of dimensions 0 and 1 (dimension 2: 1)
   int64_t *score_out;
   int64_t *trace;             // debug builds: 8 words per workgroup ticket
-  int32_t egf;                // end-gap-free mode
+  int32_t *scores;            // near-optimal mode: every cell's score, laid out as dir
   int64_t *best;              // end-gap-free: max of (score << 32 | row-major
                               // cell index) over the far faces
 };
@@ -273,13 +273,18 @@ struct SwLoader {
 // workgroup (0, 0), whose top row's lane 0 holds the origin.  kEgf:
 // end-gap-free mode (Section 2's reading of free end gaps): every cell with
 // some v_i = 0 scores 0 with no decision, and the best far-face cell is
-// reported.
-template <bool kX0, bool kX1, bool kOrigin, bool kEgf>
+// reported.  kTies: co-optimal mode: a cell's byte is its tie set, bit b - 1 for
+// every mask b whose candidate reaches the maximum (the origin's is 0).
+// kScores: near-optimal mode: the cells' scores are stored as well, four
+// consecutive cells of a line at a time.
+enum SwMode { kSwPlain = 0, kSwEgf = 1, kSwTies = 2, kSwScores = 3 };
+template <bool kX0, bool kX1, bool kOrigin, int kMode>
 __device__ __forceinline__ void sweep_row(const Sweep3Dev &sd, SwSmem &sm, int B0, int B1, int w,
                                           int j, const bool (&ok)[kSwRPW],
                                           const int (&r0)[kSwRPW], int r1, int gap, int tag,
                                           int total, bool cw, int sc, int uc, int jc) {
   constexpr int R = kSwRPW;
+  constexpr bool kEgf = kMode == kSwEgf, kTies = kMode == kSwTies, kScores = kMode == kSwScores;
   const int v0top = B0 * kSwRows + R * w;
   const int v1 = B1 * kSwLanes + j;
   const int g16 = gap * 16;  // (gap * 2 column pairs) << 3
@@ -290,6 +295,7 @@ __device__ __forceinline__ void sweep_row(const Sweep3Dev &sd, SwSmem &sm, int B
   const int32_t *sub0[R];
   uint8_t *dline[R];
   uint8_t *stage[R];
+  int32_t *sline[R];
 #pragma unroll
   for (int u = 0; u < R; ++u) {
     const int v0 = v0top + u;
@@ -300,6 +306,7 @@ __device__ __forceinline__ void sweep_row(const Sweep3Dev &sd, SwSmem &sm, int B
     const int c0 = v0 == 0 ? 0 : (v0 - 1) / kSwT + 1, q0 = v0 == 0 ? 0 : (v0 - 1) % kSwT;
     dline[u] =
         sd.dir + ((int64_t)c0 * sd.ts0 + (int64_t)c1 * sd.ts1) * kSwDbs + (q0 * kSwT + q1) * kSwT;
+    if constexpr (kScores) sline[u] = sd.scores + (dline[u] - sd.dir);
     stage[u] = &sm.stage[R * w + u][j][0];
   }
   // rows of the wave above: the loader's in0 for wave 0, else the ring
@@ -351,6 +358,13 @@ __device__ __forceinline__ void sweep_row(const Sweep3Dev &sd, SwSmem &sm, int B
     hl[u] = u < R - 1 ? sm.h0[kSwRing - 1][w][u] : sm.ring[kSwRing - 1][w][0];
   }
   int32_t b5 = kNegKey, b7 = kNegKey;
+  int32_t hist[kScores ? R : 1][4];  // the scores of the last four steps, by step % 4
+  if constexpr (kScores) {
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+#pragma unroll
+      for (int x = 0; x < 4; ++x) hist[u][x] = 0;
+  }
   // pair scores of the third residue one step ahead (they do not depend on
   // the scores), and its code two steps ahead; s2_j[s] is the residue of t
   const uint8_t *s2_j = sm.s2 + kSwSeqPad - 1 - jw;
@@ -422,6 +436,18 @@ __device__ __forceinline__ void sweep_row(const Sweep3Dev &sd, SwSmem &sm, int B
           out[u] = (ok[u] && in_t) ? (bst & ~7) : kNegKey;
         else
           out[u] = bst & ~7;
+        if constexpr (kTies) {
+          // every candidate at or above the maximal score: the signs of the
+          // differences, from mask 7 down, give the complement of the set
+          const int32_t cs[7] = {a1 + K1, c2, c3, c4, c5, c6, c7};
+          uint32_t miss = 0;
+#pragma unroll
+          for (int b = 6; b >= 0; --b)
+            miss = __builtin_amdgcn_alignbit(miss, (uint32_t)cs[b] - (uint32_t)out[u], 31);
+          best[u] = (int32_t)(miss ^ 0x7Fu);
+          if constexpr (kOrigin)
+            if (u == 0) best[u] = (j == 0 && t == 0) ? 0 : best[u];
+        }
       }
       if constexpr (kEgf) {
         if (wfar || (unsigned)(s - w - n2) < 64u) {
@@ -434,6 +460,23 @@ __device__ __forceinline__ void sweep_row(const Sweep3Dev &sd, SwSmem &sm, int B
         }
       }
       sm.ring[i & (kSwRing - 1)][w][j + 1] = out[R - 1];
+      if constexpr (kScores) {
+        // cells t - 3 .. t end at a multiple of 4: one aligned quarter of a
+        // run (cells past n2 fall in the last run's unused tail)
+        const bool quad = (t & 3) == 0 && t > 0 && t - 3 <= n2;
+        const int64_t at = (int64_t)((t + 15) >> 4) * kSwDbs + ((t - 4) & 15);
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+          hist[u][i & 3] = out[u] >> 3;
+          if (ok[u]) {
+            if (quad)
+              *reinterpret_cast<int4 *>(sline[u] + at) =
+                  make_int4(hist[u][(i + 1) & 3], hist[u][(i + 2) & 3], hist[u][(i + 3) & 3],
+                            hist[u][i & 3]);
+            if (t == 0) sline[u][0] = out[u] >> 3;  // its own block
+          }
+        }
+      }
       // direction bytes of cell t at (t - 1) mod 32 (see the flush below)
 #pragma unroll
       for (int u = 0; u < R; ++u) stage[u][(t - 1) & 31] = (uint8_t)best[u];
@@ -507,7 +550,7 @@ __device__ __forceinline__ void sweep_row(const Sweep3Dev &sd, SwSmem &sm, int B
 }
 
 // The wave's variant: exchange stores (x0, x1) and the origin.
-template <bool kEgf>
+template <int kMode>
 __device__ __forceinline__ void sweep_rows(const Sweep3Dev &sd, SwSmem &sm, int B0, int B1,
                                            int w, int j, const bool (&ok)[kSwRPW],
                                            const int (&r0)[kSwRPW], int r1, int gap, int tag,
@@ -516,22 +559,23 @@ __device__ __forceinline__ void sweep_rows(const Sweep3Dev &sd, SwSmem &sm, int 
 #define MSA_SW_ARGS sd, sm, B0, B1, w, j, ok, r0, r1, gap, tag, total, cw, sc, uc, jc
   if (B0 == 0 && B1 == 0 && w == 0) {
     if (x1)
-      sweep_row<false, true, true, kEgf>(MSA_SW_ARGS);
+      sweep_row<false, true, true, kMode>(MSA_SW_ARGS);
     else
-      sweep_row<false, false, true, kEgf>(MSA_SW_ARGS);
+      sweep_row<false, false, true, kMode>(MSA_SW_ARGS);
   } else if (x0 && x1)
-    sweep_row<true, true, false, kEgf>(MSA_SW_ARGS);
+    sweep_row<true, true, false, kMode>(MSA_SW_ARGS);
   else if (x0)
-    sweep_row<true, false, false, kEgf>(MSA_SW_ARGS);
+    sweep_row<true, false, false, kMode>(MSA_SW_ARGS);
   else if (x1)
-    sweep_row<false, true, false, kEgf>(MSA_SW_ARGS);
+    sweep_row<false, true, false, kMode>(MSA_SW_ARGS);
   else
-    sweep_row<false, false, false, kEgf>(MSA_SW_ARGS);
+    sweep_row<false, false, false, kMode>(MSA_SW_ARGS);
 #undef MSA_SW_ARGS
 }
 
 }  // namespace
 
+template <int kMode>
 __global__ __launch_bounds__(kSwThreads) void sweep3_kernel(Sweep3Dev sd, Ctrl *ctrl) {
   __shared__ SwSmem sm;
   const int tid = threadIdx.x;
@@ -585,7 +629,8 @@ __global__ __launch_bounds__(kSwThreads) void sweep3_kernel(Sweep3Dev sd, Ctrl *
   // exchange values it skips.  (Every wave and the loader take the same count.)
   const int jmax = min(kSwLanes - 1, sd.n1 - B1 * kSwLanes);
   const int wmax = min(kSwNW - 1, (sd.n0 - B0 * kSwRows) / kSwRPW);
-  const int nsteps = sd.n2 + 1 + jmax + wmax;
+  // (near-optimal mode: up to the end of the last four cells)
+  const int nsteps = (kMode == kSwScores ? (sd.n2 + 3) / 4 * 4 : sd.n2) + 1 + jmax + wmax;
   const int total = (nsteps + kSwUnroll - 1) / kSwUnroll * kSwUnroll;
 
   if (wave == kSwNW) {
@@ -667,10 +712,7 @@ __global__ __launch_bounds__(kSwThreads) void sweep3_kernel(Sweep3Dev sd, Ctrl *
   const int sc = sd.n2 + jc + w;
   const int uc = rc % kSwRPW;
   sw_barrier();  // the loader's halo of steps -1 and 0 is in LDS
-  if (sd.egf)
-    sweep_rows<true>(sd, sm, B0, B1, w, j, ok, r0, r1, gap, tag, total, x0, x1, cw, sc, uc, jc);
-  else
-    sweep_rows<false>(sd, sm, B0, B1, w, j, ok, r0, r1, gap, tag, total, x0, x1, cw, sc, uc, jc);
+  sweep_rows<kMode>(sd, sm, B0, B1, w, j, ok, r0, r1, gap, tag, total, x0, x1, cw, sc, uc, jc);
 }
 
 int launch_sweep3(const Plan &p, char *ws, const JobDev &jd, Ctrl *ctrl, int32_t flags,
@@ -694,7 +736,7 @@ int launch_sweep3(const Plan &p, char *ws, const JobDev &jd, Ctrl *ctrl, int32_t
   sd.ts1 = p.tstride[1];
   sd.score_out = jd.score_out;
   sd.trace = jd.trace;
-  sd.egf = (flags & kEndGapsFree) != 0;
+  sd.scores = jd.scores;
   sd.best = &ctrl->best;
   // One workgroup per CU: a second one would share the SIMDs and stretch the
   // steps of both, and every step sits on the sweep's critical path.  The
@@ -710,7 +752,11 @@ int launch_sweep3(const Plan &p, char *ws, const JobDev &jd, Ctrl *ctrl, int32_t
   }
   const int grid = p.sw_nb0 * p.sw_nb1;
   launch_begin();
-  hipLaunchKernelGGL(sweep3_kernel, dim3(grid), dim3(kSwThreads), pad, s, sd, ctrl);
+  auto *kernel = flags & kEndGapsFree ? sweep3_kernel<kSwEgf>
+                 : flags & kCoOptimal ? sweep3_kernel<kSwTies>
+                 : flags & kNearOpt   ? sweep3_kernel<kSwScores>
+                                      : sweep3_kernel<kSwPlain>;
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(kSwThreads), pad, s, sd, ctrl);
   return launch_end();
 }
 

@@ -1,0 +1,562 @@
+// msa_trace.hip -- traceback by several walkers, and the co-optimal list built
+// on it.
+//
+// The walk from the far corner (Section 2) is a chain of dependent reads, one
+// per column: a single wave took 0.13 us a column and 0.5 us a tile crossing.
+// But the walk from a cell depends on the cell alone, so two walks that meet in
+// a cell are one walk from there on, and walks that start near an optimal path
+// meet it soon.  So one workgroup walks the alignment in pieces at once: wave
+// 0 from the end cell, the others from guessed cells on the way to the origin.
+// Cells are told apart by their coordinate sum h, which every step lowers.  A
+// guessed walker owns the sums from its start down to the next guess's, where
+// it records its cells and masks by h; below, it compares its cell with the
+// next owner's record at the same h and stops when they are equal.  The
+// alignment is the end cell's walk up to its meeting with a guessed walk, that
+// one's up to its meeting with the next, and so on.  A walk that met nobody
+// within the next range is continued by wave 0 alone, so the result is the
+// single walk's whatever the guesses were worth.
+//
+// The guesses lie on the straight line to the origin; where the lengths are
+// far apart (a path of such sequences runs along the diagonal and has its
+// gaps at one end), on three lines: the straight one, the diagonal from the
+// origin and the diagonal from the end cell, each a family with ranges and
+// records of its own, and wave 0 watches for all of them.
+//
+// What bounds it: the latency of a tile crossing (a walker waits 1 to 2 us for
+// the next tile's directions, at every fourth column or so) times the columns
+// of the longest piece.  Measured, single walk and now: 512^3 129 and 27 us,
+// 128^4 58 and 23, 40^5 60 and 15, 40^3 16 and 13, 157 x 93 x 201 46 and 36.
+// Co-optimal alignments (co-optimal mode, k <= 3): the depth-first enumeration
+// takes at every new cell the lowest mask of its tie set, so below a cell of
+// the first alignment (the one the walkers found) a new alignment goes on like
+// the first one.  Only the columns between a tie and the meeting are walked;
+// the rest of the stack is copied.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "msa_internal.h"
+#include "msa_runtime.h"
+
+namespace msa {
+
+namespace {
+
+enum { ST_OK = 0, ST_EINVAL = -1, ST_EDEVICE = -4 };
+
+constexpr int kTrWalkers = 16;
+constexpr int kTrThreads = kTrWalkers * 64;
+
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+template <int K>
+struct TrCfg {
+  static constexpr int T = tile_edge_for_k(K);
+  static constexpr int M = (1 << K) - 1;
+  static constexpr int DBS = (ipow(T, K) + 15) / 16 * 16;
+  static constexpr int dstride(int i) { return ipow(T, K - 1 - i); }
+};
+
+// How a walk ended.
+enum { kTrMerged = 0, kTrOpen = 1, kTrEnd = 2, kTrBad = 3 };
+
+constexpr int kTrFam = 3;  // families of guesses
+// LDS bytes of the records: per sum and family a cell (8 bytes), the owner's
+// mask and the overlap's, and per sum the path's mask.
+constexpr int kTrRec = 92 * 1024;
+constexpr int tr_rec_bytes(int fam, int total) { return (total + 1) * (10 * fam + 1); }
+static_assert(tr_rec_bytes(1, kTrMaxTotal) <= kTrRec, "records of one family fit");
+
+template <int K>
+struct TrSmem {
+  alignas(16) uint8_t dirb[kTrWalkers][TrCfg<K>::DBS];  // each walker's tile
+  alignas(16) uint8_t rec[kTrRec];
+  int32_t state[kTrWalkers], hstop[kTrWalkers], hstart[kTrWalkers];
+  int32_t vstop[kTrWalkers][K];
+  int32_t hend, status;
+  int32_t seg[kTrWalkers][3], ns;  // the path's stretches: lowest and highest walker, first sum
+  int32_t done, never;  // the path is known; 0 for wave 0's own walks
+  int32_t vend[K];  // the walk's last cell
+  int32_t cnt[kTrWalkers][K + 1];
+};
+
+// The records of families f < F for sums 0 .. H.
+struct TrRec {
+  uint64_t *pos;  // [f][h]: the owner's cell (v_0 .. v_{k-2}, 16 bits each)
+  uint8_t *own;   // [f][h]: its mask there (0: it has no cell with that sum)
+  uint8_t *ov;    // [f][h]: the mask of the walker from the range above
+  uint8_t *path;  // [h]: the path's mask
+  int n;          // H + 1
+  template <int K>
+  __device__ __forceinline__ TrRec(TrSmem<K> &sm, int F, int H) : n(H + 1) {
+    pos = reinterpret_cast<uint64_t *>(sm.rec);
+    own = sm.rec + (size_t)F * n * 8;
+    ov = own + F * n;
+    path = ov + F * n;
+  }
+};
+
+// One walk from cell v (sum h), wave-uniform.  Above sum h_own it records its
+// cells and masks in family `fam`; from there down it watches the families f0
+// .. f0 + nf - 1, writes its masks to `to` and stops where it meets one (met),
+// or at a sum h_stop or less (-1: never), or at a tile's entry once `done` is
+// set.  On return v, h is the cell where it stopped.
+template <int K, bool egf, bool coopt>
+__device__ int tr_walk(const JobDev &jd, const TrRec &rc, uint8_t *dirb, int (&v)[K], int &h,
+                       int h_own, int h_stop, int fam, int f0, int nf, uint8_t *to, int &met,
+                       const int32_t &done) {
+  using C = TrCfg<K>;
+  constexpr int T = C::T;
+  constexpr int M = C::M;
+  constexpr int NQ = C::DBS / 16;      // 16-byte chunks per direction block
+  constexpr int CPL = (NQ + 63) / 64;  // chunks per lane
+  const int lane = threadIdx.x & 63;
+  u32x4 *const lds4 = reinterpret_cast<u32x4 *>(dirb);
+  int c[K], q[K];
+  int64_t t = 0;
+  {
+    bool all = true, any = false;
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      all = all && v[i] == 0;
+      any = any || v[i] == 0;
+      c[i] = v[i] == 0 ? 0 : (v[i] - 1) / T + 1;
+      t += (int64_t)c[i] * jd.tstride[i];
+    }
+    if (egf ? any : all) return kTrEnd;
+  }
+  {
+    const u32x4 *src = reinterpret_cast<const u32x4 *>(jd.dir + t * C::DBS);
+    for (int idx = lane; idx < NQ; idx += 64) lds4[idx] = src[idx];
+  }
+  u32x4 pf[K][CPL];
+  // Per lane l, what a step by mask l subtracts: of the byte offset in the
+  // tile, of the cell packed in two words, of the tile position packed with a
+  // guard bit per dimension (cleared when the position leaves the tile) and of
+  // h.  A step reads them by readlane instead of forming them bit by bit.
+  constexpr int QW = K == 5 ? 6 : 8;  // bits per packed tile position
+  static_assert(K * QW <= 32 && T <= 1 << (QW - 1), "packed tile positions");
+  uint32_t guards = 0;
+#pragma unroll
+  for (int i = 0; i < K; ++i) guards |= 1u << (QW * i + QW - 1);
+  int loff = 0, lh = 0;
+  uint32_t llo = 0, lhi = 0, lq = 0;
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    const uint32_t bit = (uint32_t)(lane & M) >> i & 1u;
+    loff += (int)bit * C::dstride(i);
+    lh += (int)bit;
+    lq |= bit << (QW * i);
+    if (i < K - 1) (i < 2 ? llo : lhi) |= bit << (16 * (i & 1));
+  }
+  // the watched records of sums w0 - lane, read again every kTrWin sums (an
+  // owner may be writing them: what is not there yet is no meeting)
+  constexpr int kTrWin = 16;
+  uint32_t wlo[kTrFam], whi[kTrFam];
+  int w0 = INT32_MAX;
+  for (;;) {
+    if (h <= h_own && h > 0 && __hip_atomic_load(&done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
+      return kTrOpen;  // the path is known without this walk
+    int d = 0;
+    uint32_t Q = guards, plo = 0, phi = 0;
+    int base[K];
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      base[i] = c[i] == 0 ? 0 : (c[i] - 1) * T + 1;
+      q[i] = v[i] - base[i];
+      d += q[i] * C::dstride(i);
+      Q |= (uint32_t)q[i] << (QW * i);
+      if (i < K - 1) (i < 2 ? plo : phi) |= (uint32_t)v[i] << (16 * (i & 1));
+    }
+    // prefetch the face neighbours' blocks (an absent neighbour: this tile's)
+#pragma unroll
+    for (int s = 0; s < K; ++s) {
+      const int64_t tn = c[s] > 0 ? t - jd.tstride[s] : t;
+      const u32x4 *src = reinterpret_cast<const u32x4 *>(jd.dir + tn * C::DBS);
+#pragma unroll
+      for (int x = 0; x < CPL; ++x) {
+        const int idx = lane + x * 64;
+        pf[s][x] = src[idx < NQ ? idx : NQ - 1];
+      }
+    }
+    // Each lane reads one candidate next byte, so that a step's byte is a
+    // register read of what was loaded a step earlier.  (The end of the walk,
+    // a cell with v_i = 0, lies in a tile of its own: no test here.)
+    int cand = dirb[max(d - loff, 0)];
+    int byte = __builtin_amdgcn_readlane(cand, 0);
+    int how = -1;
+    for (;;) {
+      if (h <= h_own) {
+        if (h <= h_stop) {
+          how = kTrOpen;
+          break;
+        }
+        if (w0 - h >= kTrWin) {
+          w0 = h;
+#pragma unroll
+          for (int f = 0; f < kTrFam; ++f) {
+            const uint64_t r = f < nf ? rc.pos[(f0 + f) * rc.n + max(h - lane, 0)] : ~0ull;
+            wlo[f] = (uint32_t)r;
+            whi[f] = (uint32_t)(r >> 32);
+          }
+        }
+        uint64_t eq = 0;
+        int mf = 0;
+#pragma unroll
+        for (int f = kTrFam - 1; f >= 0; --f) {
+          const uint64_t e = __ballot(lane == w0 - h && wlo[f] == plo && whi[f] == phi);
+          mf = e ? f : mf;
+          eq |= e;
+        }
+        if (eq) {
+          met = f0 + mf;
+          how = kTrMerged;
+          break;
+        }
+      }
+      int b;
+      if constexpr (coopt) {  // the lowest mask of the tie set
+        const int ties = byte & ((1 << M) - 1);
+        b = ties ? __builtin_ctz(ties) + 1 : 0;
+      } else {
+        b = M - (byte & M);
+      }
+      if (b == 0) {  // a cell without a move: corrupt decision data
+        how = kTrBad;
+        break;
+      }
+      byte = __builtin_amdgcn_readlane(cand, b);
+      d -= __builtin_amdgcn_readlane(loff, b);
+      cand = dirb[max(d - loff, 0)];
+      if (h > h_own) {  // (every lane stores the same values)
+        rc.pos[fam * rc.n + h] = ((uint64_t)phi << 32) | plo;
+        rc.own[fam * rc.n + h] = (uint8_t)b;
+      } else {
+        to[h] = (uint8_t)b;
+      }
+      Q -= __builtin_amdgcn_readlane(lq, b);
+      plo -= __builtin_amdgcn_readlane(llo, b);
+      if constexpr (K > 3) phi -= __builtin_amdgcn_readlane(lhi, b);
+      h -= __builtin_amdgcn_readlane(lh, b);
+      if ((Q & guards) != guards) break;  // left the tile
+    }
+    bool allz = true, anyz = false, bad = false;
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      v[i] = base[i] + (int)((Q >> (QW * i)) & ((1u << QW) - 1)) - (1 << (QW - 1));
+      bad = bad || v[i] < 0;  // a step below v_i = 0: corrupt decision data
+      allz = allz && v[i] == 0;
+      anyz = anyz || v[i] == 0;
+    }
+    if (how >= 0) return how;
+    if (bad) return kTrBad;
+    if (egf ? anyz : allz) return kTrEnd;
+    int S = 0;
+    t = 0;
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      const int ci = v[i] == 0 ? 0 : (v[i] - 1) / T + 1;
+      if (ci != c[i]) S |= 1 << i;
+      c[i] = ci;
+      t += (int64_t)ci * jd.tstride[i];
+    }
+    bool hit = false;
+#pragma unroll
+    for (int s = 0; s < K; ++s) {
+      if (S == 1 << s) {
+#pragma unroll
+        for (int x = 0; x < CPL; ++x) {
+          const int idx = lane + x * 64;
+          if (idx < NQ) lds4[idx] = pf[s][x];
+        }
+        hit = true;
+      }
+    }
+    if (!hit) {
+      const u32x4 *src = reinterpret_cast<const u32x4 *>(jd.dir + t * C::DBS);
+      for (int idx = lane; idx < NQ; idx += 64) lds4[idx] = src[idx];
+    }
+  }
+}
+
+// Guess g of G (0: the origin, G: the end cell) of family f.
+template <int K>
+__device__ __forceinline__ int tr_guess(const int (&end)[K], int most, int f, int g, int G,
+                                        int (&v)[K]) {
+  int h = 0;
+  const int up = (int)((int64_t)most * g / G), down = (int)((int64_t)most * (G - g) / G);
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    v[i] = f == 0 ? (int)((int64_t)end[i] * g / G) : f == 1 ? min(end[i], up) : max(0, end[i] - down);
+    h += v[i];
+  }
+  return h;
+}
+
+// Families of guesses for an end cell with coordinate sum H: one where the
+// lengths are within a sixteenth of the longest, or where three families'
+// records do not fit.  (Traceback with one family and with three: 512^3 38 and
+// 50 us, 300 x 257 x 281 51 and 42, 401 x 365 x 512 114 and 85, 157 x 93 x 201 63
+// and 39.)
+template <int K>
+__device__ __forceinline__ int tr_families(const int (&end)[K], int &H) {
+  int most = 0, least = INT32_MAX;
+  H = 0;
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    most = max(most, end[i]);
+    least = min(least, end[i]);
+    H += end[i];
+  }
+  return 16 * (most - least) <= most || most < 24 || tr_rec_bytes(kTrFam, H) > kTrRec ? 1 : kTrFam;
+}
+
+// The walk from cell end[] by all waves of the workgroup: sm.status, sm.vend
+// and sm.hend (its last cell) and rc.path[h], the mask of its cell with sum
+// h (0: none), for every sum above hend.
+template <int K, bool egf, bool coopt>
+__device__ void tr_walk_all(const JobDev &jd, TrSmem<K> &sm, const int (&end)[K], const TrRec &rc,
+                            int F) {
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid) >> 6;
+  const int H = rc.n - 1;
+  int most = 0;
+#pragma unroll
+  for (int i = 0; i < K; ++i) most = max(most, end[i]);
+  // G guesses a family, the last of them the end cell: strictly ascending sums
+  // (the longest dimension rises at each), and at least 4 cells apart
+  const int G = max(1, min(1 + (kTrWalkers - 1) / F, most / 4));
+  for (int x = tid; x < F * rc.n; x += kTrThreads) {
+    rc.pos[x] = ~0ull;
+    rc.own[x] = 0;
+    rc.ov[x] = 0;
+  }
+  for (int x = tid; x < rc.n; x += kTrThreads) rc.path[x] = 0;
+  if (tid < kTrWalkers) sm.state[tid] = -1;
+  if (tid == 0) sm.done = sm.never = sm.ns = 0;
+  __syncthreads();
+  int v[K], h = 0, met = 0;
+  // (the sums of all guesses are known to wave 0 before it looks)
+  if (wave > 0 && wave <= F * (G - 1))
+    sm.hstart[wave] =
+        tr_guess<K>(end, most, (wave - 1) / (G - 1), (wave - 1) % (G - 1) + 1, G, v);
+  __syncthreads();
+  if (wave > 0 && wave <= F * (G - 1)) {
+    const int f = (wave - 1) / (G - 1), g = (wave - 1) % (G - 1) + 1;
+    const int hp = g > 1 ? sm.hstart[wave - 1] : -1, hpp = g > 2 ? sm.hstart[wave - 2] : -1;
+    h = tr_guess<K>(end, most, f, g, G, v);
+    const int how = tr_walk<K, egf, coopt>(
+        jd, rc, sm.dirb[wave], v, h, __builtin_amdgcn_readfirstlane(hp),
+        __builtin_amdgcn_readfirstlane(hpp), f, f, 1, rc.ov + f * rc.n, met, sm.done);
+    sm.hstop[wave] = h;
+#pragma unroll
+    for (int i = 0; i < K; ++i) sm.vstop[wave][i] = v[i];
+    __hip_atomic_store(&sm.state[wave], how, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+  } else if (wave == 0) {
+#pragma unroll
+    for (int i = 0; i < K; ++i) v[i] = end[i];
+    h = H;
+    int how = tr_walk<K, egf, coopt>(jd, rc, sm.dirb[0], v, h, H, -1, 0, 0, G > 1 ? F : 0, rc.path,
+                                     met, sm.never);
+    // From a meeting the path goes down the family's walkers, each up to its own
+    // meeting with the next, to the first that met nobody: as soon as those
+    // walkers are done, the stretch is known.
+    int ns = 0;
+    while (how == kTrMerged) {
+      const int first = met * (G - 1) + 1;  // the family's lowest walker
+      const int st = lane < kTrWalkers ? sm.hstart[lane] : 0;
+      // the owner of sum h: the lowest walker of the family that starts at h or above
+      const uint64_t from =
+          __ballot(lane >= first && lane < first + G - 1 && lane < kTrWalkers && st >= h);
+      const int o = (int)__builtin_ctzll(from);
+      uint64_t stay;  // of the walkers from the lowest to o: those that met nobody
+      for (;;) {
+        const int x = lane >= first && lane <= o
+                          ? __hip_atomic_load(&sm.state[lane], __ATOMIC_ACQUIRE,
+                                              __HIP_MEMORY_SCOPE_WORKGROUP)
+                          : kTrMerged;
+        stay = __ballot(x != kTrMerged);
+        if (__ballot(x < 0) == 0) break;
+        __builtin_amdgcn_s_sleep(1);
+      }
+      const int low = 63 - __builtin_clzll(stay);  // (the lowest never meets anybody)
+      how = __builtin_amdgcn_readfirstlane(sm.state[low]);
+      sm.seg[ns][0] = low;
+      sm.seg[ns][1] = o;
+      sm.seg[ns][2] = h;
+      ++ns;
+      h = __builtin_amdgcn_readfirstlane(sm.hstop[low]);
+#pragma unroll
+      for (int i = 0; i < K; ++i) v[i] = __builtin_amdgcn_readfirstlane(sm.vstop[low][i]);
+      if (how == kTrOpen)  // go on alone until the walk meets someone
+        how = tr_walk<K, egf, coopt>(jd, rc, sm.dirb[0], v, h, H, -1, 0, 0, F, rc.path, met,
+                                     sm.never);
+    }
+    sm.ns = ns;
+    __hip_atomic_store(&sm.done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    sm.status = how == kTrEnd ? ST_OK : ST_EDEVICE;
+    sm.hend = h;
+#pragma unroll
+    for (int i = 0; i < K; ++i) sm.vend[i] = v[i];
+  }
+  __syncthreads();
+  // every walker of a stretch copies its part: its own sums from the meeting
+  // above it, and the ones below down to its meeting
+  for (int x = 0; x < sm.ns; ++x) {
+    const int low = sm.seg[x][0], top = sm.seg[x][1];
+    if (wave < low || wave > top) continue;
+    const int f = (wave - 1) / (G - 1), g = (wave - 1) % (G - 1) + 1;
+    const int hx = wave == top ? sm.seg[x][2] : sm.hstop[wave + 1];
+    const int hp = g > 1 ? sm.hstart[wave - 1] : 0, hpp = g > 2 ? sm.hstart[wave - 2] : 0;
+    const int h1 = max(sm.hstop[wave], hpp);
+    for (int y = max(h1, hp) + 1 + lane; y <= hx; y += 64) rc.path[y] = rc.own[f * rc.n + y];
+    for (int y = h1 + 1 + lane; y <= min(hp, hx); y += 64) rc.path[y] = rc.ov[f * rc.n + y];
+  }
+  __syncthreads();
+}
+
+// Rows of the alignment: unaligned prefixes (end gaps free; sequence 0 first),
+// the path's columns in ascending order of h, unaligned suffixes.
+template <int K>
+__device__ void tr_rows(const JobDev &jd, TrSmem<K> &sm, const int (&end)[K], const TrRec &rc) {
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid) >> 6;
+  int H = 0, pre = 0;
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    H += end[i];
+    pre += sm.vend[i];
+  }
+  const int hend = sm.hend;
+  // wave w takes the sums (w, w + 1] * per
+  const int per = (H + kTrThreads - 1) / kTrThreads * 64;
+  const int first = wave * per + 1, last = min(H, (wave + 1) * per);
+  int cnt[K + 1];  // columns, and columns with a residue of sequence i
+#pragma unroll
+  for (int i = 0; i <= K; ++i) cnt[i] = 0;
+  for (int h0 = first; h0 <= last; h0 += 64) {
+    const int m = h0 + lane <= last && h0 + lane > hend ? rc.path[h0 + lane] : 0;
+    cnt[K] += __builtin_popcountll(__ballot(m != 0));
+#pragma unroll
+    for (int i = 0; i < K; ++i) cnt[i] += __builtin_popcountll(__ballot((m >> i) & 1));
+  }
+#pragma unroll
+  for (int i = 0; i <= K; ++i) sm.cnt[wave][i] = cnt[i];
+  __syncthreads();
+  int at[K + 1], total = 0;
+#pragma unroll
+  for (int i = 0; i < K; ++i) at[i] = sm.vend[i];
+  at[K] = pre;
+  for (int w = 0; w < kTrWalkers; ++w) {
+#pragma unroll
+    for (int i = 0; i <= K; ++i) at[i] += w < wave ? sm.cnt[w][i] : 0;
+    total += sm.cnt[w][K];
+  }
+  const uint64_t below = (1ull << lane) - 1;
+  for (int h0 = first; h0 <= last; h0 += 64) {
+    const int m = h0 + lane <= last && h0 + lane > hend ? rc.path[h0 + lane] : 0;
+    const uint64_t cols = __ballot(m != 0);
+    const int64_t col = at[K] + __builtin_popcountll(cols & below);
+    at[K] += __builtin_popcountll(cols);
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      const uint64_t bits = __ballot((m >> i) & 1);
+      const int pos = at[i] + __builtin_popcountll(bits & below);
+      at[i] += __builtin_popcountll(bits);
+      if (m != 0)
+        jd.aln_out[(int64_t)i * jd.aln_cap + col] =
+            (m >> i) & 1 ? jd.seqs[jd.seq_off[i] + pos] : (uint8_t)0xFF;
+    }
+  }
+  // one-residue columns of the unaligned prefixes and suffixes
+  int64_t c0 = 0, c1 = pre + total;
+#pragma unroll
+  for (int s = 0; s < K; ++s) {
+    for (int x = tid; x < sm.vend[s]; x += kTrThreads)
+#pragma unroll
+      for (int i = 0; i < K; ++i)
+        jd.aln_out[(int64_t)i * jd.aln_cap + c0 + x] =
+            i == s ? jd.seqs[jd.seq_off[s] + x] : (uint8_t)0xFF;
+    c0 += sm.vend[s];
+    for (int x = tid; x < jd.n[s] - end[s]; x += kTrThreads)
+#pragma unroll
+      for (int i = 0; i < K; ++i)
+        jd.aln_out[(int64_t)i * jd.aln_cap + c1 + x] =
+            i == s ? jd.seqs[jd.seq_off[s] + end[s] + x] : (uint8_t)0xFF;
+    c1 += jd.n[s] - end[s];
+  }
+  if (tid == 0) *jd.aln_len_out = c1;
+}
+
+template <int K, bool egf, bool coopt>
+__device__ void tr_job(const JobDev &jd, TrSmem<K> &sm, int status, int64_t best) {
+  int end[K];
+  if constexpr (egf) {  // the end cell from its row-major index
+    int64_t lin = (int64_t)(uint32_t)best;
+#pragma unroll
+    for (int i = K - 1; i >= 0; --i) {
+      end[i] = (int)(lin % ((int64_t)jd.n[i] + 1));
+      lin /= (int64_t)jd.n[i] + 1;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < K; ++i) end[i] = jd.n[i];
+  }
+  if (status == ST_OK) {
+    int H = 0;
+    const int F = tr_families<K>(end, H);
+    const TrRec rc(sm, F, H);
+    tr_walk_all<K, egf, coopt>(jd, sm, end, rc, F);
+    status = sm.status;
+    if (status == ST_OK) tr_rows<K>(jd, sm, end, rc);
+  }
+  if (threadIdx.x == 0) {
+    *jd.status_out = status;
+    if (status != ST_OK) {
+      *jd.aln_len_out = 0;
+      *jd.score_out = 0;
+    } else if (egf) {
+      *jd.score_out = best >> 32;
+    }
+  }
+}
+
+}  // namespace
+
+template <int K>
+__global__ __launch_bounds__(kTrThreads) void trace_kernel(JobDev jd, Ctrl *ctrl) {
+  __shared__ TrSmem<K> sm;
+  const int mode = __builtin_amdgcn_readfirstlane(ctrl->flags);
+  const int st = __builtin_amdgcn_readfirstlane(
+      __hip_atomic_load(&ctrl->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  if (mode & kEndGapsFree) {
+    tr_job<K, true, false>(
+        jd, sm, st, __hip_atomic_load(&ctrl->best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  } else if (mode & kCoOptimal) {
+    if constexpr (K <= kCoMaxK) tr_job<K, false, true>(jd, sm, st, 0);
+  } else {
+    tr_job<K, false, false>(jd, sm, st, 0);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) finish_launch(ctrl);
+}
+
+template <int K>
+static int launch_trace_k(const JobDev &jd, Ctrl *ctrl, hipStream_t s) {
+  launch_begin();
+  hipLaunchKernelGGL((trace_kernel<K>), dim3(1), dim3(kTrThreads), 0, s, jd, ctrl);
+  return launch_end();
+}
+
+int launch_trace(const JobDev &jd, Ctrl *ctrl, hipStream_t s) {
+  switch (jd.k) {
+    case 2: return launch_trace_k<2>(jd, ctrl, s);
+    case 3: return launch_trace_k<3>(jd, ctrl, s);
+    case 4: return launch_trace_k<4>(jd, ctrl, s);
+    case 5: return launch_trace_k<5>(jd, ctrl, s);
+    default: return -1;
+  }
+}
+
+}  // namespace msa
