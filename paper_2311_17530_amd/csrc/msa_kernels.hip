@@ -1959,6 +1959,8 @@ int fill_occupancy(int k) { MSA_DISPATCH_K(k, occupancy_k); }
 
 int launch_coopt(const JobDev &jd, Ctrl *ctrl, int32_t max_paths, uint8_t *aln_out,
                  int64_t *len_out, int32_t *npaths_out, hipStream_t s) {
+  if (jd.k <= kCoMaxK && jd.total_len <= kTrMaxTotal)
+    return launch_coopt_trace(jd, ctrl, max_paths, aln_out, len_out, npaths_out, s);
   MSA_DISPATCH_K(jd.k, launch_coopt_k, jd, ctrl, max_paths, aln_out, len_out, npaths_out, s);
 }
 

@@ -14,6 +14,9 @@ int launch_fill(const JobDev &jd, Ctrl *ctrl, const int32_t *order, int grid, in
 int launch_traceback(const JobDev &jd, Ctrl *ctrl, hipStream_t s);
 // the same by several walkers (msa_trace.hip): k <= kTrMaxK, sum n_i <= kTrMaxTotal
 int launch_trace(const JobDev &jd, Ctrl *ctrl, hipStream_t s);
+// and the co-optimal list built on it (k <= kCoMaxK)
+int launch_coopt_trace(const JobDev &jd, Ctrl *ctrl, int32_t max_paths, uint8_t *aln_out,
+                       int64_t *len_out, int32_t *npaths_out, hipStream_t s);
 int launch_export(const JobDev &jd, const Ctrl *ctrl, uint8_t *out, int64_t ncell,
                   hipStream_t s);
 int launch_nearopt(const JobDev &jd, Ctrl *ctrl, int64_t delta, int32_t max_paths,

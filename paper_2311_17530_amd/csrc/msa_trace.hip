@@ -542,6 +542,268 @@ __global__ __launch_bounds__(kTrThreads) void trace_kernel(JobDev jd, Ctrl *ctrl
   if (threadIdx.x == 0) finish_launch(ctrl);
 }
 
+// ---------------------------------------------------------------------------
+// Co-optimal alignments.
+// ---------------------------------------------------------------------------
+constexpr int kMoreTies = 0x80;  // stack entry flag: the cell has tied masks above the one taken
+
+// Records over the first alignment's walk, in the memory of its walkers' cells.
+struct CoRec {
+  uint32_t *cell;   // [h]: the first alignment's cell (v_0, v_1), ~0: none
+  uint16_t *level;  // [h]: its column, counted from the last one
+  uint8_t *first;   // [level]: its stack (mask and kMoreTies)
+  uint8_t *stack;   // [level]: the current alignment's
+  uint8_t *seq;     // the sequences
+  __device__ __forceinline__ explicit CoRec(const TrRec &rc)
+      : cell(reinterpret_cast<uint32_t *>(rc.pos)),
+        level(reinterpret_cast<uint16_t *>(cell + rc.n)),
+        first(reinterpret_cast<uint8_t *>(level + rc.n)),
+        stack(first + rc.n),
+        seq(rc.own) {}
+};
+
+// The tie set of cell v, from its tile's block in `blk` (tile cur).
+template <int K>
+__device__ __forceinline__ int co_ties(const JobDev &jd, uint8_t *blk, int &cur,
+                                       const int (&v)[K]) {
+  using C = TrCfg<K>;
+  constexpr int T = C::T;
+  const int lane = threadIdx.x & 63;
+  int t = 0, dl = 0;
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    const int ci = v[i] == 0 ? 0 : (v[i] - 1) / T + 1;
+    t += ci * jd.tstride[i];
+    dl += (v[i] - (ci == 0 ? 0 : (ci - 1) * T + 1)) * C::dstride(i);
+  }
+  if (t != cur) {
+    const u32x4 *src = reinterpret_cast<const u32x4 *>(jd.dir + (int64_t)t * C::DBS);
+    u32x4 *dst = reinterpret_cast<u32x4 *>(blk);
+#pragma unroll
+    for (int x = 0; x < (C::DBS / 16 + 63) / 64; ++x) {
+      const int idx = lane + x * 64;
+      if (idx < C::DBS / 16) dst[idx] = src[idx];
+    }
+    cur = t;
+  }
+  return __builtin_amdgcn_readfirstlane(blk[dl]) & ((1 << C::M) - 1);
+}
+
+// Alignment p goes to aln_out + p * k * aln_cap.  Wave 0 enumerates and leaves
+// each alignment's masks in its first row; all waves expand them afterwards.
+template <int K>
+__global__ __launch_bounds__(kTrThreads) void coopt_trace_kernel(JobDev jd, Ctrl *ctrl,
+                                                                 int32_t max_paths,
+                                                                 uint8_t *aln_out,
+                                                                 int64_t *len_out,
+                                                                 int32_t *npaths_out) {
+  using C = TrCfg<K>;
+  __shared__ TrSmem<K> sm;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid) >> 6;
+  int status = __builtin_amdgcn_readfirstlane(
+      __hip_atomic_load(&ctrl->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  // the blocks hold tie sets only when the workspace was set up for them
+  if (status == ST_OK && !(ctrl->flags & kCoOptimal)) status = ST_EINVAL;
+  int end[K];
+#pragma unroll
+  for (int i = 0; i < K; ++i) end[i] = jd.n[i];
+  int H = 0;
+  const int F = tr_families<K>(end, H);
+  const TrRec rc(sm, F, H);
+  if (status == ST_OK) {
+    tr_walk_all<K, false, true>(jd, sm, end, rc, F);
+    status = sm.status;
+  }
+  int np = 0;
+  if (status == ST_OK) {
+    // ---- the first alignment's columns: wave w takes the sums w * per + 1 .. ----
+    const CoRec co(rc);
+    const int per = (H + kTrThreads - 1) / kTrThreads * 64;
+    const int lo = wave * per + 1, hi = min(H, (wave + 1) * per);
+    int cnt[K + 1];
+#pragma unroll
+    for (int i = 0; i <= K; ++i) cnt[i] = 0;
+    for (int h0 = lo; h0 <= hi; h0 += 64) {
+      const int m = h0 + lane <= hi ? rc.path[h0 + lane] : 0;
+      cnt[K] += __builtin_popcountll(__ballot(m != 0));
+#pragma unroll
+      for (int i = 0; i < K; ++i) cnt[i] += __builtin_popcountll(__ballot((m >> i) & 1));
+    }
+#pragma unroll
+    for (int i = 0; i <= K; ++i) sm.cnt[wave][i] = cnt[i];
+    for (int x = tid; x <= H; x += kTrThreads) co.cell[x] = ~0u;
+    for (int x = tid; x < H; x += kTrThreads) co.seq[x] = jd.seqs[x];
+    __syncthreads();
+    int at[K + 1], N = 0;
+#pragma unroll
+    for (int i = 0; i <= K; ++i) at[i] = 0;
+    for (int w = 0; w < kTrWalkers; ++w) {
+#pragma unroll
+      for (int i = 0; i <= K; ++i) at[i] += w < wave ? sm.cnt[w][i] : 0;
+      N += sm.cnt[w][K];
+    }
+    const uint64_t upto = lane == 63 ? ~0ull : (2ull << lane) - 1;
+    for (int h0 = lo; h0 <= hi; h0 += 64) {
+      const int h = h0 + lane;
+      const int m = h <= hi ? rc.path[h] : 0;
+      const uint64_t cols = __ballot(m != 0);
+      const int lv = N - (at[K] + __builtin_popcountll(cols & upto));  // from the last column
+      at[K] += __builtin_popcountll(cols);
+      int64_t t = 0;
+      int dl = 0, vv[K];
+#pragma unroll
+      for (int i = 0; i < K; ++i) {
+        const uint64_t bits = __ballot((m >> i) & 1);
+        vv[i] = at[i] + __builtin_popcountll(bits & upto);
+        at[i] += __builtin_popcountll(bits);
+        const int ci = vv[i] == 0 ? 0 : (vv[i] - 1) / C::T + 1;
+        t += (int64_t)ci * jd.tstride[i];
+        dl += (vv[i] - (ci == 0 ? 0 : (ci - 1) * C::T + 1)) * C::dstride(i);
+      }
+      if (m != 0) {
+        const int ties = jd.dir[t * C::DBS + dl] & ((1 << C::M) - 1);
+        const bool more = (ties & ~((1 << m) - 1)) != 0;  // tied masks above m
+        co.cell[h] = (uint32_t)vv[0] | (uint32_t)vv[1] << 16;
+        co.level[h] = (uint16_t)lv;
+        co.first[lv] = (uint8_t)(m | (more ? kMoreTies : 0));
+      }
+    }
+    __syncthreads();
+    // ---- the enumeration (wave 0) ----
+    if (wave == 0) {
+      for (int x = lane; x < N; x += 64) co.stack[x] = co.first[x];
+      int d = N, cur = -1;
+      int v[K];
+#pragma unroll
+      for (int i = 0; i < K; ++i) v[i] = 0;  // the cell after the stack's last column
+      for (;;) {
+        // v is the origin: stack[0 .. d) is an alignment (stack[d - 1] its first column)
+        uint8_t *row = aln_out + (int64_t)np * K * jd.aln_cap;
+        for (int x = lane; x < d; x += 64) row[x] = co.stack[d - 1 - x] & C::M;
+        if (lane == 0) len_out[np] = d;
+        ++np;
+        if (np == max_paths || d == 0) break;
+        // back up to the deepest column whose cell has tied masks left (lane x
+        // reads level e - x), adding the masks of the columns popped to v
+        int e = d - 1, found = -1;
+        while (e >= 0) {
+          const int lvl = e - lane;
+          const int ent = lvl >= 0 ? co.stack[lvl] : 0;
+          const uint64_t flagged = __ballot((ent & kMoreTies) != 0);
+          const int last = flagged ? __builtin_ctzll(flagged) : 63;
+          const bool popped = lane <= last && lvl >= 0;
+#pragma unroll
+          for (int i = 0; i < K; ++i)
+            v[i] += __builtin_popcountll(__ballot(popped && ((ent >> i) & 1)));
+          if (flagged) {
+            found = e - last;
+            break;
+          }
+          e -= 64;
+        }
+        if (found < 0) break;  // every alignment has been produced
+        d = found;
+        int tried = co.stack[d] & C::M;
+        int h = 0;
+#pragma unroll
+        for (int i = 0; i < K; ++i) h += v[i];
+        // down along the lowest tied masks (the first step: above `tried`) to a
+        // cell of the first alignment, whose columns below are this one's too
+        bool bad = false;
+        for (;;) {
+          if (tried == 0 && h > 0) {
+            const uint32_t p = (uint32_t)v[0] | (uint32_t)v[1] << 16;
+            if ((uint32_t)__builtin_amdgcn_readfirstlane(co.cell[h]) == p) {
+              const int lv = __builtin_amdgcn_readfirstlane((int)co.level[h]);
+              for (int x = lane; x < N - lv; x += 64) co.stack[d + x] = co.first[lv + x];
+              d += N - lv;
+              break;
+            }
+          }
+          if (h == 0) break;  // (one-column alignments meet the first one nowhere)
+          const int ties = co_ties<K>(jd, sm.dirb[0], cur, v);
+          const int rest = ties & ~((1 << tried) - 1);
+          if (rest == 0) {  // a flagged column without a tie left, or a cell without one
+            bad = true;
+            break;
+          }
+          const int b = __builtin_ctz(rest) + 1;
+#pragma unroll
+          for (int i = 0; i < K; ++i) {
+            bad = bad || (((b >> i) & 1) && v[i] == 0);
+            v[i] -= (b >> i) & 1;
+          }
+          if (bad || d >= H) {
+            bad = true;
+            break;
+          }
+          co.stack[d] = (uint8_t)(b | ((rest & ~((1 << b) - 1)) != 0 ? kMoreTies : 0));
+          h -= __builtin_popcount(b);
+          ++d;
+          tried = 0;
+        }
+        if (bad) {
+          status = ST_EDEVICE;
+          break;
+        }
+#pragma unroll
+        for (int i = 0; i < K; ++i) v[i] = 0;
+      }
+      sm.status = status;
+      sm.hend = np;
+    }
+    __threadfence_block();
+    __syncthreads();
+    status = sm.status;
+    np = sm.hend;
+    // ---- rows: a wave per alignment; a chunk's masks are read before its
+    // columns of the first row are written ----
+    if (status == ST_OK) {
+      const uint64_t below = (1ull << lane) - 1;
+      for (int p = wave; p < np; p += kTrWalkers) {
+        uint8_t *blk = aln_out + (int64_t)p * K * jd.aln_cap;
+        const int d = (int)len_out[p];
+        int pos[K];
+#pragma unroll
+        for (int i = 0; i < K; ++i) pos[i] = jd.seq_off[i];
+        for (int c0 = 0; c0 < d; c0 += 64) {
+          const int m = c0 + lane < d ? blk[c0 + lane] : 0;
+#pragma unroll
+          for (int i = 0; i < K; ++i) {
+            const uint64_t bits = __ballot((m >> i) & 1);
+            const int x = pos[i] + __builtin_popcountll(bits & below);
+            pos[i] += __builtin_popcountll(bits);
+            if (m != 0)
+              blk[(int64_t)i * jd.aln_cap + c0 + lane] =
+                  (m >> i) & 1 ? co.seq[x] : (uint8_t)0xFF;
+          }
+        }
+      }
+    }
+  }
+  __syncthreads();
+  if (tid == 0) {
+    *npaths_out = status == ST_OK ? np : 0;
+    *jd.status_out = status;
+    if (status != ST_OK) *jd.score_out = 0;
+    finish_launch(ctrl);
+  }
+}
+
+int launch_coopt_trace(const JobDev &jd, Ctrl *ctrl, int32_t max_paths, uint8_t *aln_out,
+                       int64_t *len_out, int32_t *npaths_out, hipStream_t s) {
+  launch_begin();
+  if (jd.k == 2)
+    hipLaunchKernelGGL((coopt_trace_kernel<2>), dim3(1), dim3(kTrThreads), 0, s, jd, ctrl,
+                       max_paths, aln_out, len_out, npaths_out);
+  else
+    hipLaunchKernelGGL((coopt_trace_kernel<3>), dim3(1), dim3(kTrThreads), 0, s, jd, ctrl,
+                       max_paths, aln_out, len_out, npaths_out);
+  return launch_end();
+}
+
 template <int K>
 static int launch_trace_k(const JobDev &jd, Ctrl *ctrl, hipStream_t s) {
   launch_begin();
