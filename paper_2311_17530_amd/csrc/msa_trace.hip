@@ -1,5 +1,5 @@
-// msa_trace.hip -- traceback by several walkers, and the co-optimal list built
-// on it.
+// msa_trace.hip -- traceback by several walkers, the co-optimal list built on
+// it, and the near-optimal list.
 //
 // The walk from the far corner (Section 2) is a chain of dependent reads, one
 // per column: a single wave took 0.13 us a column and 0.5 us a tile crossing.
@@ -802,6 +802,311 @@ int launch_coopt_trace(const JobDev &jd, Ctrl *ctrl, int32_t max_paths, uint8_t 
     hipLaunchKernelGGL((coopt_trace_kernel<3>), dim3(1), dim3(kTrThreads), 0, s, jd, ctrl,
                        max_paths, aln_out, len_out, npaths_out);
   return launch_end();
+}
+
+// ---------------------------------------------------------------------------
+// Near-optimal alignments (near-optimal mode, k <= 6): every global alignment
+// whose score is at least opt - delta (Section 6: alignments within a
+// threshold of the optimum set by the user).  The fill has also stored every
+// cell's score xi, laid out as the direction blocks.  Wave 0 walks depth
+// first from the far corner.  At cell v, with s the score of the columns
+// taken so far, lane b - 1 tests mask b: v - b lies in the tensor and
+// xi(v - b) + SP(col(v, b)) + s >= opt - delta.  xi(v - b) is the score of
+// some path from the origin, so every step passing the test leads to at least
+// one alignment at or above the threshold (the walk has no dead end), and
+// every such alignment is walked.  The masks of a cell are taken in
+// ascending order, so the list is sorted by the column masks read from the
+// last column to the first, and delta = 0 gives the co-optimal list.  Per
+// column the LDS stack keeps the mask taken, the set of masks that passed
+// and the score so far (sum n_i <= kNoMaxTotal); after an alignment the walk
+// jumps back to the deepest column with a passing mask left, found with one
+// wave-wide scan of the stack.  Alignment p goes to aln_out + p * k *
+// aln_cap, its score to scores_out[p]; its masks wait in its first row until
+// all waves expand the list.
+//
+// What bounds it: the chain of a step (residues, pair scores, test).  The
+// residues and the matrix sit in LDS, and so does a box of the scores at and
+// below the walk's cell, loaded by all waves at once when the walk leaves it;
+// with a global load for each of these at every step, 16 alignments of 300 x
+// 257 x 281 took 1.54 ms.
+// ---------------------------------------------------------------------------
+constexpr int kNoThreads = 512;
+
+template <int K>
+struct NoSmem {
+  static constexpr int E = K == 2 ? 64 : K == 3 ? 16 : K == 4 ? 8 : K == 5 ? 5 : 4;  // box edge
+  static constexpr int N = ipow(E, K);
+  uint64_t pass[kNoMaxTotal + 1];  // masks that passed at a column's cell
+  int32_t sofar[kNoMaxTotal + 1];  // score of the columns above it
+  int32_t box[N];                  // xi(top - x) at sum x_i * E^(K-1-i)
+  int16_t sub[32 * 32];
+  uint8_t path[kNoMaxTotal + 1];
+  uint8_t seq[kNoMaxTotal + 1];
+  int32_t top[K];                  // the box's upper corner
+  int32_t more, status, np;
+};
+
+template <int K>
+__global__ __launch_bounds__(kNoThreads) void nearopt_kernel(JobDev jd, Ctrl *ctrl, int64_t delta,
+                                                             int32_t max_paths,
+                                                             int64_t *scores_out,
+                                                             uint8_t *aln_out, int64_t *len_out,
+                                                             int32_t *npaths_out) {
+  using C = TrCfg<K>;
+  using Sm = NoSmem<K>;
+  constexpr int T = C::T;
+  constexpr int M = C::M;  // masks 1..M; lane b - 1 tests mask b
+  constexpr int E = Sm::E;
+  static_assert(M <= 64, "one lane per mask");
+  __shared__ Sm sm;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid) >> 6;
+  int status = __builtin_amdgcn_readfirstlane(
+      __hip_atomic_load(&ctrl->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  // the cell scores exist only when the workspace was set up for them
+  if (status == ST_OK && !(ctrl->flags & kNearOpt)) status = ST_EINVAL;
+  const int alpha = ctrl->alpha;
+  const int gap = ctrl->gap;
+  const int64_t threshold = *jd.score_out - delta;
+  const int total = (int)jd.total_len;
+  for (int x = tid; x < total; x += kNoThreads) sm.seq[x] = jd.seqs[x];
+  if (alpha <= 32)
+    for (int x = tid; x < alpha * alpha; x += kNoThreads)
+      sm.sub[(x / alpha) * 32 + x % alpha] = jd.sub[x];
+  if (tid == 0) {
+    sm.sofar[0] = 0;
+    sm.status = status;
+    sm.np = 0;
+  }
+#pragma unroll
+  for (int i = 0; i < K; ++i)
+    if (tid == i) sm.top[i] = jd.n[i];
+  // wave 0's walk
+  int v[K];
+#pragma unroll
+  for (int i = 0; i < K; ++i) v[i] = jd.n[i];
+  const int bl = lane + 1;  // this lane's mask
+  int lbox = 0;             // its offset in the box
+#pragma unroll
+  for (int i = 0; i < K; ++i) lbox += ((bl >> i) & 1) * ipow(E, K - 1 - i);
+  int d = 0, np = 0;
+  int tried = 0;      // masks up to this one were taken at depth d
+  bool fresh = true;  // pass[d] not computed yet
+  int64_t steps = 0;
+  const int64_t step_limit = (int64_t)max_paths * (2 * jd.total_len + 2) + 2;
+  __syncthreads();
+  while (status == ST_OK) {
+    // ---- all waves: the box of scores below sm.top ----
+    {
+      constexpr int PER = (Sm::N + kNoThreads - 1) / kNoThreads;
+      int32_t got[PER];
+#pragma unroll
+      for (int y = 0; y < PER; ++y) {
+        const int x = tid + y * kNoThreads;
+        int rem = x, t = 0, dl = 0;
+        bool ok = x < Sm::N;
+#pragma unroll
+        for (int i = K - 1; i >= 0; --i) {
+          const int u = sm.top[i] - rem % E;
+          rem /= E;
+          ok = ok && u >= 0;
+          const int uu = u < 0 ? 0 : u;
+          const int ci = uu == 0 ? 0 : (uu - 1) / T + 1;
+          t += ci * jd.tstride[i];
+          dl += (uu - (ci == 0 ? 0 : (ci - 1) * T + 1)) * C::dstride(i);
+        }
+        got[y] = jd.scores[ok ? (int64_t)t * C::DBS + dl : 0];
+      }
+#pragma unroll
+      for (int y = 0; y < PER; ++y)
+        if (tid + y * kNoThreads < Sm::N) sm.box[tid + y * kNoThreads] = got[y];
+    }
+    __syncthreads();
+    if (wave == 0) {
+      int top[K];
+#pragma unroll
+      for (int i = 0; i < K; ++i) top[i] = __builtin_amdgcn_readfirstlane(sm.top[i]);
+      int more = 0;  // the walk needs another box
+      for (;;) {
+        bool origin = true;
+#pragma unroll
+        for (int i = 0; i < K; ++i) origin = origin && v[i] == 0;
+        if (origin) {
+          // path[0..d) (path[d-1] is the first column) is alignment np
+          uint8_t *row = aln_out + (int64_t)np * K * jd.aln_cap;
+          for (int x = lane; x < d; x += 64) row[x] = sm.path[d - 1 - x];
+          if (lane == 0) {
+            len_out[np] = d;
+            scores_out[np] = sm.sofar[d];
+          }
+          ++np;
+          if (np == max_paths || d == 0) break;
+          // back up to the deepest column with a passing mask above the one
+          // taken: scan the stack 64 entries at a time (lane x reads level
+          // e - x), adding the masks of the levels popped to v
+          int e = d - 1, found = -1;
+          while (e >= 0) {
+            const int lvl = e - lane;
+            const int ent = lvl >= 0 ? sm.path[lvl] : 0;
+            const bool left = lvl >= 0 && (sm.pass[lvl] >> ent) != 0;
+            const uint64_t flagged = __ballot(left);
+            const int upto = flagged ? __builtin_ctzll(flagged) : 63;
+            const bool popped = lane <= upto && lvl >= 0;
+#pragma unroll
+            for (int i = 0; i < K; ++i)
+              v[i] += __builtin_popcountll(__ballot(popped && ((ent >> i) & 1)));
+            if (flagged) {
+              found = e - upto;
+              break;
+            }
+            e -= 64;
+          }
+          if (found < 0) break;  // every alignment has been produced
+          d = found;
+          tried = __builtin_amdgcn_readfirstlane((int)sm.path[d]);
+          fresh = false;
+          continue;
+        }
+        if (fresh) {  // v and its lower neighbours have to lie in the box
+          bool in = true;
+#pragma unroll
+          for (int i = 0; i < K; ++i) in = in && (unsigned)(top[i] - v[i]) <= (unsigned)(E - 2);
+          if (!in) {
+            more = 1;
+            break;
+          }
+        }
+        if (++steps > step_limit) {  // inconsistent scores: never loop for ever
+          status = ST_EDEVICE;
+          break;
+        }
+        // residues of v, and SP(col(v, b)) of this lane's mask: residue pairs,
+        // residue-gap pairs
+        int r[K];
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+          r[i] = v[i] >= 1 ? (int)sm.seq[jd.seq_off[i] + v[i] - 1] : 0;
+        int32_t sp = 0;
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+#pragma unroll
+          for (int j = i + 1; j < K; ++j) {
+            const int32_t ps = alpha <= 32 ? (int32_t)sm.sub[r[i] * 32 + r[j]]
+                                           : (int32_t)jd.sub[r[i] * alpha + r[j]];
+            const int bi = (bl >> i) & 1, bj = (bl >> j) & 1;
+            sp += (bi && bj) ? ps : (bi ^ bj) ? gap : 0;
+          }
+        uint64_t set;
+        if (fresh) {
+          bool ok = lane < M;
+          int x = 0;
+#pragma unroll
+          for (int i = 0; i < K; ++i) {
+            ok = ok && v[i] - ((bl >> i) & 1) >= 0;
+            x += (top[i] - v[i]) * ipow(E, K - 1 - i);
+          }
+          const int32_t xi = sm.box[ok ? x + lbox : 0];
+          set = __ballot(ok && (int64_t)xi + sp + sm.sofar[d] >= threshold);
+          if (set == 0) {  // a cell off the origin from which no alignment reaches the threshold
+            status = ST_EDEVICE;
+            break;
+          }
+          sm.pass[d] = set;  // every lane stores the same value
+          fresh = false;
+        } else {
+          const uint64_t p = sm.pass[d];
+          set = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)p) |
+                (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(p >> 32)) << 32;
+        }
+        // (masks up to `tried` were taken; a column on the stack keeps at least
+        // one more whenever the walk comes back to it)
+        const uint64_t rest = tried >= 64 ? 0 : set & ~((1ull << tried) - 1);
+        if (rest == 0 || d >= total) {  // or a walk longer than any alignment
+          status = ST_EDEVICE;
+          break;
+        }
+        const int b = __builtin_ctzll(rest) + 1;
+        const int32_t spb = __builtin_amdgcn_readlane(sp, b - 1);
+        // every lane stores the same values; the one wave's LDS accesses stay
+        // in program order, so no barrier is needed before they are read back
+        sm.path[d] = (uint8_t)b;
+        sm.sofar[d + 1] = sm.sofar[d] + spb;
+#pragma unroll
+        for (int i = 0; i < K; ++i) v[i] -= (b >> i) & 1;
+        ++d;
+        tried = 0;
+        fresh = true;
+      }
+      sm.more = more;
+      sm.status = status;
+      sm.np = np;
+#pragma unroll
+      for (int i = 0; i < K; ++i)
+        if (lane == i) sm.top[i] = v[i];
+    }
+    __syncthreads();
+    status = sm.status;
+    if (!sm.more) break;
+  }
+  __threadfence_block();
+  __syncthreads();
+  np = sm.np;
+  // ---- rows: a wave per alignment; a chunk's masks are read before its
+  // columns of the first row are written ----
+  if (status == ST_OK) {
+    const uint64_t below = (1ull << lane) - 1;
+    for (int p = wave; p < np; p += kNoThreads / 64) {
+      uint8_t *blk = aln_out + (int64_t)p * K * jd.aln_cap;
+      const int len = (int)len_out[p];
+      int pos[K];
+#pragma unroll
+      for (int i = 0; i < K; ++i) pos[i] = jd.seq_off[i];
+      for (int c0 = 0; c0 < len; c0 += 64) {
+        const int m = c0 + lane < len ? blk[c0 + lane] : 0;
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+          const uint64_t bits = __ballot((m >> i) & 1);
+          const int x = pos[i] + __builtin_popcountll(bits & below);
+          pos[i] += __builtin_popcountll(bits);
+          if (m != 0)
+            blk[(int64_t)i * jd.aln_cap + c0 + lane] = (m >> i) & 1 ? sm.seq[x] : (uint8_t)0xFF;
+        }
+      }
+    }
+  }
+  __syncthreads();
+  if (tid == 0) {
+    *npaths_out = status == ST_OK ? np : 0;
+    *jd.status_out = status;
+    if (status != ST_OK) *jd.score_out = 0;
+    finish_launch(ctrl);
+  }
+}
+
+template <int K>
+static int launch_nearopt_k(const JobDev &jd, Ctrl *ctrl, int64_t delta, int32_t max_paths,
+                            int64_t *scores_out, uint8_t *aln_out, int64_t *len_out,
+                            int32_t *npaths_out, hipStream_t s) {
+  launch_begin();
+  hipLaunchKernelGGL((nearopt_kernel<K>), dim3(1), dim3(kNoThreads), 0, s, jd, ctrl, delta,
+                     max_paths, scores_out, aln_out, len_out, npaths_out);
+  return launch_end();
+}
+
+int launch_nearopt(const JobDev &jd, Ctrl *ctrl, int64_t delta, int32_t max_paths,
+                   int64_t *scores_out, uint8_t *aln_out, int64_t *len_out, int32_t *npaths_out,
+                   hipStream_t s) {
+#define MSA_NO_ARGS jd, ctrl, delta, max_paths, scores_out, aln_out, len_out, npaths_out, s
+  switch (jd.k) {
+    case 2: return launch_nearopt_k<2>(MSA_NO_ARGS);
+    case 3: return launch_nearopt_k<3>(MSA_NO_ARGS);
+    case 4: return launch_nearopt_k<4>(MSA_NO_ARGS);
+    case 5: return launch_nearopt_k<5>(MSA_NO_ARGS);
+    case 6: return launch_nearopt_k<6>(MSA_NO_ARGS);
+    default: return -1;
+  }
+#undef MSA_NO_ARGS
 }
 
 template <int K>
