@@ -1605,6 +1605,7 @@ __global__ __launch_bounds__(64) void batch_traceback_kernel(const BatchArgs *__
   const int gst = __hip_atomic_load(&ctrl->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   for (int j = blockIdx.x; j < njobs; j += gridDim.x) {
     const JobDev &jd = jobs[j];
+    if (KHI <= kTrMaxK && jd.total_len <= kTrMaxTotal) continue;  // batch_trace_kernel's
     const int jst = __hip_atomic_load(jd.jstatus, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int st = gst != ST_OK ? gst : jst;
     switch (jd.k) {
@@ -1746,6 +1747,7 @@ constexpr int kBatchThreads = 256;
 // columns, the traceback over the jobs, one wave per job at a time.
 constexpr int kBatchAuxGrid = 1024;
 constexpr int kBatchTraceGrid = 4096;
+constexpr int kBatchLongGrid = 256;  // where only jobs beyond the walkers' bounds are left
 
 template <int KLO, int KHI>
 static int launch_batch_k(const BatchArgs *d_args, const JobDev *d_jobs, Ctrl *ctrl, int grid,
@@ -1756,7 +1758,9 @@ static int launch_batch_k(const BatchArgs *d_args, const JobDev *d_jobs, Ctrl *c
   hipLaunchKernelGGL((batch_fill_kernel<KLO, KHI, kBatchThreads>), dim3(grid),
                      dim3(kBatchThreads), 0, s, d_args, d_jobs, ctrl);
   if (KLO <= 4 && 4 <= KHI) launch_batch_sweep4(d_args, ctrl, s);
-  hipLaunchKernelGGL((batch_traceback_kernel<KLO, KHI>), dim3(kBatchTraceGrid), dim3(64), 0, s,
+  if (KHI <= kTrMaxK) launch_batch_trace(KHI <= 4 ? 0 : 1, d_args, d_jobs, ctrl, s);
+  hipLaunchKernelGGL((batch_traceback_kernel<KLO, KHI>),
+                     dim3(KHI <= kTrMaxK ? kBatchLongGrid : kBatchTraceGrid), dim3(64), 0, s,
                      d_args, d_jobs, ctrl);
   hipLaunchKernelGGL(batch_finish_kernel, dim3(1), dim3(64), 0, s, d_args, ctrl);
   return launch_end();

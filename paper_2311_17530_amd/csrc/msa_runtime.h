@@ -14,6 +14,9 @@ int launch_fill(const JobDev &jd, Ctrl *ctrl, const int32_t *order, int grid, in
 int launch_traceback(const JobDev &jd, Ctrl *ctrl, hipStream_t s);
 // the same by several walkers (msa_trace.hip): k <= kTrMaxK, sum n_i <= kTrMaxTotal
 int launch_trace(const JobDev &jd, Ctrl *ctrl, hipStream_t s);
+// the same for a batched launch's jobs of k class 0 or 1 (nothing for others)
+void launch_batch_trace(int kclass, const BatchArgs *d_args, const JobDev *d_jobs, Ctrl *ctrl,
+                        hipStream_t s);
 // and the co-optimal list built on it (k <= kCoMaxK)
 int launch_coopt_trace(const JobDev &jd, Ctrl *ctrl, int32_t max_paths, uint8_t *aln_out,
                        int64_t *len_out, int32_t *npaths_out, hipStream_t s);

@@ -56,10 +56,20 @@ struct TrCfg {
   static constexpr int dstride(int i) { return ipow(T, K - 1 - i); }
 };
 
+// The thread index, opaque: what follows from it is formed where it is used
+// instead of being kept in registers across a batched launch's jobs.
+__device__ __forceinline__ int tr_tid() {
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  return tid;
+}
+
 // How a walk ended.
 enum { kTrMerged = 0, kTrOpen = 1, kTrEnd = 2, kTrBad = 3 };
 
-constexpr int kTrFam = 3;  // families of guesses
+// Families of guesses (k = 5, whose sequences are short and whose walk takes
+// the most registers: the straight line alone).
+template <int K> constexpr int kTrFam = K <= 4 ? 3 : 1;
 // LDS bytes of the records: per sum and family a cell (8 bytes), the owner's
 // mask and the overlap's, and per sum the path's mask.
 constexpr int kTrRec = 92 * 1024;
@@ -101,7 +111,7 @@ struct TrRec {
 // or at a sum h_stop or less (-1: never), or at a tile's entry once `done` is
 // set.  On return v, h is the cell where it stopped.
 template <int K, bool egf, bool coopt>
-__device__ int tr_walk(const JobDev &jd, const TrRec &rc, uint8_t *dirb, int (&v)[K], int &h,
+__device__ __forceinline__ int tr_walk(const JobDev &jd, const TrRec &rc, uint8_t *dirb, int (&v)[K], int &h,
                        int h_own, int h_stop, int fam, int f0, int nf, uint8_t *to, int &met,
                        const int32_t &done) {
   using C = TrCfg<K>;
@@ -109,7 +119,7 @@ __device__ int tr_walk(const JobDev &jd, const TrRec &rc, uint8_t *dirb, int (&v
   constexpr int M = C::M;
   constexpr int NQ = C::DBS / 16;      // 16-byte chunks per direction block
   constexpr int CPL = (NQ + 63) / 64;  // chunks per lane
-  const int lane = threadIdx.x & 63;
+  const int lane = tr_tid() & 63;
   u32x4 *const lds4 = reinterpret_cast<u32x4 *>(dirb);
   int c[K], q[K];
   int64_t t = 0;
@@ -151,7 +161,7 @@ __device__ int tr_walk(const JobDev &jd, const TrRec &rc, uint8_t *dirb, int (&v
   // the watched records of sums w0 - lane, read again every kTrWin sums (an
   // owner may be writing them: what is not there yet is no meeting)
   constexpr int kTrWin = 16;
-  uint32_t wlo[kTrFam], whi[kTrFam];
+  uint32_t wlo[kTrFam<K>], whi[kTrFam<K>];
   int w0 = INT32_MAX;
   for (;;) {
     if (h <= h_own && h > 0 && __hip_atomic_load(&done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
@@ -193,7 +203,7 @@ __device__ int tr_walk(const JobDev &jd, const TrRec &rc, uint8_t *dirb, int (&v
         if (w0 - h >= kTrWin) {
           w0 = h;
 #pragma unroll
-          for (int f = 0; f < kTrFam; ++f) {
+          for (int f = 0; f < kTrFam<K>; ++f) {
             const uint64_t r = f < nf ? rc.pos[(f0 + f) * rc.n + max(h - lane, 0)] : ~0ull;
             wlo[f] = (uint32_t)r;
             whi[f] = (uint32_t)(r >> 32);
@@ -202,7 +212,7 @@ __device__ int tr_walk(const JobDev &jd, const TrRec &rc, uint8_t *dirb, int (&v
         uint64_t eq = 0;
         int mf = 0;
 #pragma unroll
-        for (int f = kTrFam - 1; f >= 0; --f) {
+        for (int f = kTrFam<K> - 1; f >= 0; --f) {
           const uint64_t e = __ballot(lane == w0 - h && wlo[f] == plo && whi[f] == phi);
           mf = e ? f : mf;
           eq |= e;
@@ -307,16 +317,18 @@ __device__ __forceinline__ int tr_families(const int (&end)[K], int &H) {
     least = min(least, end[i]);
     H += end[i];
   }
-  return 16 * (most - least) <= most || most < 24 || tr_rec_bytes(kTrFam, H) > kTrRec ? 1 : kTrFam;
+  return 16 * (most - least) <= most || most < 24 || tr_rec_bytes(kTrFam<K>, H) > kTrRec
+             ? 1
+             : kTrFam<K>;
 }
 
 // The walk from cell end[] by all waves of the workgroup: sm.status, sm.vend
 // and sm.hend (its last cell) and rc.path[h], the mask of its cell with sum
 // h (0: none), for every sum above hend.
 template <int K, bool egf, bool coopt>
-__device__ void tr_walk_all(const JobDev &jd, TrSmem<K> &sm, const int (&end)[K], const TrRec &rc,
+__device__ __forceinline__ void tr_walk_all(const JobDev &jd, TrSmem<K> &sm, const int (&end)[K], const TrRec &rc,
                             int F) {
-  const int tid = threadIdx.x;
+  const int tid = tr_tid();
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid) >> 6;
   const int H = rc.n - 1;
@@ -418,8 +430,8 @@ __device__ void tr_walk_all(const JobDev &jd, TrSmem<K> &sm, const int (&end)[K]
 // Rows of the alignment: unaligned prefixes (end gaps free; sequence 0 first),
 // the path's columns in ascending order of h, unaligned suffixes.
 template <int K>
-__device__ void tr_rows(const JobDev &jd, TrSmem<K> &sm, const int (&end)[K], const TrRec &rc) {
-  const int tid = threadIdx.x;
+__device__ __forceinline__ void tr_rows(const JobDev &jd, TrSmem<K> &sm, const int (&end)[K], const TrRec &rc) {
+  const int tid = tr_tid();
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid) >> 6;
   int H = 0, pre = 0;
@@ -490,7 +502,7 @@ __device__ void tr_rows(const JobDev &jd, TrSmem<K> &sm, const int (&end)[K], co
 }
 
 template <int K, bool egf, bool coopt>
-__device__ void tr_job(const JobDev &jd, TrSmem<K> &sm, int status, int64_t best) {
+__device__ __forceinline__ void tr_job(const JobDev &jd, TrSmem<K> &sm, int status, int64_t best) {
   int end[K];
   if constexpr (egf) {  // the end cell from its row-major index
     int64_t lin = (int64_t)(uint32_t)best;
@@ -540,6 +552,85 @@ __global__ __launch_bounds__(kTrThreads) void trace_kernel(JobDev jd, Ctrl *ctrl
   }
   __syncthreads();
   if (threadIdx.x == 0) finish_launch(ctrl);
+}
+
+__device__ __forceinline__ int64_t tr_uni(int64_t x) {
+  return (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)x) |
+         (int64_t)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32;
+}
+template <class T>
+__device__ __forceinline__ T *tr_uni(T *p) {
+  return reinterpret_cast<T *>(tr_uni(reinterpret_cast<int64_t>(p)));
+}
+
+// What the walk reads of a job's descriptor, in scalar registers.
+__device__ __forceinline__ JobDev tr_desc(const JobDev &jd) {
+  JobDev r;
+#pragma unroll
+  for (int i = 0; i < kTrMaxK; ++i) {
+    r.n[i] = __builtin_amdgcn_readfirstlane(jd.n[i]);
+    r.tstride[i] = __builtin_amdgcn_readfirstlane(jd.tstride[i]);
+    r.seq_off[i] = __builtin_amdgcn_readfirstlane(jd.seq_off[i]);
+  }
+  r.dir = tr_uni(jd.dir);
+  r.seqs = tr_uni(jd.seqs);
+  r.aln_out = tr_uni(jd.aln_out);
+  r.aln_cap = tr_uni(jd.aln_cap);
+  r.aln_len_out = tr_uni(jd.aln_len_out);
+  r.status_out = tr_uni(jd.status_out);
+  r.score_out = tr_uni(jd.score_out);
+  return r;
+}
+
+// A batched launch's jobs, one workgroup each at a time; a job beyond the
+// walkers' bounds is left to the single walk's kernel.
+template <int KLO, int KHI>
+__global__ __launch_bounds__(kTrThreads) void batch_trace_kernel(const BatchArgs *__restrict__ a,
+                                                                 const JobDev *__restrict__ jobs,
+                                                                 Ctrl *ctrl) {
+  constexpr size_t kBytes =
+      sizeof(TrSmem<KHI>) > sizeof(TrSmem<KLO>) ? sizeof(TrSmem<KHI>) : sizeof(TrSmem<KLO>);
+  __shared__ alignas(16) char mem[kBytes];
+  const int njobs = __builtin_amdgcn_readfirstlane(a->njobs);
+  const int gst = __builtin_amdgcn_readfirstlane(
+      __hip_atomic_load(&ctrl->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  for (int j = blockIdx.x; j < njobs; j += gridDim.x) {
+    if (__builtin_amdgcn_readfirstlane((int)(jobs[j].total_len > kTrMaxTotal))) continue;
+    const JobDev jd = tr_desc(jobs[j]);
+    const int jst = __builtin_amdgcn_readfirstlane(
+        __hip_atomic_load(jobs[j].jstatus, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    const int st = gst != ST_OK ? gst : jst;
+    __syncthreads();  // the last job's records are read no more
+    switch (__builtin_amdgcn_readfirstlane(jobs[j].k)) {
+      case 2:
+        if constexpr (KLO <= 2 && 2 <= KHI)
+          tr_job<2, false, false>(jd, *reinterpret_cast<TrSmem<2> *>(mem), st, 0);
+        break;
+      case 3:
+        if constexpr (KLO <= 3 && 3 <= KHI)
+          tr_job<3, false, false>(jd, *reinterpret_cast<TrSmem<3> *>(mem), st, 0);
+        break;
+      case 4:
+        if constexpr (KLO <= 4 && 4 <= KHI)
+          tr_job<4, false, false>(jd, *reinterpret_cast<TrSmem<4> *>(mem), st, 0);
+        break;
+      case 5:
+        if constexpr (KLO <= 5 && 5 <= KHI)
+          tr_job<5, false, false>(jd, *reinterpret_cast<TrSmem<5> *>(mem), st, 0);
+        break;
+      default: break;
+    }
+  }
+}
+
+// One workgroup per compute unit holds the walkers' LDS.
+void launch_batch_trace(int kclass, const BatchArgs *d_args, const JobDev *d_jobs, Ctrl *ctrl,
+                        hipStream_t s) {
+  const dim3 grid((unsigned)device_cu_count()), block(kTrThreads);
+  if (kclass == 0)
+    hipLaunchKernelGGL((batch_trace_kernel<2, 4>), grid, block, 0, s, d_args, d_jobs, ctrl);
+  else if (kclass == 1)
+    hipLaunchKernelGGL((batch_trace_kernel<5, 5>), grid, block, 0, s, d_args, d_jobs, ctrl);
 }
 
 // ---------------------------------------------------------------------------
@@ -824,22 +915,41 @@ int launch_coopt_trace(const JobDev &jd, Ctrl *ctrl, int32_t max_paths, uint8_t 
 // aln_cap, its score to scores_out[p]; its masks wait in its first row until
 // all waves expand the list.
 //
-// What bounds it: the chain of a step (residues, pair scores, test).  The
-// residues and the matrix sit in LDS, and so does a box of the scores at and
-// below the walk's cell, loaded by all waves at once when the walk leaves it;
-// with a global load for each of these at every step, 16 alignments of 300 x
-// 257 x 281 took 1.54 ms.
+// What bounds it: the chain of a step (scores and pair scores of the cell, the
+// test, the choice).  A box of the scores at and below the walk's cell and the
+// pair scores of its residues sit in LDS, loaded by all waves at once when the
+// walk leaves the box.  The list below a cell depends on the cell and on the
+// score so far alone, and its first entry is what a walk that comes to both
+// again goes on with; so new cells are recorded with that score (k <= 5), and
+// a walk that meets such a record copies the columns below it.  16 alignments
+// of 300 x 257 x 281: 1.54 ms with global loads for everything at every step,
+// 1.38 with the box alone.
 // ---------------------------------------------------------------------------
-constexpr int kNoThreads = 512;
+constexpr int kNoThreads = 1024;
+constexpr int kNoPool = 3072;    // recorded cells
+constexpr int kNoWalks = 512;    // recorded walks
 
 template <int K>
 struct NoSmem {
-  static constexpr int E = K == 2 ? 64 : K == 3 ? 16 : K == 4 ? 8 : K == 5 ? 5 : 4;  // box edge
+  static constexpr int E = K == 2 ? 32 : K == 3 ? 16 : K == 4 ? 8 : K == 5 ? 5 : 4;  // box edge
   static constexpr int N = ipow(E, K);
+  static constexpr int NP = K * (K - 1) / 2;
+  static constexpr bool Memo = K <= 5;  // a cell fits the record (13 bits a coordinate)
+  static constexpr int Pool = Memo ? kNoPool : 1;
+  uint64_t cell[Pool];             // recorded cell (v_0 .. v_{k-2}), by record
   uint64_t pass[kNoMaxTotal + 1];  // masks that passed at a column's cell
   int32_t sofar[kNoMaxTotal + 1];  // score of the columns above it
   int32_t box[N];                  // xi(top - x) at sum x_i * E^(K-1-i)
-  int16_t sub[32 * 32];
+  int32_t pair[NP][E * E];         // pair scores of the box's residues, by x_i * E + x_j
+  int32_t score[Pool];             // a record's score so far,
+  uint32_t set[Pool];              // its cell's passing masks
+  uint8_t mask[Pool];              // and the one taken (the lowest)
+  uint16_t walk[Pool];             // its walk
+  uint16_t link[Pool];             // another record of the same coordinate sum
+  uint16_t head[Memo ? kNoMaxTotal + 1 : 1];  // by coordinate sum (0xFFFF: none)
+  uint16_t wend[kNoWalks];         // a walk's records end before this one
+  int16_t wnext[kNoWalks];         // and go on with this one (-1: the origin,
+  int32_t wlast[kNoWalks];         // with this score)
   uint8_t path[kNoMaxTotal + 1];
   uint8_t seq[kNoMaxTotal + 1];
   int32_t top[K];                  // the box's upper corner
@@ -871,9 +981,8 @@ __global__ __launch_bounds__(kNoThreads) void nearopt_kernel(JobDev jd, Ctrl *ct
   const int64_t threshold = *jd.score_out - delta;
   const int total = (int)jd.total_len;
   for (int x = tid; x < total; x += kNoThreads) sm.seq[x] = jd.seqs[x];
-  if (alpha <= 32)
-    for (int x = tid; x < alpha * alpha; x += kNoThreads)
-      sm.sub[(x / alpha) * 32 + x % alpha] = jd.sub[x];
+  if constexpr (Sm::Memo)
+    for (int x = tid; x <= total; x += kNoThreads) sm.head[x] = 0xFFFF;
   if (tid == 0) {
     sm.sofar[0] = 0;
     sm.status = status;
@@ -893,6 +1002,10 @@ __global__ __launch_bounds__(kNoThreads) void nearopt_kernel(JobDev jd, Ctrl *ct
   int d = 0, np = 0;
   int tried = 0;      // masks up to this one were taken at depth d
   bool fresh = true;  // pass[d] not computed yet
+  int32_t sf = 0;     // sofar[d]
+  int h = total;      // coordinate sum of v
+  int nrec = 0, nwalk = 0;  // records, and finished walks, so far
+  bool rec = Sm::Memo && total <= kNoPool;  // this walk's cells are recorded
   int64_t steps = 0;
   const int64_t step_limit = (int64_t)max_paths * (2 * jd.total_len + 2) + 2;
   __syncthreads();
@@ -921,6 +1034,18 @@ __global__ __launch_bounds__(kNoThreads) void nearopt_kernel(JobDev jd, Ctrl *ct
 #pragma unroll
       for (int y = 0; y < PER; ++y)
         if (tid + y * kNoThreads < Sm::N) sm.box[tid + y * kNoThreads] = got[y];
+      // and the pair scores of its residues (0 where a coordinate is 0 or below)
+#pragma unroll
+      for (int i = 0; i < K; ++i)
+#pragma unroll
+        for (int j = i + 1; j < K; ++j)
+          for (int x = tid; x < E * E; x += kNoThreads) {
+            const int a = sm.top[i] - x / E, b = sm.top[j] - x % E;
+            const int p = i * (2 * K - i - 1) / 2 + (j - i - 1);
+            sm.pair[p][x] = a >= 1 && b >= 1 ? (int32_t)jd.sub[sm.seq[jd.seq_off[i] + a - 1] * alpha +
+                                                               sm.seq[jd.seq_off[j] + b - 1]]
+                                             : 0;
+          }
     }
     __syncthreads();
     if (wave == 0) {
@@ -929,19 +1054,24 @@ __global__ __launch_bounds__(kNoThreads) void nearopt_kernel(JobDev jd, Ctrl *ct
       for (int i = 0; i < K; ++i) top[i] = __builtin_amdgcn_readfirstlane(sm.top[i]);
       int more = 0;  // the walk needs another box
       for (;;) {
-        bool origin = true;
-#pragma unroll
-        for (int i = 0; i < K; ++i) origin = origin && v[i] == 0;
-        if (origin) {
+        if (h == 0) {
           // path[0..d) (path[d-1] is the first column) is alignment np
           uint8_t *row = aln_out + (int64_t)np * K * jd.aln_cap;
           for (int x = lane; x < d; x += 64) row[x] = sm.path[d - 1 - x];
           if (lane == 0) {
             len_out[np] = d;
-            scores_out[np] = sm.sofar[d];
+            scores_out[np] = sf;
           }
           ++np;
           if (np == max_paths || d == 0) break;
+          if constexpr (Sm::Memo) {  // the walk's records end here
+            if (rec) {
+              sm.wend[nwalk] = (uint16_t)nrec;
+              sm.wnext[nwalk] = -1;
+              sm.wlast[nwalk] = sf;
+              ++nwalk;
+            }
+          }
           // back up to the deepest column with a passing mask above the one
           // taken: scan the stack 64 entries at a time (lane x reads level
           // e - x), adding the masks of the levels popped to v
@@ -965,10 +1095,54 @@ __global__ __launch_bounds__(kNoThreads) void nearopt_kernel(JobDev jd, Ctrl *ct
           if (found < 0) break;  // every alignment has been produced
           d = found;
           tried = __builtin_amdgcn_readfirstlane((int)sm.path[d]);
+          sf = __builtin_amdgcn_readfirstlane(sm.sofar[d]);
+          h = 0;
+#pragma unroll
+          for (int i = 0; i < K; ++i) h += v[i];
+          // (a walk is recorded whole or not at all)
+          rec = Sm::Memo && nrec + h <= kNoPool && nwalk < kNoWalks;
           fresh = false;
           continue;
         }
-        if (fresh) {  // v and its lower neighbours have to lie in the box
+        uint64_t cell = 0;
+        if constexpr (Sm::Memo) {
+#pragma unroll
+          for (int i = 0; i < K - 1; ++i) cell |= (uint64_t)(uint32_t)v[i] << (13 * i);
+          if (fresh && np > 0) {
+            // met a record of this cell and score?  (one lookup per new cell)
+            int x = __builtin_amdgcn_readfirstlane((int)sm.head[h]);
+            while (x != 0xFFFF) {
+              const bool same = sm.cell[x] == cell && sm.score[x] == sf;
+              if (__builtin_amdgcn_readfirstlane((int)same)) break;
+              x = __builtin_amdgcn_readfirstlane((int)sm.link[x]);
+            }
+            if (x != 0xFFFF) {
+              if (rec) {  // this walk goes on with that record
+                sm.wend[nwalk] = (uint16_t)nrec;
+                sm.wnext[nwalk] = (int16_t)x;
+                ++nwalk;
+                rec = false;
+              }
+              while (x >= 0) {
+                const int w = __builtin_amdgcn_readfirstlane((int)sm.walk[x]);
+                const int n = __builtin_amdgcn_readfirstlane((int)sm.wend[w]) - x;
+                for (int y = lane; y < n; y += 64) {
+                  sm.path[d + y] = sm.mask[x + y];
+                  sm.pass[d + y] = sm.set[x + y];
+                  sm.sofar[d + y] = sm.score[x + y];
+                }
+                d += n;
+                x = __builtin_amdgcn_readfirstlane((int)sm.wnext[w]);
+                sf = __builtin_amdgcn_readfirstlane(sm.wlast[w]);
+              }
+#pragma unroll
+              for (int i = 0; i < K; ++i) v[i] = 0;
+              h = 0;  // the path is whole
+              continue;
+            }
+          }
+        }
+        {  // v and its lower neighbours have to lie in the box
           bool in = true;
 #pragma unroll
           for (int i = 0; i < K; ++i) in = in && (unsigned)(top[i] - v[i]) <= (unsigned)(E - 2);
@@ -981,19 +1155,14 @@ __global__ __launch_bounds__(kNoThreads) void nearopt_kernel(JobDev jd, Ctrl *ct
           status = ST_EDEVICE;
           break;
         }
-        // residues of v, and SP(col(v, b)) of this lane's mask: residue pairs,
-        // residue-gap pairs
-        int r[K];
-#pragma unroll
-        for (int i = 0; i < K; ++i)
-          r[i] = v[i] >= 1 ? (int)sm.seq[jd.seq_off[i] + v[i] - 1] : 0;
+        // SP(col(v, b)) of this lane's mask: residue pairs, residue-gap pairs
         int32_t sp = 0;
 #pragma unroll
         for (int i = 0; i < K; ++i)
 #pragma unroll
           for (int j = i + 1; j < K; ++j) {
-            const int32_t ps = alpha <= 32 ? (int32_t)sm.sub[r[i] * 32 + r[j]]
-                                           : (int32_t)jd.sub[r[i] * alpha + r[j]];
+            const int32_t ps =
+                sm.pair[i * (2 * K - i - 1) / 2 + (j - i - 1)][(top[i] - v[i]) * E + top[j] - v[j]];
             const int bi = (bl >> i) & 1, bj = (bl >> j) & 1;
             sp += (bi && bj) ? ps : (bi ^ bj) ? gap : 0;
           }
@@ -1007,13 +1176,12 @@ __global__ __launch_bounds__(kNoThreads) void nearopt_kernel(JobDev jd, Ctrl *ct
             x += (top[i] - v[i]) * ipow(E, K - 1 - i);
           }
           const int32_t xi = sm.box[ok ? x + lbox : 0];
-          set = __ballot(ok && (int64_t)xi + sp + sm.sofar[d] >= threshold);
+          set = __ballot(ok && (int64_t)xi + sp + sf >= threshold);
           if (set == 0) {  // a cell off the origin from which no alignment reaches the threshold
             status = ST_EDEVICE;
             break;
           }
           sm.pass[d] = set;  // every lane stores the same value
-          fresh = false;
         } else {
           const uint64_t p = sm.pass[d];
           set = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)p) |
@@ -1031,9 +1199,23 @@ __global__ __launch_bounds__(kNoThreads) void nearopt_kernel(JobDev jd, Ctrl *ct
         // every lane stores the same values; the one wave's LDS accesses stay
         // in program order, so no barrier is needed before they are read back
         sm.path[d] = (uint8_t)b;
-        sm.sofar[d + 1] = sm.sofar[d] + spb;
+        sm.sofar[d] = sf;
+        if constexpr (Sm::Memo) {
+          if (rec && fresh) {
+            sm.cell[nrec] = cell;
+            sm.score[nrec] = sf;
+            sm.set[nrec] = (uint32_t)set;
+            sm.mask[nrec] = (uint8_t)b;
+            sm.walk[nrec] = (uint16_t)nwalk;
+            sm.link[nrec] = sm.head[h];
+            sm.head[h] = (uint16_t)nrec;
+            ++nrec;
+          }
+        }
+        sf += spb;
 #pragma unroll
         for (int i = 0; i < K; ++i) v[i] -= (b >> i) & 1;
+        h -= __builtin_popcount(b);
         ++d;
         tried = 0;
         fresh = true;

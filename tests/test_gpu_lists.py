@@ -1,0 +1,71 @@
+"""GPU parity of the co-optimal and near-optimal lists where their records can
+go wrong: many alignments on inputs full of ties (records met again and again,
+more walks than are recorded), a sum of lengths beyond the records, every k of
+the near-optimal mode, both sides of the co-optimal length bound.  Rows and
+scores equal the oracle's exactly.
+"""
+import sys
+
+import numpy as np
+import pytest
+
+import paper_2311_17530_amd as msa
+from msa_inputs import dna_scoring, protein_scoring
+from oracle import oracle_coopt, oracle_nearopt
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    msa.lib()
+
+
+def draw(seed, lens, alpha):
+    rng = np.random.Generator(np.random.PCG64(seed))
+    return [rng.integers(0, alpha, size=n).astype(np.uint8) for n in lens]
+
+
+@pytest.mark.parametrize("lens,paths,delta", [
+    ([60, 50], 1500, 0), ([60, 50], 700, 6), ([1600, 1520], 20, 3), ([90, 20, 40], 600, 2),
+    ([25, 31, 28], 300, 9), ([9, 14, 7, 12], 300, 12), ([6, 5, 7, 4, 6], 200, 20),
+    ([4, 3, 4, 3, 2, 4], 150, 14)], ids=str)
+def test_nearopt_list(lens, paths, delta):
+    for seed in range(2):
+        sub, gap = dna_scoring() if seed == 0 else protein_scoring()
+        seqs = draw(900 + seed, lens, 4)
+        say("nearopt", lens, paths, delta, "seed", seed)
+        s0, want = oracle_nearopt(seqs, sub, gap, delta, paths)
+        dev = msa.DeviceAligner(lens, sub, gap, nearopt=True)
+        dev.set_sequences(seqs)
+        for _ in range(2):
+            dev.run_nearopt(delta, paths)
+            s1, got = dev.result_nearopt()
+            assert s1 == s0 and len(got) == len(want)
+            for (sa, ra), (sb, rb) in zip(got, want):
+                assert sa == sb and np.array_equal(ra, rb)
+
+
+@pytest.mark.parametrize("lens,paths", [
+    ([80, 70], 2000), ([4000, 4191], 8), ([4000, 4192], 8), ([70, 15, 33], 800),
+    ([30, 30, 30], 500)], ids=str)
+def test_coopt_list(lens, paths):
+    sub, gap = dna_scoring()
+    seqs = draw(77, lens, 4)
+    say("coopt", lens, paths)
+    s0, want = oracle_coopt(seqs, sub, gap, paths)[:2]
+    dev = msa.DeviceAligner(lens, sub, gap, cooptimal=True)
+    dev.set_sequences(seqs)
+    for _ in range(2):
+        dev.run_coopt(paths)
+        s1, got = dev.result_coopt()
+        assert s1 == s0 and len(got) == len(want)
+        assert all(np.array_equal(a, b) for a, b in zip(got, want))
