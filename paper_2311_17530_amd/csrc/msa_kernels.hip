@@ -1715,7 +1715,16 @@ int launch_fill(const JobDev &jd, Ctrl *ctrl, const int32_t *order, int grid, in
 }
 
 int launch_traceback(const JobDev &jd, Ctrl *ctrl, hipStream_t s) {
-  if (jd.k <= kTrMaxK && jd.total_len <= kTrMaxTotal) return launch_trace(jd, ctrl, s);
+  // The walkers start later than a single wave and share its compute unit, so
+  // they lose where the walk is short (single wave and walkers, related and
+  // unrelated sequences: 24^3 8.1 and 9.8, 9.0 and 11.1 us; 40^3 11.0 and 13.0, 12.8
+  // and 14.9; 64^3 17.9 and 16.8, 19.5 and 18.8; 24^4 12.4 and 12.2, 12.6 and 13.3;
+  // 40^4 19.1 and 14.9, 20.5 and 21.9), but for k = 5, whose single walk changes its
+  // tile every few columns (12^5 11.8 and 9.0, 23 and 12).
+  int longest = 0;
+  for (int i = 0; i < jd.k; ++i) longest = jd.n[i] > longest ? jd.n[i] : longest;
+  const bool brief = jd.k <= 3 ? longest < 64 : jd.k == 4 && longest < 32;
+  if (jd.k <= kTrMaxK && jd.total_len <= kTrMaxTotal && !brief) return launch_trace(jd, ctrl, s);
   MSA_DISPATCH_K(jd.k, launch_traceback_k, jd, ctrl, s);
 }
 

@@ -24,8 +24,11 @@
 //
 // What bounds it: the latency of a tile crossing (a walker waits 1 to 2 us for
 // the next tile's directions, at every fourth column or so) times the columns
-// of the longest piece.  Measured, single walk and now: 512^3 129 and 27 us,
-// 128^4 58 and 23, 40^5 60 and 15, 40^3 16 and 13, 157 x 93 x 201 46 and 36.
+// of the longest piece.  Measured, single walk and walkers: related sequences
+// 384^3 94 and 25 us, 128^4 69 and 29, 40^5 57 and 16; unrelated ones, whose walks
+// meet late, 384^3 106 and 78, 128^4 68 and 66, 40^5 76 and 32.  Short walks of k <= 4
+// keep the single wave (launch_traceback).
+//
 // Co-optimal alignments (co-optimal mode, k <= 3): the depth-first enumeration
 // takes at every new cell the lowest mask of its tie set, so below a cell of
 // the first alignment (the one the walkers found) a new alignment goes on like
@@ -110,7 +113,15 @@ struct TrRec {
 // .. f0 + nf - 1, writes its masks to `to` and stops where it meets one (met),
 // or at a sum h_stop or less (-1: never), or at a tile's entry once `done` is
 // set.  On return v, h is the cell where it stopped.
-template <int K, bool egf, bool coopt>
+//
+// Wave 0 (main: h_own is the end cell's sum, no records) watches only where it
+// enters a tile: walks that met stay together, and its steps are the longest
+// chain where the guesses are worth little.  The others watch one family at
+// every step, since a range may be shorter than a tile.  (Wave 0 watching at
+// every step, three families: unrelated sequences 40^3 21.7 us against 15.4, 96^3
+// 46 and 29; the others watching at entries alone: related sequences 128^3 27 us
+// against 15.)
+template <int K, bool egf, bool coopt, bool main>
 __device__ __forceinline__ int tr_walk(const JobDev &jd, const TrRec &rc, uint8_t *dirb, int (&v)[K], int &h,
                        int h_own, int h_stop, int fam, int f0, int nf, uint8_t *to, int &met,
                        const int32_t &done) {
@@ -121,6 +132,7 @@ __device__ __forceinline__ int tr_walk(const JobDev &jd, const TrRec &rc, uint8_
   constexpr int CPL = (NQ + 63) / 64;  // chunks per lane
   const int lane = tr_tid() & 63;
   u32x4 *const lds4 = reinterpret_cast<u32x4 *>(dirb);
+  uint8_t *const own = rc.own + fam * rc.n;
   int c[K], q[K];
   int64_t t = 0;
   {
@@ -161,7 +173,7 @@ __device__ __forceinline__ int tr_walk(const JobDev &jd, const TrRec &rc, uint8_
   // the watched records of sums w0 - lane, read again every kTrWin sums (an
   // owner may be writing them: what is not there yet is no meeting)
   constexpr int kTrWin = 16;
-  uint32_t wlo[kTrFam<K>], whi[kTrFam<K>];
+  uint64_t win = 0;
   int w0 = INT32_MAX;
   for (;;) {
     if (h <= h_own && h > 0 && __hip_atomic_load(&done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
@@ -176,6 +188,12 @@ __device__ __forceinline__ int tr_walk(const JobDev &jd, const TrRec &rc, uint8_
       d += q[i] * C::dstride(i);
       Q |= (uint32_t)q[i] << (QW * i);
       if (i < K - 1) (i < 2 ? plo : phi) |= (uint32_t)v[i] << (16 * (i & 1));
+    }
+    uint64_t seen[kTrFam<K>];  // (main: the watched records here)
+    if constexpr (main) {
+#pragma unroll
+      for (int f = 0; f < kTrFam<K>; ++f)
+        seen[f] = rc.pos[(f0 + min(f, max(nf - 1, 0))) * rc.n + h];
     }
     // prefetch the face neighbours' blocks (an absent neighbour: this tile's)
 #pragma unroll
@@ -193,34 +211,34 @@ __device__ __forceinline__ int tr_walk(const JobDev &jd, const TrRec &rc, uint8_
     // a cell with v_i = 0, lies in a tile of its own: no test here.)
     int cand = dirb[max(d - loff, 0)];
     int byte = __builtin_amdgcn_readlane(cand, 0);
+    if constexpr (main) {
+      const uint64_t cell = ((uint64_t)phi << 32) | plo;
+      int mf = -1;
+#pragma unroll
+      for (int f = kTrFam<K> - 1; f >= 0; --f)
+        mf = __builtin_amdgcn_ballot_w64(f < nf && seen[f] == cell) ? f : mf;
+      if (mf >= 0) {
+        met = f0 + mf;
+        return kTrMerged;
+      }
+    }
     int how = -1;
     for (;;) {
-      if (h <= h_own) {
-        if (h <= h_stop) {
-          how = kTrOpen;
-          break;
-        }
-        if (w0 - h >= kTrWin) {
-          w0 = h;
-#pragma unroll
-          for (int f = 0; f < kTrFam<K>; ++f) {
-            const uint64_t r = f < nf ? rc.pos[(f0 + f) * rc.n + max(h - lane, 0)] : ~0ull;
-            wlo[f] = (uint32_t)r;
-            whi[f] = (uint32_t)(r >> 32);
+      if constexpr (!main) {
+        if (h <= h_own) {
+          if (h <= h_stop) {
+            how = kTrOpen;
+            break;
           }
-        }
-        uint64_t eq = 0;
-        int mf = 0;
-#pragma unroll
-        for (int f = kTrFam<K> - 1; f >= 0; --f) {
-          const uint64_t e = __ballot(lane == w0 - h && wlo[f] == plo && whi[f] == phi);
-          mf = e ? f : mf;
-          eq |= e;
-        }
-        if (eq) {
-          met = f0 + mf;
-          how = kTrMerged;
-          break;
+          if (w0 - h >= kTrWin) {
+            w0 = h;
+            win = rc.pos[f0 * rc.n + max(h - lane, 0)];
+          }
+          if (__ballot(lane == w0 - h && (uint32_t)win == plo && (uint32_t)(win >> 32) == phi)) {
+            met = f0;
+            how = kTrMerged;
+            break;
+          }
         }
       }
       int b;
@@ -237,15 +255,16 @@ __device__ __forceinline__ int tr_walk(const JobDev &jd, const TrRec &rc, uint8_
       byte = __builtin_amdgcn_readlane(cand, b);
       d -= __builtin_amdgcn_readlane(loff, b);
       cand = dirb[max(d - loff, 0)];
-      if (h > h_own) {  // (every lane stores the same values)
-        rc.pos[fam * rc.n + h] = ((uint64_t)phi << 32) | plo;
-        rc.own[fam * rc.n + h] = (uint8_t)b;
-      } else {
+      // (every lane stores the same values)
+      if constexpr (main) {
         to[h] = (uint8_t)b;
+      } else {
+        if (h > h_own) rc.pos[fam * rc.n + h] = ((uint64_t)phi << 32) | plo;
+        (h > h_own ? own : to)[h] = (uint8_t)b;
+        plo -= __builtin_amdgcn_readlane(llo, b);
+        if constexpr (K > 3) phi -= __builtin_amdgcn_readlane(lhi, b);
       }
       Q -= __builtin_amdgcn_readlane(lq, b);
-      plo -= __builtin_amdgcn_readlane(llo, b);
-      if constexpr (K > 3) phi -= __builtin_amdgcn_readlane(lhi, b);
       h -= __builtin_amdgcn_readlane(lh, b);
       if ((Q & guards) != guards) break;  // left the tile
     }
@@ -357,7 +376,7 @@ __device__ __forceinline__ void tr_walk_all(const JobDev &jd, TrSmem<K> &sm, con
     const int f = (wave - 1) / (G - 1), g = (wave - 1) % (G - 1) + 1;
     const int hp = g > 1 ? sm.hstart[wave - 1] : -1, hpp = g > 2 ? sm.hstart[wave - 2] : -1;
     h = tr_guess<K>(end, most, f, g, G, v);
-    const int how = tr_walk<K, egf, coopt>(
+    const int how = tr_walk<K, egf, coopt, false>(
         jd, rc, sm.dirb[wave], v, h, __builtin_amdgcn_readfirstlane(hp),
         __builtin_amdgcn_readfirstlane(hpp), f, f, 1, rc.ov + f * rc.n, met, sm.done);
     sm.hstop[wave] = h;
@@ -365,10 +384,11 @@ __device__ __forceinline__ void tr_walk_all(const JobDev &jd, TrSmem<K> &sm, con
     for (int i = 0; i < K; ++i) sm.vstop[wave][i] = v[i];
     __hip_atomic_store(&sm.state[wave], how, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
   } else if (wave == 0) {
+    __builtin_amdgcn_s_setprio(3);  // the others' work may be of no use, this wave's always is
 #pragma unroll
     for (int i = 0; i < K; ++i) v[i] = end[i];
     h = H;
-    int how = tr_walk<K, egf, coopt>(jd, rc, sm.dirb[0], v, h, H, -1, 0, 0, G > 1 ? F : 0, rc.path,
+    int how = tr_walk<K, egf, coopt, true>(jd, rc, sm.dirb[0], v, h, H, -1, 0, 0, G > 1 ? F : 0, rc.path,
                                      met, sm.never);
     // From a meeting the path goes down the family's walkers, each up to its own
     // meeting with the next, to the first that met nobody: as soon as those
@@ -401,7 +421,7 @@ __device__ __forceinline__ void tr_walk_all(const JobDev &jd, TrSmem<K> &sm, con
 #pragma unroll
       for (int i = 0; i < K; ++i) v[i] = __builtin_amdgcn_readfirstlane(sm.vstop[low][i]);
       if (how == kTrOpen)  // go on alone until the walk meets someone
-        how = tr_walk<K, egf, coopt>(jd, rc, sm.dirb[0], v, h, H, -1, 0, 0, F, rc.path, met,
+        how = tr_walk<K, egf, coopt, true>(jd, rc, sm.dirb[0], v, h, H, -1, 0, 0, F, rc.path, met,
                                      sm.never);
     }
     sm.ns = ns;

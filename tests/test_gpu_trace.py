@@ -72,3 +72,18 @@ def test_egf_rows_match_oracle(lens):
         s0, r0 = oracle_align_egf(seqs, sub, gap)[:2]
         s1, r1 = dev.result()
         assert s1 == s0 and np.array_equal(r1, r0)
+
+
+# both sides of the longest length from which the walkers take the walk
+@pytest.mark.parametrize("lens", [[63, 10], [64, 10], [63, 20, 41], [12, 64, 30], [31, 12, 9, 10],
+                                  [10, 9, 32, 12]], ids=lambda s: "x".join(map(str, s)))
+def test_rows_match_oracle_at_the_walkers_bound(lens):
+    for sub, gap in (protein_scoring(), dna_scoring()):
+        dev = msa.DeviceAligner(lens, sub, gap)
+        seqs = draw(900 + sum(lens), lens, sub.shape[0])
+        say("trace", lens)
+        dev.set_sequences(seqs)
+        dev.run()
+        s0, r0 = oracle_align(seqs, sub, gap)[:2]
+        s1, r1 = dev.result()
+        assert s1 == s0 and np.array_equal(r1, r0)
