@@ -25,6 +25,15 @@ namespace msa {
 inline void launch_begin() { (void)hipGetLastError(); }
 inline int launch_end() { return hipGetLastError() == hipSuccess ? 0 : -1; }
 
+// A pointer into device memory, known as such to the compiler.  What a kernel
+// reads from a descriptor in memory, or forms from an integer, is a pointer to
+// anywhere: its accesses are flat ones, which the waits for LDS also wait for and
+// which take 64-bit addresses in vector registers.
+template <class T>
+__device__ __forceinline__ T *as_global(T *p) {
+  return (T *)(__attribute__((address_space(1))) T *)(uint64_t)p;
+}
+
 constexpr int kMaxK = 8;
 constexpr int kNegKey = -(1 << 30);  // "-infinity" key; see range check
 
@@ -249,6 +258,32 @@ struct Sweep4Dev {
 };
 static_assert(sizeof(Sweep4Dev) % 4 == 0, "copied by words");
 
+// Streaming fill of k = 5 (msa_sweep5.hip): a workgroup owns the 4^4 lines of one
+// tile column along dimension 4.
+constexpr int kS5SeqMax = 128;     // longest fifth sequence (pair scores kept in LDS)
+// words before and after the exchange region that a block may read (up to 8
+// steps before a slice and 40 after it)
+constexpr int kS5Step = 176;       // exchange words of a block's step
+constexpr int kS5PadFront = 8 * 256, kS5PadBack = 40 * 256;
+
+// Device descriptor of a streaming k = 5 fill.
+struct Sweep5Dev {
+  int32_t n[5];
+  int32_t nb[4];              // blocks (tile columns) along dimensions 0..3
+  int32_t S;                  // steps a block's slice of the exchange region holds
+  int32_t ts[4];              // tile strides of dimensions 0..3 (dimension 4: 1)
+  int32_t alpha, gap;         // batched launches (the plain path reads the control block)
+  const uint8_t *seqs;
+  const int8_t *sub;
+  int32_t *x;                 // exchange region, [block][step][word]
+  uint8_t *dir;               // tile-major direction blocks
+  int64_t *score_out;
+  const int32_t *order;       // blocks in the order workgroups take them (plain path)
+  int32_t *status;            // batched launches: the job's status word, and the launch's
+  int32_t *kbase;             // next queue slot of its blocks of each coordinate sum
+};
+static_assert(sizeof(Sweep5Dev) % 4 == 0, "copied by words");
+
 // Blocks are taken in ascending order of this key, by earliest start: a block
 // along dimension 0 follows its predecessor by a few steps, one along dimension
 // 1 or 2 by its 16 lanes more.
@@ -270,11 +305,12 @@ struct BatchArgs {
   int64_t tiles;              // tiles of all jobs
   int64_t cols;               // columns of all jobs (queue length)
   int32_t njobs;
-  // streaming k = 4 jobs: descriptors, blocks before each of them, the block
+  // streaming k = 4 (k class 1: k = 5) jobs: descriptors, blocks before each of them, the block
   // queue ((job, block) pairs), their number, the queue's length and the tag
   // of the launch's exchange values
   int32_t s4n;
   const Sweep4Dev *s4jobs;
+  const Sweep5Dev *s5jobs;
   const int32_t *s4pre;
   int32_t *s4q;
   int32_t s4total, s4tag;

@@ -1767,6 +1767,7 @@ static int launch_batch_k(const BatchArgs *d_args, const JobDev *d_jobs, Ctrl *c
   hipLaunchKernelGGL((batch_fill_kernel<KLO, KHI, kBatchThreads>), dim3(grid),
                      dim3(kBatchThreads), 0, s, d_args, d_jobs, ctrl);
   if (KLO <= 4 && 4 <= KHI) launch_batch_sweep4(d_args, ctrl, s);
+  if (KLO <= 5 && 5 <= KHI) launch_batch_sweep5(d_args, ctrl, s);
   if (KHI <= kTrMaxK) launch_batch_trace(KHI <= 4 ? 0 : 1, d_args, d_jobs, ctrl, s);
   hipLaunchKernelGGL((batch_traceback_kernel<KLO, KHI>),
                      dim3(KHI <= kTrMaxK ? kBatchLongGrid : kBatchTraceGrid), dim3(64), 0, s,

@@ -44,16 +44,20 @@ struct JobSizes {
   int64_t small = 0;     // host-initialised bytes
   int64_t big = 0;       // device-only bytes (path, faces, dir)
   int64_t out = 0;       // output rows
-  bool s4 = false;       // streaming k = 4 fill
+  bool s4 = false;       // streaming fill (k = 4, 5)
   std::vector<int32_t> keys;  // its blocks per key
   int64_t x = 0;         // its exchange regions (bytes)
   int64_t total(int64_t ntiles) const {
     return small + big + x + out + 12 * ntiles + (int64_t)sizeof(JobDev) + 64 +
-           (s4 ? (int64_t)sizeof(Sweep4Dev) + 8 : 0);
+           (s4 ? (int64_t)std::max(sizeof(Sweep4Dev), sizeof(Sweep5Dev)) + 8 : 0);
   }
+  int64_t blocks() const {  // of a streaming fill
+    return p.k == 5 ? p.ntiles / p.P[4] : (int64_t)p.s4_nb[0] * p.s4_nb[1] * p.s4_nb[2];
+  }
+  int32_t steps() const { return p.k == 5 ? p.s5_steps : p.s4_steps; }
 };
 
-// cap: bytes of the arena the job has to fit.  A k = 4 job takes the streaming
+// cap: bytes of the arena the job has to fit.  A k = 4 or 5 job takes the streaming
 // fill where that is possible; where only the tile fill's smaller layout fits
 // the arena, it keeps that.
 int sizes_of(const msa_job &j, int64_t cap, JobSizes *s) {
@@ -70,11 +74,11 @@ int sizes_of(const msa_job &j, int64_t cap, JobSizes *s) {
            a256(std::max<int64_t>(p.face_elems * 4, 256)) +   // face planes
            a256(p.ntiles * p.dbs);                            // direction blocks
   s->out = a256((int64_t)j.k * s->cap);
-  if (sweep4_eligible(p, j.alpha, 0)) {
+  if (sweep4_eligible(p, j.alpha, 0) || sweep5_eligible(p, j.alpha, 0)) {
     JobSizes t = *s;
     t.s4 = true;
-    t.keys = sweep4_key_counts(p);
-    t.x = a256(sweep4_x_words(p) * 4);
+    t.keys = p.k == 5 ? sweep5_key_counts(p) : sweep4_key_counts(p);
+    t.x = a256((p.k == 5 ? sweep5_x_words(p) : sweep4_x_words(p)) * 4);
     t.small = a256(std::max<int64_t>(p.total_len, 1)) + a256((int64_t)t.keys.size() * 4) + 256;
     t.big = a256(std::max<int64_t>(p.total_len, 1)) + a256(p.ntiles * p.dbs);
     if (t.total(p.ntiles) + Launch::overhead_bytes(1, p.ntiles) <= cap) *s = t;
@@ -245,17 +249,16 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
   if (off_args != kArgsOff || off_jobs != kJobsOff) return MSA_EINVAL;
   const int64_t off_jt = o;    o = a256(o + (int64_t)(nj + 1) * 8);
   const int64_t off_jc = o;    o = a256(o + (int64_t)(nj + 1) * 8);
-  int n4 = 0;               // streaming k = 4 jobs, their blocks and exchange bytes
+  int n4 = 0;               // streaming jobs, their blocks and exchange bytes
   int64_t blocks4 = 0, x4 = 0;
   for (int i = 0; i < nj; ++i)
     if (sz[i].s4) {
       ++n4;
-      const int32_t *nb = sz[i].p.s4_nb;
-      blocks4 += (int64_t)nb[0] * nb[1] * nb[2];
+      blocks4 += sz[i].blocks();
       x4 += sz[i].x;
     }
   if (blocks4 >= ((int64_t)1 << 30)) return MSA_ENOMEM;
-  const int64_t off_s4jobs = o; o = a256(o + (int64_t)n4 * sizeof(Sweep4Dev));
+  const int64_t off_s4jobs = o; o = a256(o + (int64_t)n4 * (kc == 1 ? sizeof(Sweep5Dev) : sizeof(Sweep4Dev)));
   const int64_t off_s4pre = o;  o = a256(o + (int64_t)(n4 + 1) * 4);
   // substitution matrices, deduplicated by content
   std::map<std::string, int64_t> subs;
@@ -340,6 +343,7 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
   std::vector<int64_t *> wave_base(nj);
   JobDev *jd_all = reinterpret_cast<JobDev *>(h + off_jobs);
   Sweep4Dev *s4_all = reinterpret_cast<Sweep4Dev *>(h + off_s4jobs);
+  Sweep5Dev *s5_all = reinterpret_cast<Sweep5Dev *>(h + off_s4jobs);
   int32_t *s4pre = reinterpret_cast<int32_t *>(h + off_s4pre);
   std::vector<int32_t *> s4base;        // queue slots per key, of each streaming job
   std::vector<const JobSizes *> s4size;
@@ -409,23 +413,36 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
     memcpy(&jd_all[i], &jd, sizeof(JobDev));
     if (s4) {
       const int n = (int)s4base.size() - 1;
-      Sweep4Dev sd;
-      fill_sweep4dev(p, &sd);
-      sd.alpha = j.alpha;
-      sd.gap = j.gap;
-      sd.seqs = jd.seqs;
-      sd.sub = jd.sub;
-      sd.x0 = reinterpret_cast<int32_t *>(d_ + xo) + kS4PadFront;
-      sd.x1 = sd.x0 + p.s4_x0;
-      sd.x2 = sd.x1 + p.s4_x1;
+      int32_t *const x = reinterpret_cast<int32_t *>(d_ + xo);
+      int32_t *const kb = reinterpret_cast<int32_t *>(d_ + o_wcnt);
       xo += sz[i].x;
-      sd.dir = jd.dir;
-      sd.score_out = jd.score_out;
-      sd.status = jd.jstatus;
-      sd.kbase = reinterpret_cast<const int32_t *>(d_ + o_wcnt);
-      memcpy(&s4_all[n], &sd, sizeof(sd));
+      auto fill = [&](auto &sd) {
+        sd.alpha = j.alpha;
+        sd.gap = j.gap;
+        sd.seqs = jd.seqs;
+        sd.sub = jd.sub;
+        sd.dir = jd.dir;
+        sd.score_out = jd.score_out;
+        sd.status = jd.jstatus;
+        sd.kbase = kb;
+      };
+      if (kc == 1) {
+        Sweep5Dev sd;
+        fill_sweep5dev(p, &sd);
+        fill(sd);
+        sd.x = x + kS5PadFront;
+        memcpy(&s5_all[n], &sd, sizeof(sd));
+      } else {
+        Sweep4Dev sd;
+        fill_sweep4dev(p, &sd);
+        fill(sd);
+        sd.x0 = x + kS4PadFront;
+        sd.x1 = sd.x0 + p.s4_x0;
+        sd.x2 = sd.x1 + p.s4_x1;
+        memcpy(&s4_all[n], &sd, sizeof(sd));
+      }
       if (n == 0) s4pre[0] = 0;
-      s4pre[n + 1] = s4pre[n] + p.s4_nb[0] * p.s4_nb[1] * p.s4_nb[2];
+      s4pre[n + 1] = s4pre[n] + (int32_t)sz[i].blocks();
     }
     meta_[i].k = j.k;
     meta_[i].cap = sz[i].cap;
@@ -466,7 +483,7 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
   // left to run alone at the end; within a job the keys ascend.
   {
     auto bin = [&](int n, int key) {
-      return (int)s4size[n]->keys.size() - 1 - key + s4size[n]->p.s4_steps / 5;
+      return (int)s4size[n]->keys.size() - 1 - key + s4size[n]->steps() / 5;
     };
     int top = -1;
     for (int n = 0; n < n4; ++n) top = std::max(top, bin(n, 0));
@@ -500,6 +517,7 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
   args.njobs = nj;
   args.s4n = n4;
   args.s4jobs = reinterpret_cast<const Sweep4Dev *>(d_ + off_s4jobs);
+  args.s5jobs = reinterpret_cast<const Sweep5Dev *>(d_ + off_s4jobs);
   args.s4pre = reinterpret_cast<const int32_t *>(d_ + off_s4pre);
   args.s4q = reinterpret_cast<int32_t *>(d_ + off_s4q);
   args.s4total = (int32_t)blocks4;

@@ -96,6 +96,16 @@ int make_plan(const int32_t *lens, int32_t k, Plan *p, bool streams) {
     q.s4 = sweep4_x_words(q) * 4 <= std::max<int64_t>(2 * q.face_elems * 4, kS4SmallX) &&
            (int64_t)q.tstride[0] * q.dbs < ((int64_t)1 << 32);
   }
+  if (streams && k == 5 && q.n[4] <= kS5SeqMax) {
+    // the most steps a block runs
+    q.s5_steps = ((q.n[4] + 3) / 4 * 4 + 1 + 4 * (q.T - 1) + 7) / 8 * 8;
+    q.s5_x = q.ntiles / q.P[4] * q.s5_steps * kS5Step;
+    // Shapes whose exchange region would be far larger than the face planes
+    // keep the tile fill; the kernel forms offsets in the region in 32 bits.
+    const int64_t bytes = sweep5_x_words(q) * 4;
+    q.s5 = bytes <= std::max<int64_t>(2 * q.face_elems * 4, kS4SmallX) &&
+           bytes < ((int64_t)1 << 32);
+  }
   // workspace layout
   int64_t o = 0;
   q.off_ctrl = o;   o = align256(o + (int64_t)sizeof(Ctrl));
@@ -108,10 +118,11 @@ int make_plan(const int32_t *lens, int32_t k, Plan *p, bool streams) {
   q.off_faces = o;
   if (!mul_ok(q.face_elems, 4, lim)) return MSA_ENOMEM;
   // at least one block, so a clamped (unconditional) read at offset 0 is in
-  // range; the streaming k = 4 fill's exchange regions share the planes' memory
+  // range; the streaming k = 4 and k = 5 fills' exchange regions share the planes' memory
   // (the words of a tile fill carry no valid tag, and it reads none of theirs)
   o = align256(o + std::max<int64_t>(
-                       {q.face_elems * 4, q.s4 ? sweep4_x_words(q) * 4 : 0, (int64_t)256}));
+                       {q.face_elems * 4, q.s4 ? sweep4_x_words(q) * 4 : 0,
+                        q.s5 ? sweep5_x_words(q) * 4 : 0, (int64_t)256}));
   q.off_dir = o;
   if (!mul_ok(q.ntiles, q.dbs, lim)) return MSA_ENOMEM;
   o = align256(o + q.ntiles * q.dbs);
@@ -150,6 +161,10 @@ int make_plan(const int32_t *lens, int32_t k, Plan *p, bool streams) {
   if (q.s4) {
     q.off_s4order = o;
     o = align256(o + (int64_t)q.s4_nb[0] * q.s4_nb[1] * q.s4_nb[2] * 4);
+  }
+  if (q.s5) {
+    q.off_s4order = o;
+    o = align256(o + q.ntiles / q.P[4] * 4);
   }
   q.bytes = o;
   *p = q;
@@ -202,6 +217,45 @@ void make_sweep4_order(const Plan &p, std::vector<int32_t> *order) {
   for (int b0 = 0; b0 < nb0; ++b0)
     for (int b1 = 0; b1 < nb1; ++b1)
       for (int b2 = 0; b2 < nb2; ++b2) (*order)[count[key(b0, b1, b2)]++] = b++;
+}
+
+int64_t sweep5_x_words(const Plan &p) { return kS5PadFront + p.s5_x + kS5PadBack; }
+
+bool sweep5_eligible(const Plan &p, int alpha, int32_t flags) {
+  return p.s5 && flags == 0 && alpha >= 1 && alpha <= kS4SubMax;
+}
+
+void fill_sweep5dev(const Plan &p, Sweep5Dev *sd) {
+  memset(sd, 0, sizeof(*sd));
+  for (int i = 0; i < 5; ++i) sd->n[i] = p.n[i];
+  for (int i = 0; i < 4; ++i) {
+    sd->nb[i] = p.P[i];
+    sd->ts[i] = p.tstride[i];
+  }
+  sd->S = p.s5_steps;
+}
+
+std::vector<int32_t> sweep5_key_counts(const Plan &p) {
+  std::vector<int32_t> cnt(1, 1);
+  for (int i = 0; i < 4; ++i) {
+    std::vector<int32_t> nxt(cnt.size() + p.P[i] - 1, 0);
+    for (size_t x = 0; x < cnt.size(); ++x)
+      for (int c = 0; c < p.P[i]; ++c) nxt[x + c] += cnt[x];
+    cnt.swap(nxt);
+  }
+  return cnt;
+}
+
+void make_sweep5_order(const Plan &p, std::vector<int32_t> *order) {
+  const std::vector<int32_t> cnt = sweep5_key_counts(p);
+  std::vector<int32_t> at(cnt.size(), 0);
+  for (size_t x = 1; x < cnt.size(); ++x) at[x] = at[x - 1] + cnt[x - 1];
+  order->assign(p.ntiles / p.P[4], 0);
+  int32_t b = 0;
+  for (int c0 = 0; c0 < p.P[0]; ++c0)
+    for (int c1 = 0; c1 < p.P[1]; ++c1)
+      for (int c2 = 0; c2 < p.P[2]; ++c2)
+        for (int c3 = 0; c3 < p.P[3]; ++c3) (*order)[at[c0 + c1 + c2 + c3]++] = b++;
 }
 
 // The streaming k = 3 fill covers the plain mode and one of the end-gap-free,

@@ -50,12 +50,25 @@ struct Plan {
   int32_t s4_nb[3] = {}, s4_steps = 0;
   int64_t s4_x0 = 0, s4_x1 = 0, s4_x2 = 0;  // int32 elements
   int64_t off_s4order = 0;
+  // streaming fill of k = 5: one block per tile column along dimension 4, steps
+  // and words of the exchange region (at off_faces), the block order at
+  // off_s4order
+  bool s5 = false;
+  int32_t s5_steps = 0;
+  int64_t s5_x = 0;          // int32 elements
 };
 
 // The streaming k = 4 fill runs the plain mode of k = 4 plans whose alphabet
 // and fourth sequence fit its LDS tables.
 bool sweep4_eligible(const Plan &p, int alpha, int32_t flags);
 int64_t sweep4_x_words(const Plan &p);
+// The streaming k = 5 fill runs the plain mode of k = 5 plans whose alphabet
+// and fifth sequence fit its LDS tables.
+bool sweep5_eligible(const Plan &p, int alpha, int32_t flags);
+int64_t sweep5_x_words(const Plan &p);
+void fill_sweep5dev(const Plan &p, Sweep5Dev *sd);
+std::vector<int32_t> sweep5_key_counts(const Plan &p);  // blocks per coordinate sum
+void make_sweep5_order(const Plan &p, std::vector<int32_t> *order);
 // Sizes of a streaming k = 4 fill (no pointers).
 void fill_sweep4dev(const Plan &p, Sweep4Dev *sd);
 // Blocks per key (sweep4_key), from key 0 to the last block's.

@@ -119,6 +119,12 @@ int prepare_workspace(const Plan &p, char *ws, const int8_t *submat, int alpha, 
                               hipMemcpyHostToDevice, s) == hipSuccess;
     ok = ok && hipMemsetAsync(ws + p.off_faces, 0, (size_t)sweep4_x_words(p) * 4, s) == hipSuccess;
   }
+  if (sweep5_eligible(p, alpha, flags)) {  // and for k = 5
+    make_sweep5_order(p, &s4order);
+    ok = ok && hipMemcpyAsync(ws + p.off_s4order, s4order.data(), s4order.size() * 4,
+                              hipMemcpyHostToDevice, s) == hipSuccess;
+    ok = ok && hipMemsetAsync(ws + p.off_faces, 0, (size_t)sweep5_x_words(p) * 4, s) == hipSuccess;
+  }
   ok = ok && hipStreamSynchronize(s) == hipSuccess;
   std::lock_guard<std::mutex> lk(g_mu);
   if (ok) {
@@ -168,6 +174,8 @@ static int run_fill(const Plan &p, char *ws, JobDev &jd, hipStream_t s, int alph
     return launch_sweep3(p, ws, jd, ctrl, workspace_flags(ws), s);
   if (tc.variant != 2 && sweep4_eligible(p, alpha, workspace_flags(ws)))
     return launch_sweep4(p, ws, jd, ctrl, s);
+  if (tc.variant != 2 && sweep5_eligible(p, alpha, workspace_flags(ws)))
+    return launch_sweep5(p, ws, jd, ctrl, s);
   const int32_t *order = reinterpret_cast<const int32_t *>(ws + p.off_order);
   int grid = fill_grid(p, tc.variant == 2 ? tc.wpc : 0);
   if (jd.ncols > 0 && grid > jd.ncols) grid = jd.ncols;

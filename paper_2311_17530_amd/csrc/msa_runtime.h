@@ -43,9 +43,12 @@ int launch_sweep3(const Plan &p, char *ws, const JobDev &jd, Ctrl *ctrl, int32_t
                   hipStream_t s);
 // streaming k = 4 fill (msa_sweep4.hip), for plans with sweep4_eligible
 int launch_sweep4(const Plan &p, char *ws, const JobDev &jd, Ctrl *ctrl, hipStream_t s);
+// streaming k = 5 fill (msa_sweep5.hip), for plans with sweep5_eligible
+int launch_sweep5(const Plan &p, char *ws, const JobDev &jd, Ctrl *ctrl, hipStream_t s);
 // the same for the k = 4 jobs of a batched launch: block queue and persistent
 // fill (fixed arguments, for launch_batch)
 void launch_batch_sweep4(const BatchArgs *d_args, Ctrl *ctrl, hipStream_t s);
+void launch_batch_sweep5(const BatchArgs *d_args, Ctrl *ctrl, hipStream_t s);  // and k = 5
 
 // runtime (msa_runtime.cpp)
 int device_cu_count();

@@ -118,7 +118,8 @@ extern "C" void msa_dp_tune_clear(void) { tune_clear(); }
 static std::vector<TuneChoice> candidates(int kind, int k, int32_t max_len) {
   std::vector<TuneChoice> cs;
   if (kind == kTunePlain) {
-    if ((k == 3 && max_len <= kSwSeqMax) || (k == 4 && max_len <= kS4SeqMax))
+    if ((k == 3 && max_len <= kSwSeqMax) || (k == 4 && max_len <= kS4SeqMax) ||
+        (k == 5 && max_len <= kS5SeqMax))
       cs.push_back(TuneChoice{1, 0});
     const int occ = std::max(fill_occupancy(k), 1);
     for (int w = 1; w <= occ; ++w) cs.push_back(TuneChoice{2, w});
