@@ -28,7 +28,9 @@ inline int launch_end() { return hipGetLastError() == hipSuccess ? 0 : -1; }
 // A pointer into device memory, known as such to the compiler.  What a kernel
 // reads from a descriptor in memory, or forms from an integer, is a pointer to
 // anywhere: its accesses are flat ones, which the waits for LDS also wait for and
-// which take 64-bit addresses in vector registers.
+// which take 64-bit addresses in vector registers.  (The batched streaming fills,
+// whose barriers wait for LDS at every step: 256 jobs of k = 3 and 4 30.8 ms with
+// flat accesses, 25.7 with global ones.)
 template <class T>
 __device__ __forceinline__ T *as_global(T *p) {
   return (T *)(__attribute__((address_space(1))) T *)(uint64_t)p;

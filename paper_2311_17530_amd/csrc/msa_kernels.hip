@@ -168,10 +168,11 @@ constexpr int kMaxNap = MSA_MAX_NAP;
 // stores have completed (see process_tile), so a reader that has seen the
 // flag reads the final face values.
 __device__ inline int32_t face_load(const int32_t *p) {
-  return __hip_atomic_load(const_cast<int32_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __hip_atomic_load(as_global(const_cast<int32_t *>(p)), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ inline void face_store(int32_t *p, int32_t v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(as_global(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Tile coordinates of a (wave-uniform) row-major tile index: the digits in
@@ -198,7 +199,7 @@ __device__ void load_tables(const JobDev &jd, int alpha, Smem<K> &sm) {
   const int tid = threadIdx.x;
   if (alpha <= kSubLds)
     for (int e = tid; e < alpha * alpha; e += NT)
-      sm.SUB[(e / alpha) * kSubLds + e % alpha] = (int16_t)(((int32_t)jd.sub[e]) * (1 << K));
+      sm.SUB[(e / alpha) * kSubLds + e % alpha] = (int16_t)(((int32_t)as_global(jd.sub)[e]) * (1 << K));
   if constexpr (K >= 4)
     for (int p = tid; p < Cfg<K>::L; p += NT) sm.LORD[p] = kLineOrder<K>.v[p];
 }
@@ -268,7 +269,7 @@ struct HaloSlots {
 // once (a load in every wait would also wait for the tile's stores: one
 // counter tracks both).
 template <int K, int NT>
-__device__ void process_tile(const JobDev &jd, int alpha, int gap, int tile, int epoch,
+__device__ __forceinline__ void process_tile(const JobDev &jd, int alpha, int gap, int tile, int epoch,
                              Ctrl *ctrl, int32_t *jstatus, Smem<K> &sm,
                              const HaloSlots<K, NT> &hs, bool egf = false,
                              int64_t *best_key = nullptr, bool coopt = false,
@@ -315,7 +316,7 @@ __device__ void process_tile(const JobDev &jd, int alpha, int gap, int tile, int
       const int v = lo[i] + q;
       const bool use = tid < T && q < ext[i] && v >= 1;
       const int pos = use ? jd.seq_off[i] + v - 1 : 0;
-      r[i] = any_seq ? (int)jd.seqs[pos] : 0;
+      r[i] = any_seq ? (int)as_global(jd.seqs)[pos] : 0;
       r[i] = use ? r[i] : 0;
     }
     bool bad = false;
@@ -394,7 +395,7 @@ __device__ void process_tile(const JobDev &jd, int alpha, int gap, int tile, int
   // running wavefront would otherwise flood the memory system with
   // device-coherent loads and slow every tile's halo and face traffic.
   if (wave == 0) {
-    const int32_t *f = jd.flags;
+    const int32_t *f = as_global(jd.flags);
     bool need = false;
     if (K <= kPruneMaxK && prune) {
       need = ((kbits >> (tid & 63)) & 1) != 0;
@@ -402,13 +403,13 @@ __device__ void process_tile(const JobDev &jd, int alpha, int gap, int tile, int
 #pragma unroll
       for (int i = 0; i < K; ++i)
         if ((tid >> i) & 1) tn -= jd.tstride[i];
-      f = jd.flags + (need ? tn : tile);
+      f = as_global(jd.flags) + (need ? tn : tile);
     } else {
 #pragma unroll
       for (int i = 0; i < K; ++i) {
         if (tid == i && c[i] > 0 && !(own0 && i == 0)) {
           need = true;
-          f = jd.flags + (tile - jd.tstride[i]);
+          f = as_global(jd.flags) + (tile - jd.tstride[i]);
         }
       }
     }
@@ -834,7 +835,7 @@ __device__ void process_tile(const JobDev &jd, int alpha, int gap, int tile, int
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   __syncthreads();
   if (wave == 0)
-    __hip_atomic_store(jd.flags + tile, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(as_global(jd.flags) + tile, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   MSA_TRACE_POINT(jd, tile, 6);
   // The score and the direction block are stored after the flag: only the
   // traceback, a later kernel, reads them, and the completion wait before the
@@ -843,12 +844,12 @@ __device__ void process_tile(const JobDev &jd, int alpha, int gap, int tile, int
     int s = 0;
 #pragma unroll
     for (int i = 0; i < K; ++i) s += ext[i] * C::sstride(i);
-    *jd.score_out = (int64_t)(sm.S[s] >> K);
+    *as_global(jd.score_out) = (int64_t)(sm.S[s] >> K);
   }
 
   // ---- direction block: cell (line, t) at byte line * T + t ----
   {
-    uint8_t *blk = jd.dir + (int64_t)tile * C::DBS;
+    uint8_t *blk = as_global(jd.dir) + (int64_t)tile * C::DBS;
     if constexpr (C::REGDIR) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {

@@ -712,8 +712,8 @@ void batch_sweep4_kernel(const BatchArgs *__restrict__ a, Ctrl *ctrl) {
   __shared__ S4Smem sm;
   const int total = __builtin_amdgcn_readfirstlane(a->s4total);
   const int tag = __builtin_amdgcn_readfirstlane(a->s4tag);
-  const int32_t *const q = a->s4q;
-  const Sweep4Dev *const jobs = a->s4jobs;
+  const int32_t *const q = as_global(a->s4q);
+  const Sweep4Dev *const jobs = as_global(a->s4jobs);
   const int64_t wl =
       __hip_atomic_load(&ctrl->wait_limit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const int64_t wlim = wl > 0 ? wl : kS4WaitTicks;
@@ -739,6 +739,14 @@ void batch_sweep4_kernel(const BatchArgs *__restrict__ a, Ctrl *ctrl) {
         w[i] = __builtin_amdgcn_readfirstlane(src[i]);
       __builtin_memcpy(&sd, w, sizeof(sd));
     }
+    sd.seqs = as_global(sd.seqs);
+    sd.sub = as_global(sd.sub);
+    sd.x0 = as_global(sd.x0);
+    sd.x1 = as_global(sd.x1);
+    sd.x2 = as_global(sd.x2);
+    sd.dir = as_global(sd.dir);
+    sd.score_out = as_global(sd.score_out);
+    sd.status = as_global(sd.status);
     s4_block(sd, sm, blk, sd.alpha, sd.gap, tag, sd.status, ctrl, wlim);
   }
 }

@@ -59,12 +59,16 @@ struct TrCfg {
   static constexpr int dstride(int i) { return ipow(T, K - 1 - i); }
 };
 
-// The thread index, opaque: what follows from it is formed where it is used
-// instead of being kept in registers across a batched launch's jobs.
-__device__ __forceinline__ int tr_tid() {
-  int tid = threadIdx.x;
-  asm volatile("" : "+v"(tid));
-  return tid;
+// The lane, and the thread index from the wave's (a scalar) and it, opaque: what
+// follows from them is formed where it is used instead of being kept in vector
+// registers across a batched launch's jobs, as is the kernel's own index.
+__device__ __forceinline__ int tr_lane() {
+  int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0));
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
+__device__ __forceinline__ int tr_wave() {
+  return __builtin_amdgcn_readfirstlane((int)threadIdx.x) >> 6;
 }
 
 // How a walk ended.
@@ -130,7 +134,7 @@ __device__ __forceinline__ int tr_walk(const JobDev &jd, const TrRec &rc, uint8_
   constexpr int M = C::M;
   constexpr int NQ = C::DBS / 16;      // 16-byte chunks per direction block
   constexpr int CPL = (NQ + 63) / 64;  // chunks per lane
-  const int lane = tr_tid() & 63;
+  const int lane = tr_lane();
   u32x4 *const lds4 = reinterpret_cast<u32x4 *>(dirb);
   uint8_t *const own = rc.own + fam * rc.n;
   int c[K], q[K];
@@ -346,10 +350,9 @@ __device__ __forceinline__ int tr_families(const int (&end)[K], int &H) {
 // h (0: none), for every sum above hend.
 template <int K, bool egf, bool coopt>
 __device__ __forceinline__ void tr_walk_all(const JobDev &jd, TrSmem<K> &sm, const int (&end)[K], const TrRec &rc,
-                            int F) {
-  const int tid = tr_tid();
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid) >> 6;
+                            int F, int wave) {
+  const int lane = tr_lane();
+  const int tid = wave * 64 + lane;
   const int H = rc.n - 1;
   int most = 0;
 #pragma unroll
@@ -450,10 +453,10 @@ __device__ __forceinline__ void tr_walk_all(const JobDev &jd, TrSmem<K> &sm, con
 // Rows of the alignment: unaligned prefixes (end gaps free; sequence 0 first),
 // the path's columns in ascending order of h, unaligned suffixes.
 template <int K>
-__device__ __forceinline__ void tr_rows(const JobDev &jd, TrSmem<K> &sm, const int (&end)[K], const TrRec &rc) {
-  const int tid = tr_tid();
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid) >> 6;
+__device__ __forceinline__ void tr_rows(const JobDev &jd, TrSmem<K> &sm, const int (&end)[K],
+                                        const TrRec &rc, int wave) {
+  const int lane = tr_lane();
+  const int tid = wave * 64 + lane;
   int H = 0, pre = 0;
 #pragma unroll
   for (int i = 0; i < K; ++i) {
@@ -522,7 +525,8 @@ __device__ __forceinline__ void tr_rows(const JobDev &jd, TrSmem<K> &sm, const i
 }
 
 template <int K, bool egf, bool coopt>
-__device__ __forceinline__ void tr_job(const JobDev &jd, TrSmem<K> &sm, int status, int64_t best) {
+__device__ __forceinline__ void tr_job(const JobDev &jd, TrSmem<K> &sm, int status, int64_t best,
+                                       int wave) {
   int end[K];
   if constexpr (egf) {  // the end cell from its row-major index
     int64_t lin = (int64_t)(uint32_t)best;
@@ -539,11 +543,11 @@ __device__ __forceinline__ void tr_job(const JobDev &jd, TrSmem<K> &sm, int stat
     int H = 0;
     const int F = tr_families<K>(end, H);
     const TrRec rc(sm, F, H);
-    tr_walk_all<K, egf, coopt>(jd, sm, end, rc, F);
+    tr_walk_all<K, egf, coopt>(jd, sm, end, rc, F, wave);
     status = sm.status;
-    if (status == ST_OK) tr_rows<K>(jd, sm, end, rc);
+    if (status == ST_OK) tr_rows<K>(jd, sm, end, rc, wave);
   }
-  if (threadIdx.x == 0) {
+  if (wave * 64 + tr_lane() == 0) {
     *jd.status_out = status;
     if (status != ST_OK) {
       *jd.aln_len_out = 0;
@@ -559,16 +563,18 @@ __device__ __forceinline__ void tr_job(const JobDev &jd, TrSmem<K> &sm, int stat
 template <int K>
 __global__ __launch_bounds__(kTrThreads) void trace_kernel(JobDev jd, Ctrl *ctrl) {
   __shared__ TrSmem<K> sm;
+  const int wave = tr_wave();
   const int mode = __builtin_amdgcn_readfirstlane(ctrl->flags);
   const int st = __builtin_amdgcn_readfirstlane(
       __hip_atomic_load(&ctrl->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
   if (mode & kEndGapsFree) {
     tr_job<K, true, false>(
-        jd, sm, st, __hip_atomic_load(&ctrl->best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        jd, sm, st, __hip_atomic_load(&ctrl->best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+        wave);
   } else if (mode & kCoOptimal) {
-    if constexpr (K <= kCoMaxK) tr_job<K, false, true>(jd, sm, st, 0);
+    if constexpr (K <= kCoMaxK) tr_job<K, false, true>(jd, sm, st, 0, wave);
   } else {
-    tr_job<K, false, false>(jd, sm, st, 0);
+    tr_job<K, false, false>(jd, sm, st, 0, wave);
   }
   __syncthreads();
   if (threadIdx.x == 0) finish_launch(ctrl);
@@ -580,7 +586,7 @@ __device__ __forceinline__ int64_t tr_uni(int64_t x) {
 }
 template <class T>
 __device__ __forceinline__ T *tr_uni(T *p) {
-  return reinterpret_cast<T *>(tr_uni(reinterpret_cast<int64_t>(p)));
+  return as_global(reinterpret_cast<T *>(tr_uni(reinterpret_cast<int64_t>(p))));
 }
 
 // What the walk reads of a job's descriptor, in scalar registers.
@@ -611,6 +617,7 @@ __global__ __launch_bounds__(kTrThreads) void batch_trace_kernel(const BatchArgs
   constexpr size_t kBytes =
       sizeof(TrSmem<KHI>) > sizeof(TrSmem<KLO>) ? sizeof(TrSmem<KHI>) : sizeof(TrSmem<KLO>);
   __shared__ alignas(16) char mem[kBytes];
+  const int wave = tr_wave();
   const int njobs = __builtin_amdgcn_readfirstlane(a->njobs);
   const int gst = __builtin_amdgcn_readfirstlane(
       __hip_atomic_load(&ctrl->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
@@ -624,19 +631,19 @@ __global__ __launch_bounds__(kTrThreads) void batch_trace_kernel(const BatchArgs
     switch (__builtin_amdgcn_readfirstlane(jobs[j].k)) {
       case 2:
         if constexpr (KLO <= 2 && 2 <= KHI)
-          tr_job<2, false, false>(jd, *reinterpret_cast<TrSmem<2> *>(mem), st, 0);
+          tr_job<2, false, false>(jd, *reinterpret_cast<TrSmem<2> *>(mem), st, 0, wave);
         break;
       case 3:
         if constexpr (KLO <= 3 && 3 <= KHI)
-          tr_job<3, false, false>(jd, *reinterpret_cast<TrSmem<3> *>(mem), st, 0);
+          tr_job<3, false, false>(jd, *reinterpret_cast<TrSmem<3> *>(mem), st, 0, wave);
         break;
       case 4:
         if constexpr (KLO <= 4 && 4 <= KHI)
-          tr_job<4, false, false>(jd, *reinterpret_cast<TrSmem<4> *>(mem), st, 0);
+          tr_job<4, false, false>(jd, *reinterpret_cast<TrSmem<4> *>(mem), st, 0, wave);
         break;
       case 5:
         if constexpr (KLO <= 5 && 5 <= KHI)
-          tr_job<5, false, false>(jd, *reinterpret_cast<TrSmem<5> *>(mem), st, 0);
+          tr_job<5, false, false>(jd, *reinterpret_cast<TrSmem<5> *>(mem), st, 0, wave);
         break;
       default: break;
     }
@@ -724,7 +731,7 @@ __global__ __launch_bounds__(kTrThreads) void coopt_trace_kernel(JobDev jd, Ctrl
   const int F = tr_families<K>(end, H);
   const TrRec rc(sm, F, H);
   if (status == ST_OK) {
-    tr_walk_all<K, false, true>(jd, sm, end, rc, F);
+    tr_walk_all<K, false, true>(jd, sm, end, rc, F, wave);
     status = sm.status;
   }
   int np = 0;
