@@ -167,12 +167,14 @@ constexpr int kMaxNap = MSA_MAX_NAP;
 // cache state); a tile's completion flag is stored only after the wave's face
 // stores have completed (see process_tile), so a reader that has seen the
 // flag reads the final face values.
+// (Their addresses are formed from integers, so these are flat accesses.  As global
+// ones: 128^4 pruned 940 -> 924 us, but 90 x 60 x 80 x 70 end-gap-free 718 -> 732, and with
+// the descriptor's other pointers 60 x 50 x 40 pruned 231 -> 236; flat ones stay.)
 __device__ inline int32_t face_load(const int32_t *p) {
-  return __hip_atomic_load(as_global(const_cast<int32_t *>(p)), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
+  return __hip_atomic_load(const_cast<int32_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ inline void face_store(int32_t *p, int32_t v) {
-  __hip_atomic_store(as_global(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Tile coordinates of a (wave-uniform) row-major tile index: the digits in
@@ -199,7 +201,7 @@ __device__ void load_tables(const JobDev &jd, int alpha, Smem<K> &sm) {
   const int tid = threadIdx.x;
   if (alpha <= kSubLds)
     for (int e = tid; e < alpha * alpha; e += NT)
-      sm.SUB[(e / alpha) * kSubLds + e % alpha] = (int16_t)(((int32_t)as_global(jd.sub)[e]) * (1 << K));
+      sm.SUB[(e / alpha) * kSubLds + e % alpha] = (int16_t)(((int32_t)jd.sub[e]) * (1 << K));
   if constexpr (K >= 4)
     for (int p = tid; p < Cfg<K>::L; p += NT) sm.LORD[p] = kLineOrder<K>.v[p];
 }
@@ -269,7 +271,7 @@ struct HaloSlots {
 // once (a load in every wait would also wait for the tile's stores: one
 // counter tracks both).
 template <int K, int NT>
-__device__ __forceinline__ void process_tile(const JobDev &jd, int alpha, int gap, int tile, int epoch,
+__device__ void process_tile(const JobDev &jd, int alpha, int gap, int tile, int epoch,
                              Ctrl *ctrl, int32_t *jstatus, Smem<K> &sm,
                              const HaloSlots<K, NT> &hs, bool egf = false,
                              int64_t *best_key = nullptr, bool coopt = false,
@@ -316,7 +318,7 @@ __device__ __forceinline__ void process_tile(const JobDev &jd, int alpha, int ga
       const int v = lo[i] + q;
       const bool use = tid < T && q < ext[i] && v >= 1;
       const int pos = use ? jd.seq_off[i] + v - 1 : 0;
-      r[i] = any_seq ? (int)as_global(jd.seqs)[pos] : 0;
+      r[i] = any_seq ? (int)jd.seqs[pos] : 0;
       r[i] = use ? r[i] : 0;
     }
     bool bad = false;
@@ -395,7 +397,7 @@ __device__ __forceinline__ void process_tile(const JobDev &jd, int alpha, int ga
   // running wavefront would otherwise flood the memory system with
   // device-coherent loads and slow every tile's halo and face traffic.
   if (wave == 0) {
-    const int32_t *f = as_global(jd.flags);
+    const int32_t *f = jd.flags;
     bool need = false;
     if (K <= kPruneMaxK && prune) {
       need = ((kbits >> (tid & 63)) & 1) != 0;
@@ -403,13 +405,13 @@ __device__ __forceinline__ void process_tile(const JobDev &jd, int alpha, int ga
 #pragma unroll
       for (int i = 0; i < K; ++i)
         if ((tid >> i) & 1) tn -= jd.tstride[i];
-      f = as_global(jd.flags) + (need ? tn : tile);
+      f = jd.flags + (need ? tn : tile);
     } else {
 #pragma unroll
       for (int i = 0; i < K; ++i) {
         if (tid == i && c[i] > 0 && !(own0 && i == 0)) {
           need = true;
-          f = as_global(jd.flags) + (tile - jd.tstride[i]);
+          f = jd.flags + (tile - jd.tstride[i]);
         }
       }
     }
@@ -835,7 +837,7 @@ __device__ __forceinline__ void process_tile(const JobDev &jd, int alpha, int ga
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   __syncthreads();
   if (wave == 0)
-    __hip_atomic_store(as_global(jd.flags) + tile, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(jd.flags + tile, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   MSA_TRACE_POINT(jd, tile, 6);
   // The score and the direction block are stored after the flag: only the
   // traceback, a later kernel, reads them, and the completion wait before the
@@ -844,12 +846,12 @@ __device__ __forceinline__ void process_tile(const JobDev &jd, int alpha, int ga
     int s = 0;
 #pragma unroll
     for (int i = 0; i < K; ++i) s += ext[i] * C::sstride(i);
-    *as_global(jd.score_out) = (int64_t)(sm.S[s] >> K);
+    *jd.score_out = (int64_t)(sm.S[s] >> K);
   }
 
   // ---- direction block: cell (line, t) at byte line * T + t ----
   {
-    uint8_t *blk = as_global(jd.dir) + (int64_t)tile * C::DBS;
+    uint8_t *blk = jd.dir + (int64_t)tile * C::DBS;
     if constexpr (C::REGDIR) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -1717,14 +1719,16 @@ int launch_fill(const JobDev &jd, Ctrl *ctrl, const int32_t *order, int grid, in
 
 int launch_traceback(const JobDev &jd, Ctrl *ctrl, hipStream_t s) {
   // The walkers start later than a single wave and share its compute unit, so
-  // they lose where the walk is short (single wave and walkers, related and
-  // unrelated sequences: 24^3 8.1 and 9.8, 9.0 and 11.1 us; 40^3 11.0 and 13.0, 12.8
-  // and 14.9; 64^3 17.9 and 16.8, 19.5 and 18.8; 24^4 12.4 and 12.2, 12.6 and 13.3;
-  // 40^4 19.1 and 14.9, 20.5 and 21.9), but for k = 5, whose single walk changes its
-  // tile every few columns (12^5 11.8 and 9.0, 23 and 12).
+  // they lose where the walk is short (single wave and walkers, related sequences,
+  // unrelated ones, lengths of one alignment 1 : 0.45: 40^3 11.0 and 13.0, 12.8 and
+  // 14.9, 10.6 and 13.2 us; 64^3 17.9 and 16.8, 19.5 and 18.8, 15.8 and 17.7; 96^3
+  // 23.7 and 14.2, 28.1 and 26.9, 22.4 and 22.0; 40^4 19.1 and 14.9, 20.5 and 21.9, 16.3
+  // and 18.5; 64^4 30.3 and 24.6, 31.0 and 33.6, 25.6 and 25.4; 96^4 43.1 and 23.5, 47.0
+  // and 54.0, 37.5 and 30.0), but for k = 5, whose single walk changes its tile every
+  // few columns (12^5 11.8 and 9.0, 23 and 12).
   int longest = 0;
   for (int i = 0; i < jd.k; ++i) longest = jd.n[i] > longest ? jd.n[i] : longest;
-  const bool brief = jd.k <= 3 ? longest < 64 : jd.k == 4 && longest < 32;
+  const bool brief = jd.k <= 4 && longest < 96;
   if (jd.k <= kTrMaxK && jd.total_len <= kTrMaxTotal && !brief) return launch_trace(jd, ctrl, s);
   MSA_DISPATCH_K(jd.k, launch_traceback_k, jd, ctrl, s);
 }

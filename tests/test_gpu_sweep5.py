@@ -92,3 +92,36 @@ def test_sweep5_bad_residue_code():
         say("sweep5 bad code in sequence", d)
         dev.run()
         assert int(dev.d_status.item()) == msa.MSA_EINVAL
+
+
+@pytest.mark.parametrize("alpha", [1, 32, 33])  # 33: past the matrix kept in LDS
+def test_sweep5_alphabets(alpha):
+    rng = np.random.Generator(np.random.PCG64(alpha))
+    m = np.triu(rng.integers(-9, 10, (alpha, alpha)))
+    sub, gap = (m + np.triu(m, 1).T).astype(np.int8), -3
+    lens = [6, 9, 5, 7, 10]
+    dev = msa.DeviceAligner(lens, sub, gap)
+    seqs = draw(alpha, lens, alpha)
+    say("sweep5 alphabet", alpha)
+    dev.set_sequences(seqs)
+    dev.run()
+    s0, r0, d0 = oracle_align(seqs, sub, gap, want_dir=True)
+    s1, r1 = dev.result()
+    assert s1 == s0 and np.array_equal(r1, r0)
+    assert np.array_equal(dev.export_dirs(), d0)
+
+
+def test_sweep5_batched_jobs_match_oracle():
+    """Jobs of uneven lengths in one batch, empty ones and one past the fifth
+    length's bound (which takes the tile fill beside the others) among them."""
+    shapes = [[5, 6, 7, 8, 9], [0, 0, 0, 0, 0], [12, 3, 9, 4, 16], [2, 3, 4, 3, 129],
+              [1, 0, 5, 2, 128], [13, 12, 11, 10, 9], [4, 4, 4, 4, 4]]
+    for rnd in range(3):
+        jobs = []
+        for i, lens in enumerate(shapes):
+            sub, gap = dna_scoring() if i % 2 else protein_scoring()
+            jobs.append((draw(40 * rnd + i, lens, sub.shape[0]), sub, gap))
+        say("sweep5 batch", rnd)
+        for (seqs, sub, gap), (st, s1, r1) in zip(jobs, msa.align_batch(jobs)):
+            s0, r0 = oracle_align(seqs, sub, gap)[:2]
+            assert st == msa.MSA_OK and s1 == s0 and np.array_equal(r1, r0)
