@@ -19,16 +19,16 @@
 //     key.  The lanes with the same edges are consecutive words, so that a layer
 //     is a few runs (by lane order, every layer touched each line of a step:
 //     1.96 GB of fetch for 41^5 cells, 1.32 now).  A fifth wave loads the 369
-//     words of the layers q_i = -1 kS5Pf steps ahead, again while a tag is stale.  A position with the dimensions N at -1 lies in the block
-//     one lower along them, ahead of this one by the sum of that block's extents
-//     along N in steps.
+//     words of the layers q_i = -1 kS5Pf steps ahead, again while a tag is stale.
+//     A position with the dimensions N at -1 lies in the block one lower along
+//     them, ahead of this one by the sum of that block's extents along N in steps.
 //   - Workgroups take blocks in the order of the sum of their coordinates, so a
 //     workgroup only waits for workgroups that are already running.
 //
 // What bounds it: a step's latency and issue together.  A step takes 0.5 us for a
 // workgroup alone on its compute unit and 0.7 for four of them, of which its 90
 // vector instructions a compute wave take 0.6 at most.  Measured: 40^5 2.50 ms with
-// the tile kernel, 0.90 now; 28^5 0.66 and 0.32.  On the way there: halo words
+// the tile kernel, 0.92 now; 28^5 0.66 and 0.32.  On the way there: halo words
 // loaded by the compute waves 1.47 ms (every step waited for memory); one
 // workgroup a block 1.47; waiting several steps ahead after a stall, 1.78 against
 // 1.70; prefetch 4 steps ahead, 3.1; 3 workgroups a compute unit (128 registers),
