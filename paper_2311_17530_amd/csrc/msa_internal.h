@@ -111,11 +111,12 @@ struct Ctrl {
                       // (batched launches report it)
   int64_t wait_limit;  // batched launches: dependency-wait time-out in 100 MHz
                        // ticks (0: 2 s)
-  int32_t sweeps;   // streaming k = 4 fills finished on this workspace: their
-                    // exchange values carry the tag sweeps % 15 + 1
-  int32_t s4head;   // next slot of a batched launch's k = 4 block queue
-  int32_t swept;    // 1 once the current fill is a streaming k = 4 one; the
-                    // kernel that ends the alignment then counts it
+  int32_t sweeps;   // streaming fills finished on this workspace: their
+                    // exchange values carry the tag sweeps % 7 + 1 (k = 3) or
+                    // sweeps % 15 + 1 (k = 4, 5)
+  int32_t s4head;   // next slot of a batched launch's queue of streaming blocks
+  int32_t swept;    // 1 once the current fill is a streaming one; the kernel
+                    // that ends the alignment then counts it
   int32_t pad[23];
 };
 static_assert(sizeof(Ctrl) == 256, "control block is one 256-byte slot");
@@ -158,7 +159,7 @@ __device__ __forceinline__ void finish_launch(Ctrl *ctrl) {
   ctrl->status = 0;
   ctrl->best = INT64_MIN;
   ctrl->epoch = ctrl->epoch + 1;
-  // a streaming k = 4 fill's tag is not used again until every other one was
+  // a streaming fill's tag is not used again until every other one was
   ctrl->sweeps = ctrl->sweeps + ctrl->swept;
   ctrl->swept = 0;
 }

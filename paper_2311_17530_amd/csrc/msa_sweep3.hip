@@ -25,8 +25,8 @@
 //     to the left), so every lane reads its neighbours at fixed offsets; the
 //     other rows' lane -1 values have an array of their own (h0).
 //   - Exchange between workgroups: the outputs of the last row go to region
-//     X0 and those of lane 63 of every row to region X1, each value tagged
-//     with the launch's epoch in its low 3 bits (keys keep those bits clear);
+//     X0 and those of lane 63 of every row to region X1, each value with
+//     the launch's tag (1..7) in its low 3 bits (keys keep those bits clear);
 //     the compute waves store them as they compute them.  A loader wave
 //     (wave kSwNW) does every global load of the exchange: it loads the
 //     neighbours' values kSwPf steps ahead, checks their tags (reloading
@@ -583,8 +583,9 @@ __global__ __launch_bounds__(kSwThreads) void sweep3_kernel(Sweep3Dev sd, Ctrl *
   const int j = tid & 63;
   const int alpha = ctrl->alpha;
   const int gap = ctrl->gap;
-  const int epoch = __hip_atomic_load(&ctrl->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const int tag = (epoch - 1) % 7 + 1;
+  // (not from the epoch, which launches that leave the exchange regions as
+  // they are advance too: tile fills, repeated tracebacks)
+  const int tag = ctrl->sweeps % 7 + 1;
 
   // ---- ticket: workgroups in order of their block diagonal B0 + B1 ----
   if (tid == 0) sm.ticket = atomicAdd(&ctrl->head, 1);
@@ -608,6 +609,7 @@ __global__ __launch_bounds__(kSwThreads) void sweep3_kernel(Sweep3Dev sd, Ctrl *
   // A ticket past the grid means the counter was not reset since the last
   // fill (a fill must be followed by its traceback): nothing to do.
   if (ticket >= sd.nb0 * sd.nb1) return;
+  if (ticket == 0 && tid == 0) ctrl->swept = 1;
   int T = ticket;
   int B0 = 0, B1 = 0;
   for (int a = 0; a <= sd.nb0 + sd.nb1 - 2; ++a) {  // diagonals B0 + B1 = a

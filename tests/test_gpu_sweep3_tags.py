@@ -1,0 +1,93 @@
+"""The streaming three-sequence fill accepts a neighbour's exchange word by the
+launch's tag in it, so no word of an earlier fill may carry the tag of the
+current one.  Calls that end a launch on the workspace without rewriting the
+exchange regions (tile fills, repeated tracebacks) come between streaming
+fills here, as many as there are tags.  Every mode; results equal the oracle's.
+"""
+import sys
+
+import numpy as np
+import pytest
+
+import paper_2311_17530_amd as msa
+from msa_inputs import protein_scoring
+from oracle import oracle_align, oracle_align_egf, oracle_coopt, oracle_nearopt
+
+pytestmark = pytest.mark.gpu
+
+LENS = [60, 130, 40]  # 3 x 3 blocks
+PATHS, DELTA = 6, 9
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    msa.lib()
+    msa.tune_clear()
+    yield
+    msa.tune_clear()
+
+
+def draw(seed):
+    rng = np.random.Generator(np.random.PCG64(seed))
+    return [rng.integers(0, 20, size=n).astype(np.uint8) for n in LENS]
+
+
+def run_and_check(dev, mode, seqs, sub, gap):
+    dev.set_sequences(seqs)
+    if mode == "coopt":
+        dev.run_coopt(PATHS)
+        s1, got = dev.result_coopt()
+        s0, want = oracle_coopt(seqs, sub, gap, PATHS)[:2]
+        assert s1 == s0 and len(got) == len(want)
+        assert all(np.array_equal(a, b) for a, b in zip(got, want))
+    elif mode == "nearopt":
+        dev.run_nearopt(DELTA, PATHS)
+        s1, got = dev.result_nearopt()
+        s0, want = oracle_nearopt(seqs, sub, gap, DELTA, PATHS)
+        assert s1 == s0 and len(got) == len(want)
+        assert all(a[0] == b[0] and np.array_equal(a[1], b[1]) for a, b in zip(got, want))
+    else:
+        oracle = oracle_align_egf if mode == "egf" else oracle_align
+        dev.run()
+        s1, r1 = dev.result()
+        s0, r0 = oracle(seqs, sub, gap)[:2]
+        assert s1 == s0 and np.array_equal(r1, r0)
+
+
+@pytest.mark.parametrize("mode", ["plain", "egf", "coopt", "nearopt"])
+@pytest.mark.parametrize("between", [0, 5, 6, 7])
+def test_tile_fills_between_streaming_fills(mode, between):
+    sub, gap = protein_scoring()
+    dev = msa.DeviceAligner(LENS, sub, gap, end_gaps_free=mode == "egf",
+                            cooptimal=mode == "coopt", nearopt=mode == "nearopt")
+    seed = 3000
+    try:
+        for rnd in range(3 if between else 18):
+            msa.tune_set(msa.MSA_TUNE_PLAIN, 3, max(LENS), 0, 0)
+            say("streaming fill", mode, between, rnd)
+            run_and_check(dev, mode, draw(seed), sub, gap)
+            seed += 1
+            msa.tune_set(msa.MSA_TUNE_PLAIN, 3, max(LENS), 2, 0)
+            for _ in range(between):
+                run_and_check(dev, mode, draw(seed), sub, gap)
+                seed += 1
+    finally:
+        msa.tune_clear()
+
+
+def test_repeated_tracebacks_between_streaming_fills():
+    sub, gap = protein_scoring()
+    dev = msa.DeviceAligner(LENS, sub, gap)
+    for rnd in range(4):
+        say("streaming fill, then six tracebacks more", rnd)
+        run_and_check(dev, "plain", draw(4000 + rnd), sub, gap)
+        for _ in range(6):
+            dev.run_traceback()
