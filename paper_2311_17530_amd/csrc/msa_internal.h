@@ -111,9 +111,8 @@ struct Ctrl {
                       // (batched launches report it)
   int64_t wait_limit;  // batched launches: dependency-wait time-out in 100 MHz
                        // ticks (0: 2 s)
-  int32_t sweeps;   // streaming fills finished on this workspace: their
-                    // exchange values carry the tag sweeps % 7 + 1 (k = 3) or
-                    // sweeps % 15 + 1 (k = 4, 5)
+  int32_t sweeps;   // streaming fills finished on this workspace (see
+                    // next_sweep): their exchange values carry its tag
   int32_t s4head;   // next slot of a batched launch's queue of streaming blocks
   int32_t swept;    // 1 once the current fill is a streaming one; the kernel
                     // that ends the alignment then counts it
@@ -152,6 +151,20 @@ struct WaitClock {
   }
 };
 
+// Count of streaming fills.  A fill's exchange values carry sweep_tag(count,
+// tags) in the key's low bits: 3 of them (7 tags, 0 is none) for k = 3, 4 for k
+// = 4 and 5.  The count starts again after a multiple of both numbers of tags,
+// so that the tags go round without a break and it never overflows (a negative
+// tag would set the key's other bits).
+constexpr int kSweepTags3 = 7, kSweepTags = 15, kSweepCycle = 105;
+static_assert(kSweepCycle % kSweepTags3 == 0 && kSweepCycle % kSweepTags == 0, "whole cycles");
+__host__ __device__ inline int32_t next_sweep(int32_t sweeps, int32_t more) {
+  return (int32_t)(((uint32_t)sweeps + (uint32_t)more) % kSweepCycle);
+}
+__host__ __device__ inline int sweep_tag(int32_t sweeps, int tags) {
+  return (int)((uint32_t)sweeps % (uint32_t)tags) + 1;
+}
+
 // Readies the control block for the next launch on this workspace (one lane
 // of the kernel that ends an alignment).
 __device__ __forceinline__ void finish_launch(Ctrl *ctrl) {
@@ -160,7 +173,7 @@ __device__ __forceinline__ void finish_launch(Ctrl *ctrl) {
   ctrl->best = INT64_MIN;
   ctrl->epoch = ctrl->epoch + 1;
   // a streaming fill's tag is not used again until every other one was
-  ctrl->sweeps = ctrl->sweeps + ctrl->swept;
+  ctrl->sweeps = next_sweep(ctrl->sweeps, ctrl->swept);
   ctrl->swept = 0;
 }
 

@@ -311,13 +311,13 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
   int rc = ensure_host(in_bytes, out_bytes);
   if (rc) return rc;
   if (x_clean_ < o) x_clean_ = o;
-  const int s4tag = sweeps_ % 15 + 1;
+  const int s4tag = sweep_tag(sweeps_, kSweepTags);
   int64_t xzero = 0;
   if (n4 > 0) {
     if (s4tag == 1) x_clean_ = cap_ / 256 * 256;
     xzero = std::max<int64_t>(0, x_clean_ - xlo);
     x_clean_ = std::min(x_clean_, xlo);
-    ++sweeps_;
+    sweeps_ = next_sweep(sweeps_, 1);
   }
 
   // ---- host image of the input region ----

@@ -115,9 +115,9 @@ class Launch {
   bool busy_ = false;
   int launch_status_ = MSA_OK;
   int64_t wait_limit_ = 0;
-  // streaming k = 4 jobs: launches with such jobs so far (their tags), and the
-  // arena offset from which everything is zero or a word of one of the last
-  // launches with a tag
+  // streaming jobs (k = 4, 5): the count of launches with such jobs
+  // (next_sweep; their tags), and the arena offset from which everything is
+  // zero or a word of one of the last launches with a tag
   int32_t sweeps_ = 0;
   int64_t x_clean_ = 0;
   // The launch sequence of each k class, captured once on this arena (its

@@ -585,7 +585,7 @@ __global__ __launch_bounds__(kSwThreads) void sweep3_kernel(Sweep3Dev sd, Ctrl *
   const int gap = ctrl->gap;
   // (not from the epoch, which launches that leave the exchange regions as
   // they are advance too: tile fills, repeated tracebacks)
-  const int tag = ctrl->sweeps % 7 + 1;
+  const int tag = sweep_tag(ctrl->sweeps, kSweepTags3);
 
   // ---- ticket: workgroups in order of their block diagonal B0 + B1 ----
   if (tid == 0) sm.ticket = atomicAdd(&ctrl->head, 1);

@@ -662,7 +662,7 @@ void sweep4_kernel(Sweep4Dev sd, Ctrl *ctrl) {
   if (threadIdx.x == 0) sm.item = atomicAdd(&ctrl->head, 1);
   const int alpha = ctrl->alpha;
   const int gap = ctrl->gap;
-  const int tag = ctrl->sweeps % 15 + 1;
+  const int tag = sweep_tag(ctrl->sweeps, kSweepTags);
   s4_barrier();
   const int ticket = __builtin_amdgcn_readfirstlane(sm.item);
   // a ticket past the grid: the counter was not reset since the last fill

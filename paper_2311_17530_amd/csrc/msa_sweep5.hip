@@ -546,7 +546,7 @@ void sweep5_kernel(Sweep5Dev sd, Ctrl *ctrl) {
   __shared__ S5Smem sm;
   const int alpha = ctrl->alpha;
   const int gap = ctrl->gap;
-  const int tag = ctrl->sweeps % 15 + 1;
+  const int tag = sweep_tag(ctrl->sweeps, kSweepTags);
   const int total = sd.nb[0] * sd.nb[1] * sd.nb[2] * sd.nb[3];
   const bool more = total > (int)gridDim.x;
   auto next = [&](int ticket) {

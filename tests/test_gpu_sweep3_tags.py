@@ -91,3 +91,37 @@ def test_repeated_tracebacks_between_streaming_fills():
         run_and_check(dev, "plain", draw(4000 + rnd), sub, gap)
         for _ in range(6):
             dev.run_traceback()
+
+
+@pytest.mark.parametrize("lens", [[30, 70, 20], [9, 20, 18, 11], [6, 5, 9, 7, 8]],
+                         ids=lambda s: "k%d" % len(s))
+def test_count_of_streaming_fills_stays_small(lens):
+    """The count behind the tags is word 38 of the control block, which a
+    workspace starts with.  It starts again after 105 fills and, set to the
+    largest integer, goes on with valid tags."""
+    import torch
+    sub, gap = protein_scoring()
+    dev = msa.DeviceAligner(lens, sub, gap)
+    off = dev.ws_ptr - dev.ws.data_ptr() + 4 * 38
+    count = dev.ws[off: off + 4].view(torch.int32)
+
+    def one(seed):
+        rng = np.random.Generator(np.random.PCG64(seed))
+        seqs = [rng.integers(0, 20, size=n).astype(np.uint8) for n in lens]
+        dev.set_sequences(seqs)
+        dev.run()
+        s1, r1 = dev.result()
+        s0, r0 = oracle_align(seqs, sub, gap)[:2]
+        assert s1 == s0 and np.array_equal(r1, r0), seed
+
+    say("count of streaming fills", lens)
+    for n in range(110):
+        assert int(count.item()) == n % 105
+        if n % 10 == 0 or n > 100:
+            one(5000 + n)
+        else:
+            dev.run()
+    count.fill_(2 ** 31 - 1)
+    for n in range(4):
+        one(6000 + n)
+        assert 0 <= int(count.item()) < 105
