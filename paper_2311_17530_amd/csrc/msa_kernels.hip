@@ -1763,31 +1763,41 @@ constexpr int kBatchAuxGrid = 1024;
 constexpr int kBatchTraceGrid = 4096;
 constexpr int kBatchLongGrid = 256;  // where only jobs beyond the walkers' bounds are left
 
+// Only the kernels that the launch's jobs need (`parts`): one that finds nothing to
+// do still takes 3 to 8 us, which a launch of few jobs feels (one k = 3 job of 16..48
+// residues through the server: 160 us with five kernels, 262 with eight; four
+// jobs in a batch: 209 and 222).
 template <int KLO, int KHI>
-static int launch_batch_k(const BatchArgs *d_args, const JobDev *d_jobs, Ctrl *ctrl, int grid,
-                          hipStream_t s) {
+static int launch_batch_k(int parts, const BatchArgs *d_args, const JobDev *d_jobs, Ctrl *ctrl,
+                          int grid, hipStream_t s) {
   launch_begin();
   hipLaunchKernelGGL(batch_zero_kernel, dim3(kBatchAuxGrid), dim3(256), 0, s, d_args);
-  hipLaunchKernelGGL(batch_queue_kernel, dim3(kBatchAuxGrid), dim3(256), 0, s, d_args, d_jobs);
-  hipLaunchKernelGGL((batch_fill_kernel<KLO, KHI, kBatchThreads>), dim3(grid),
-                     dim3(kBatchThreads), 0, s, d_args, d_jobs, ctrl);
-  if (KLO <= 4 && 4 <= KHI) launch_batch_sweep4(d_args, ctrl, s);
-  if (KLO <= 5 && 5 <= KHI) launch_batch_sweep5(d_args, ctrl, s);
-  if (KHI <= kTrMaxK) launch_batch_trace(KHI <= 4 ? 0 : 1, d_args, d_jobs, ctrl, s);
-  hipLaunchKernelGGL((batch_traceback_kernel<KLO, KHI>),
-                     dim3(KHI <= kTrMaxK ? kBatchLongGrid : kBatchTraceGrid), dim3(64), 0, s,
-                     d_args, d_jobs, ctrl);
+  if (parts & kBatchTiles) {
+    hipLaunchKernelGGL(batch_queue_kernel, dim3(kBatchAuxGrid), dim3(256), 0, s, d_args, d_jobs);
+    hipLaunchKernelGGL((batch_fill_kernel<KLO, KHI, kBatchThreads>), dim3(grid),
+                       dim3(kBatchThreads), 0, s, d_args, d_jobs, ctrl);
+  }
+  if (parts & kBatchStreams) {
+    if (KLO <= 4 && 4 <= KHI) launch_batch_sweep4(d_args, ctrl, s);
+    if (KLO <= 5 && 5 <= KHI) launch_batch_sweep5(d_args, ctrl, s);
+  }
+  if (KHI <= kTrMaxK && (parts & kBatchWalkers))
+    launch_batch_trace(KHI <= 4 ? 0 : 1, d_args, d_jobs, ctrl, s);
+  if (KHI > kTrMaxK || (parts & kBatchSingle))
+    hipLaunchKernelGGL((batch_traceback_kernel<KLO, KHI>),
+                       dim3(KHI <= kTrMaxK ? kBatchLongGrid : kBatchTraceGrid), dim3(64), 0, s,
+                       d_args, d_jobs, ctrl);
   hipLaunchKernelGGL(batch_finish_kernel, dim3(1), dim3(64), 0, s, d_args, ctrl);
   return launch_end();
 }
 
-int launch_batch(int kclass, const BatchArgs *d_args, const JobDev *d_jobs, Ctrl *ctrl, int grid,
-                 hipStream_t s) {
+int launch_batch(int kclass, int parts, const BatchArgs *d_args, const JobDev *d_jobs, Ctrl *ctrl,
+                 int grid, hipStream_t s) {
   switch (kclass) {
-    case 0: return launch_batch_k<2, 4>(d_args, d_jobs, ctrl, grid, s);
-    case 1: return launch_batch_k<5, 5>(d_args, d_jobs, ctrl, grid, s);
-    case 2: return launch_batch_k<6, 6>(d_args, d_jobs, ctrl, grid, s);
-    default: return launch_batch_k<7, 8>(d_args, d_jobs, ctrl, grid, s);
+    case 0: return launch_batch_k<2, 4>(parts, d_args, d_jobs, ctrl, grid, s);
+    case 1: return launch_batch_k<5, 5>(parts, d_args, d_jobs, ctrl, grid, s);
+    case 2: return launch_batch_k<6, 6>(parts, d_args, d_jobs, ctrl, grid, s);
+    default: return launch_batch_k<7, 8>(parts, d_args, d_jobs, ctrl, grid, s);
   }
 }
 

@@ -138,12 +138,9 @@ int Launch::init(int64_t bytes, hipStream_t shared) {
     cap_ = bytes;
     x_clean_ = cap_;  // nothing known of the new arena
   }
-  // Pinned staging and the four k classes' launch graphs are made here, once
-  // per arena, so that launches under load (a server's slots) allocate and
-  // instantiate nothing while other slots' persistent fills run.
+  // Pinned staging is made here, once per arena, so that launches allocate none.
   int rc = ensure_host(1 << 20, 1 << 20);
   if (rc) return rc;
-  for (int kc = 0; kc < 4; ++kc) (void)ensure_graph(kc, batch_grid(kc));
   // The stream's first kernel and its first copies each way make the runtime
   // create the hardware queues behind them; doing it here keeps that out of
   // the time when other slots' persistent fills run (the queue list changes
@@ -154,6 +151,21 @@ int Launch::init(int64_t bytes, hipStream_t shared) {
       hipStreamSynchronize(stream_) != hipSuccess)
     return MSA_EDEVICE;
   return MSA_OK;
+}
+
+// (Walks past the walkers' bounds are rare beyond k class 0: those graphs come
+// when they are needed.)
+void Launch::ensure_graphs() {
+  for (int kc = 0; kc < 4; ++kc) {
+    const int grid = batch_grid(kc);
+    for (int parts = 0; parts < kBatchParts; ++parts) {
+      const bool fills = kc <= 1 ? (parts & (kBatchTiles | kBatchStreams)) != 0
+                                 : (parts & (kBatchTiles | kBatchStreams)) == kBatchTiles;
+      const int walks = parts & (kBatchWalkers | kBatchSingle);
+      if (fills && (kc == 0 ? walks != 0 : walks == (kc == 1 ? kBatchWalkers : kBatchSingle)))
+        (void)ensure_graph(kc, parts, grid);
+    }
+  }
 }
 
 // Persistent workgroups of the batched fill: every one that fits, or the
@@ -167,36 +179,37 @@ int Launch::batch_grid(int kc) const {
 }
 
 void Launch::drop_graphs() {
-  for (int kc = 0; kc < 4; ++kc) {
-    if (graph_[kc]) (void)hipGraphExecDestroy(graph_[kc]);
-    graph_[kc] = nullptr;
-    graph_failed_[kc] = false;
-  }
+  for (auto &row : graph_)
+    for (Graph &gr : row) {
+      if (gr.exec) (void)hipGraphExecDestroy(gr.exec);
+      gr = Graph();
+    }
 }
 
 // Captures the launch sequence of k class kc on this arena.  Returns 0 when
 // a graph is ready; otherwise the caller launches the kernels directly.
-int Launch::ensure_graph(int kc, int grid) {
-  if (graph_[kc] && graph_grid_[kc] != grid) {  // another tuned grid: capture again
-    (void)hipGraphExecDestroy(graph_[kc]);
-    graph_[kc] = nullptr;
+int Launch::ensure_graph(int kc, int parts, int grid) {
+  Graph &gr = graph_[kc][parts];
+  if (gr.exec && gr.grid != grid) {  // another tuned grid: capture again
+    (void)hipGraphExecDestroy(gr.exec);
+    gr.exec = nullptr;
   }
-  if (graph_[kc]) return 0;
-  if (graph_failed_[kc]) return -1;
-  graph_grid_[kc] = grid;
+  if (gr.exec) return 0;
+  if (gr.failed) return -1;
+  gr.grid = grid;
   hipGraph_t g = nullptr;
   bool ok = hipStreamBeginCapture(stream_, hipStreamCaptureModeThreadLocal) == hipSuccess;
   if (ok) {
-    const int rc = launch_batch(kc, reinterpret_cast<const BatchArgs *>(d_ + kArgsOff),
+    const int rc = launch_batch(kc, parts, reinterpret_cast<const BatchArgs *>(d_ + kArgsOff),
                                 reinterpret_cast<const JobDev *>(d_ + kJobsOff),
                                 reinterpret_cast<Ctrl *>(d_), grid, stream_);
     ok = hipStreamEndCapture(stream_, &g) == hipSuccess && rc == 0 && g;
   }
-  ok = ok && hipGraphInstantiate(&graph_[kc], g, nullptr, nullptr, 0) == hipSuccess;
+  ok = ok && hipGraphInstantiate(&gr.exec, g, nullptr, nullptr, 0) == hipSuccess;
   if (g) (void)hipGraphDestroy(g);
   if (!ok) {
-    graph_[kc] = nullptr;
-    graph_failed_[kc] = true;
+    gr.exec = nullptr;
+    gr.failed = true;
     (void)hipGetLastError();  // clear a capture error; the direct launches follow
     return -1;
   }
@@ -528,15 +541,18 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
 
   // ---- enqueue: inputs, the launch sequence (a graph replay), outputs ----
   const int grid = batch_grid(kc);
-  const bool graph = ensure_graph(kc, grid) == 0;
+  int parts = (tiles > 0 ? kBatchTiles : 0) | (n4 > 0 ? kBatchStreams : 0);
+  for (int i = 0; i < nj; ++i)
+    parts |= kc <= 1 && sz[i].p.total_len <= kTrMaxTotal ? kBatchWalkers : kBatchSingle;
+  const bool graph = ensure_graph(kc, parts, grid) == 0;
   bool ok = true;
   for (hipEvent_t e : after) ok = ok && hipStreamWaitEvent(stream_, e, 0) == hipSuccess;
   ok = ok && hipEventRecord(start_, stream_) == hipSuccess;
   ok = ok && hipMemcpyAsync(d_, h, (size_t)in_bytes, hipMemcpyHostToDevice, stream_) == hipSuccess;
   if (graph)
-    ok = ok && hipGraphLaunch(graph_[kc], stream_) == hipSuccess;
+    ok = ok && hipGraphLaunch(graph_[kc][parts].exec, stream_) == hipSuccess;
   else
-    ok = ok && launch_batch(kc, reinterpret_cast<const BatchArgs *>(d_ + off_args),
+    ok = ok && launch_batch(kc, parts, reinterpret_cast<const BatchArgs *>(d_ + off_args),
                             reinterpret_cast<const JobDev *>(d_ + off_jobs),
                             reinterpret_cast<Ctrl *>(d_ + off_ctrl), grid, stream_) == 0;
   ok = ok && hipMemcpyAsync(h_out_, d_ + off_out, (size_t)out_bytes, hipMemcpyDeviceToHost,

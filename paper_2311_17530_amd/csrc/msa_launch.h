@@ -46,6 +46,10 @@ class Launch {
   // one of its own.
   int init(int64_t bytes, hipStream_t shared = nullptr);
   int64_t capacity() const { return cap_; }
+  // Captures the launch sequences now that otherwise the first launch with such
+  // jobs captures: for a server, whose launches instantiate nothing while other
+  // slots' persistent fills run.
+  void ensure_graphs();
 
   // Fixed bytes of a launch besides the jobs (control block, tables, queue).
   static int64_t overhead_bytes(int njobs, int64_t ntiles_total);
@@ -120,15 +124,19 @@ class Launch {
   // zero or a word of one of the last launches with a tag
   int32_t sweeps_ = 0;
   int64_t x_clean_ = 0;
-  // The launch sequence of each k class, captured once on this arena (its
-  // arguments are the arena's fixed batch descriptor and control block) and
-  // replayed for every batch; dropped when the arena is reallocated.
-  hipGraphExec_t graph_[4] = {};
-  int graph_grid_[4] = {};  // the fill grid each graph was captured with
-  bool graph_failed_[4] = {};
+  // The launch sequences of each k class, by the parts a batch needs
+  // (launch_batch), each captured once on this arena (its arguments are the
+  // arena's fixed batch descriptor and control block) and replayed for every
+  // batch; dropped when the arena is reallocated.
+  struct Graph {
+    hipGraphExec_t exec = nullptr;
+    int grid = 0;  // the fill grid it was captured with
+    bool failed = false;
+  };
+  Graph graph_[4][16];  // [k class][parts]
   int ensure_host(int64_t in_bytes, int64_t out_bytes);
   int batch_grid(int kc) const;
-  int ensure_graph(int kc, int grid);
+  int ensure_graph(int kc, int parts, int grid);
   void drop_graphs();
 };
 

@@ -32,11 +32,13 @@ int fill_occupancy(int k);
 int launch_prune_bounds(const PruneDev &pd, Ctrl *ctrl, hipStream_t s);
 int launch_prune_select(const PruneDev &pd, Ctrl *ctrl, int pass, hipStream_t s);
 int launch_prune_check(const PruneDev &pd, Ctrl *ctrl, hipStream_t s);
-// The batched launch sequence (flag clearing, queue, fill, traceback, control
+// The batched launch sequence (flag clearing, queues, fills, tracebacks, control
 // block reset) for the batch described by d_args; grid workgroups for the
-// persistent fill.  Fixed arguments only, so it can be captured in a graph.
-int launch_batch(int kclass, const BatchArgs *d_args, const JobDev *d_jobs, Ctrl *ctrl, int grid,
-                 hipStream_t s);
+// persistent tile fill.  `parts`: which of them the batch's jobs need.  Fixed
+// arguments only, so it can be captured in a graph.
+enum { kBatchTiles = 1, kBatchStreams = 2, kBatchWalkers = 4, kBatchSingle = 8, kBatchParts = 16 };
+int launch_batch(int kclass, int parts, const BatchArgs *d_args, const JobDev *d_jobs, Ctrl *ctrl,
+                 int grid, hipStream_t s);
 int batch_occupancy(int kclass);
 // streaming k = 3 fill (msa_sweep3.hip), for plans with sweep3_eligible
 int launch_sweep3(const Plan &p, char *ws, const JobDev &jd, Ctrl *ctrl, int32_t flags,

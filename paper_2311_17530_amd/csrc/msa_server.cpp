@@ -303,6 +303,7 @@ extern "C" msa_server *msa_server_create(int64_t hbm_budget_bytes, int32_t max_i
   for (auto &sl : s->slots) {
     sl.launch.reset(new Launch());
     if (sl.launch->init(s->slot_bytes) != MSA_OK) return nullptr;
+    sl.launch->ensure_graphs();
   }
   if (hipEventCreate(&s->ref) != hipSuccess || hipEventRecord(s->ref, nullptr) != hipSuccess ||
       hipEventSynchronize(s->ref) != hipSuccess)
