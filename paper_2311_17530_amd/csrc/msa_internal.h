@@ -81,6 +81,7 @@ struct JobDev {
   const int32_t *wcnt;        // (k+1) x nwaves: tuples (c_d..c_{k-1}) summing to s
   const int64_t *wbase;       // nwaves: queue slot of this job's first tile of wave w
   int64_t qbase;              // first tile of this job in the launch's tile numbering
+  int32_t walkers;            // traceback by several walkers (0: by a single wave)
 };
 
 // Control block of one persistent launch (in device memory).

@@ -1608,7 +1608,7 @@ __global__ __launch_bounds__(64) void batch_traceback_kernel(const BatchArgs *__
   const int gst = __hip_atomic_load(&ctrl->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   for (int j = blockIdx.x; j < njobs; j += gridDim.x) {
     const JobDev &jd = jobs[j];
-    if (KHI <= kTrMaxK && jd.total_len <= kTrMaxTotal) continue;  // batch_trace_kernel's
+    if (jd.walkers) continue;  // batch_trace_kernel's
     const int jst = __hip_atomic_load(jd.jstatus, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int st = gst != ST_OK ? gst : jst;
     switch (jd.k) {
@@ -1718,18 +1718,7 @@ int launch_fill(const JobDev &jd, Ctrl *ctrl, const int32_t *order, int grid, in
 }
 
 int launch_traceback(const JobDev &jd, Ctrl *ctrl, hipStream_t s) {
-  // The walkers start later than a single wave and share its compute unit, so
-  // they lose where the walk is short (single wave and walkers, related sequences,
-  // unrelated ones, lengths of one alignment 1 : 0.45: 40^3 11.0 and 13.0, 12.8 and
-  // 14.9, 10.6 and 13.2 us; 64^3 17.9 and 16.8, 19.5 and 18.8, 15.8 and 17.7; 96^3
-  // 23.7 and 14.2, 28.1 and 26.9, 22.4 and 22.0; 40^4 19.1 and 14.9, 20.5 and 21.9, 16.3
-  // and 18.5; 64^4 30.3 and 24.6, 31.0 and 33.6, 25.6 and 25.4; 96^4 43.1 and 23.5, 47.0
-  // and 54.0, 37.5 and 30.0), but for k = 5, whose single walk changes its tile every
-  // few columns (12^5 11.8 and 9.0, 23 and 12).
-  int longest = 0;
-  for (int i = 0; i < jd.k; ++i) longest = jd.n[i] > longest ? jd.n[i] : longest;
-  const bool brief = jd.k <= 4 && longest < 96;
-  if (jd.k <= kTrMaxK && jd.total_len <= kTrMaxTotal && !brief) return launch_trace(jd, ctrl, s);
+  if (trace_by_walkers(jd.n, jd.k, 1, 1)) return launch_trace(jd, ctrl, s);
   MSA_DISPATCH_K(jd.k, launch_traceback_k, jd, ctrl, s);
 }
 
@@ -1761,7 +1750,6 @@ constexpr int kBatchThreads = 256;
 // columns, the traceback over the jobs, one wave per job at a time.
 constexpr int kBatchAuxGrid = 1024;
 constexpr int kBatchTraceGrid = 4096;
-constexpr int kBatchLongGrid = 256;  // where only jobs beyond the walkers' bounds are left
 
 // Only the kernels that the launch's jobs need (`parts`): one that finds nothing to
 // do still takes 3 to 8 us, which a launch of few jobs feels (one k = 3 job of 16..48
@@ -1784,8 +1772,7 @@ static int launch_batch_k(int parts, const BatchArgs *d_args, const JobDev *d_jo
   if (KHI <= kTrMaxK && (parts & kBatchWalkers))
     launch_batch_trace(KHI <= 4 ? 0 : 1, d_args, d_jobs, ctrl, s);
   if (KHI > kTrMaxK || (parts & kBatchSingle))
-    hipLaunchKernelGGL((batch_traceback_kernel<KLO, KHI>),
-                       dim3(KHI <= kTrMaxK ? kBatchLongGrid : kBatchTraceGrid), dim3(64), 0, s,
+    hipLaunchKernelGGL((batch_traceback_kernel<KLO, KHI>), dim3(kBatchTraceGrid), dim3(64), 0, s,
                        d_args, d_jobs, ctrl);
   hipLaunchKernelGGL(batch_finish_kernel, dim3(1), dim3(64), 0, s, d_args, ctrl);
   return launch_end();

@@ -153,8 +153,8 @@ int Launch::init(int64_t bytes, hipStream_t shared) {
   return MSA_OK;
 }
 
-// (Walks past the walkers' bounds are rare beyond k class 0: those graphs come
-// when they are needed.)
+// (Walks past the walkers' bounds, or many k = 5 jobs, are rare: those graphs
+// come when they are needed.)
 void Launch::ensure_graphs() {
   for (int kc = 0; kc < 4; ++kc) {
     const int grid = batch_grid(kc);
@@ -162,7 +162,7 @@ void Launch::ensure_graphs() {
       const bool fills = kc <= 1 ? (parts & (kBatchTiles | kBatchStreams)) != 0
                                  : (parts & (kBatchTiles | kBatchStreams)) == kBatchTiles;
       const int walks = parts & (kBatchWalkers | kBatchSingle);
-      if (fills && (kc == 0 ? walks != 0 : walks == (kc == 1 ? kBatchWalkers : kBatchSingle)))
+      if (fills && ((walks == kBatchWalkers && kc <= 1) || (walks == kBatchSingle && kc != 1)))
         (void)ensure_graph(kc, parts, grid);
     }
   }
@@ -358,6 +358,14 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
   Sweep4Dev *s4_all = reinterpret_cast<Sweep4Dev *>(h + off_s4jobs);
   Sweep5Dev *s5_all = reinterpret_cast<Sweep5Dev *>(h + off_s4jobs);
   int32_t *s4pre = reinterpret_cast<int32_t *>(h + off_s4pre);
+  // Walkers take the walks of all jobs, or of none: where there are few jobs each
+  // has a compute unit, and a short walk is done before the longest (64 jobs of
+  // k = 2 and 100..300 residues 38 us; the shorter half by the single wave's
+  // kernel, after the walkers', 78).
+  const int cus = device_cu_count();
+  bool walkers = false;
+  for (int i = 0; i < nj; ++i)
+    walkers = walkers || trace_by_walkers(jobs[i]->lens, jobs[i]->k, nj, cus);
   std::vector<int32_t *> s4base;        // queue slots per key, of each streaming job
   std::vector<const JobSizes *> s4size;
   int64_t xo = xlo;
@@ -422,6 +430,7 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
     jd.status_out = reinterpret_cast<int32_t *>(d_ + off_stat) + i;
     jd.aln_out = reinterpret_cast<uint8_t *>(d_ + job_out[i]);
     jd.aln_cap = sz[i].cap;
+    jd.walkers = walkers && j.k <= kTrMaxK && p.total_len <= kTrMaxTotal;
     jd.trace = nullptr;
     memcpy(&jd_all[i], &jd, sizeof(JobDev));
     if (s4) {
@@ -542,8 +551,7 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
   // ---- enqueue: inputs, the launch sequence (a graph replay), outputs ----
   const int grid = batch_grid(kc);
   int parts = (tiles > 0 ? kBatchTiles : 0) | (n4 > 0 ? kBatchStreams : 0);
-  for (int i = 0; i < nj; ++i)
-    parts |= kc <= 1 && sz[i].p.total_len <= kTrMaxTotal ? kBatchWalkers : kBatchSingle;
+  for (int i = 0; i < nj; ++i) parts |= jd_all[i].walkers ? kBatchWalkers : kBatchSingle;
   const bool graph = ensure_graph(kc, parts, grid) == 0;
   bool ok = true;
   for (hipEvent_t e : after) ok = ok && hipStreamWaitEvent(stream_, e, 0) == hipSuccess;

@@ -12,9 +12,12 @@ namespace msa {
 int launch_fill(const JobDev &jd, Ctrl *ctrl, const int32_t *order, int grid, int pass,
                 hipStream_t s);
 int launch_traceback(const JobDev &jd, Ctrl *ctrl, hipStream_t s);
+// whether several walkers take the walk of an alignment (lengths n) that is
+// traced back as one of njobs on a device of `cus` compute units
+bool trace_by_walkers(const int32_t *n, int k, int njobs, int cus);
 // the same by several walkers (msa_trace.hip): k <= kTrMaxK, sum n_i <= kTrMaxTotal
 int launch_trace(const JobDev &jd, Ctrl *ctrl, hipStream_t s);
-// the same for a batched launch's jobs of k class 0 or 1 (nothing for others)
+// the same for those of a batched launch's jobs that say so (k class 0 or 1)
 void launch_batch_trace(int kclass, const BatchArgs *d_args, const JobDev *d_jobs, Ctrl *ctrl,
                         hipStream_t s);
 // and the co-optimal list built on it (k <= kCoMaxK)

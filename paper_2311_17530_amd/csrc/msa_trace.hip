@@ -26,8 +26,8 @@
 // the next tile's directions, at every fourth column or so) times the columns
 // of the longest piece.  Measured, single walk and walkers: related sequences
 // 384^3 94 and 25 us, 128^4 69 and 29, 40^5 57 and 16; unrelated ones, whose walks
-// meet late, 384^3 106 and 78, 128^4 68 and 66, 40^5 76 and 32.  Short walks of k <= 4
-// keep the single wave (launch_traceback).
+// meet late, 384^3 106 and 78, 128^4 68 and 66, 40^5 76 and 32.  Short walks, and
+// those of many jobs at once, keep the single wave (trace_by_walkers).
 //
 // Co-optimal alignments (co-optimal mode, k <= 3): the depth-first enumeration
 // takes at every new cell the lowest mask of its tie set, so below a cell of
@@ -608,8 +608,8 @@ __device__ __forceinline__ JobDev tr_desc(const JobDev &jd) {
   return r;
 }
 
-// A batched launch's jobs, one workgroup each at a time; a job beyond the
-// walkers' bounds is left to the single walk's kernel.
+// A batched launch's jobs, one workgroup each at a time; the others are left to
+// the single walk's kernel.
 template <int KLO, int KHI>
 __global__ __launch_bounds__(kTrThreads) void batch_trace_kernel(const BatchArgs *__restrict__ a,
                                                                  const JobDev *__restrict__ jobs,
@@ -622,7 +622,7 @@ __global__ __launch_bounds__(kTrThreads) void batch_trace_kernel(const BatchArgs
   const int gst = __builtin_amdgcn_readfirstlane(
       __hip_atomic_load(&ctrl->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
   for (int j = blockIdx.x; j < njobs; j += gridDim.x) {
-    if (__builtin_amdgcn_readfirstlane((int)(jobs[j].total_len > kTrMaxTotal))) continue;
+    if (!__builtin_amdgcn_readfirstlane(jobs[j].walkers)) continue;
     const JobDev jd = tr_desc(jobs[j]);
     const int jst = __builtin_amdgcn_readfirstlane(
         __hip_atomic_load(jobs[j].jstatus, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
@@ -1316,6 +1316,39 @@ int launch_nearopt(const JobDev &jd, Ctrl *ctrl, int64_t delta, int32_t max_path
     default: return -1;
   }
 #undef MSA_NO_ARGS
+}
+
+// Where the walkers take a walk.  They start later than a single wave, share its
+// compute unit and take all of it, so they lose
+//   - on short walks (single wave and walkers, related sequences, unrelated ones, lengths of
+//     one alignment 1 : 0.45: 40^3 11.0 and 13.0, 12.8 and 14.9, 10.6 and 13.2 us; 64^3
+//     17.9 and 16.8, 19.5 and 18.8, 15.8 and 17.7; 96^3 23.7 and 14.2, 28.1 and 26.9, 22.4
+//     and 22.0; 40^4 19.1 and 14.9, 20.5 and 21.9, 16.3 and 18.5; 64^4 30.3 and 24.6, 31.0
+//     and 33.6, 25.6 and 25.4; 96^4 43.1 and 23.5, 47.0 and 54.0, 37.5 and 30.0; 96^2 15.6
+//     and 9.6, 17.9 and 13.9), but for k = 5, whose single walk changes its tile every few
+//     columns (12^5 11.8 and 9.0, 23 and 12);
+//   - for k = 2, whose single walk crosses the fewest tiles, also on longer ones
+//     where the lengths are apart, so that three families share the walkers (96 x 48
+//     15.6 and 18.3, 128 x 43 19.8 and 21.3, 160 x 80 24.1 and 25.2, 250 x 84 36.2 and
+//     36.8, 300 x 60 43.1 and 40.0);
+//   - where the jobs at once are more than half the compute units (k = 5: than all
+//     of them), since one wave a job runs beside many others (related, unrelated: 64
+//     jobs of 100..160 residues, k = 3, 37 and 31, 51 and 52; 256 of them 38 and 40, 53
+//     and 66; 1024 74 and 130, 103 and 201; 256 jobs of k = 5, 4..10 residues 17 and
+//     13, 28 and 16; 1024 27 and 38, 41 and 50).
+bool trace_by_walkers(const int32_t *n, int k, int njobs, int cus) {
+  int64_t total = 0;
+  int most = 0, least = INT32_MAX;
+  for (int i = 0; i < k; ++i) {
+    total += n[i];
+    most = n[i] > most ? n[i] : most;
+    least = n[i] < least ? n[i] : least;
+  }
+  if (k > kTrMaxK || total > kTrMaxTotal) return false;
+  if (k == 5) return njobs == 1 || njobs <= cus;
+  const bool apart = 16 * (most - least) > most;  // (as in tr_families)
+  if (most < 96 || (k == 2 && apart && most < 256)) return false;
+  return njobs == 1 || njobs <= cus / 2;
 }
 
 template <int K>

@@ -79,3 +79,17 @@ def test_server_launches_of_every_composition():
             jobs = jobs_of(shapes, 100 + b)
             tickets = [srv.submit(*j) for j in jobs]
             check(jobs, [srv.wait(t, 30_000_000) for t in tickets])
+
+
+@pytest.mark.parametrize("k,njobs", [(3, 128), (3, 129), (5, 256), (5, 257)])
+def test_traceback_of_few_and_of_many_jobs(k, njobs):
+    """Both sides of the number of jobs up to which walkers take the tracebacks
+    (half the compute units, k = 5: as many), walks of every length among them."""
+    rng = np.random.Generator(np.random.PCG64(70 + njobs))
+    sub, gap = protein_scoring()
+    shapes = [[int(x) for x in rng.integers(0, 9, k)] for _ in range(njobs)]
+    for i in range(0, njobs, 9):
+        shapes[i] = [100, 97, 12][:k] + [3] * (k - 3) if k == 3 else [9, 12, 8, 11, 10]
+    jobs = [([rng.integers(0, 20, n).astype(np.uint8) for n in lens], sub, gap) for lens in shapes]
+    say("batch of", njobs, "jobs, k =", k)
+    check(jobs, msa.align_batch(jobs, hbm_budget_bytes=4 << 30))
