@@ -258,6 +258,33 @@ void make_sweep5_order(const Plan &p, std::vector<int32_t> *order) {
         for (int c3 = 0; c3 < p.P[3]; ++c3) (*order)[at[c0 + c1 + c2 + c3]++] = b++;
 }
 
+// Where the streaming k = 3 fill is the faster one in the co-optimal and
+// near-optimal modes (in the others it always is but for lines far longer than the
+// other lengths).  Its time is that of its steps in a row: the third length,
+// 66 steps a block along dimension 1 and 14 along dimension 0 later.  The tile
+// fill's is that of its waves, and more steps a wave than measured here are
+// too many.  Tile and streaming fill, us, by steps a wave:
+//   near-optimal, whose stores of scores lengthen every step of a full block:
+//     300 x 257 x 281 (13.1) 646 and 534, 157 x 238 x 213 (13.7) 425 and 405, 419 x
+//     560 x 464 (13.9) 1226 and 1156; 20 x 200 x 200 (14.2) 284 and 305, 87 x 359 x 173
+//     (14.4) 417 and 458, 133 x 400 x 400 (14.8) 633 and 687, 20 x 512 x 512 (15.6) 678
+//     and 783; with few rows, 5 x 40 x 300 (14.3) 186 and 143, 1 x 64 x 600 (15.2) 304
+//     and 284, 2 x 512 x 512 (15.8) 467 and 501;
+//   both, few lines in all, whose tiles are small: co-optimal 2 x 2 x 300 (13.8)
+//     138 and 136, 1 x 1 x 600 (14.7) 239 and 264, 3 x 3 x 1000 (15.2) 413 and 432, 4 x 4 x
+//     600 (14.8) 274 and 264; near-optimal 1 x 1 x 1000 315 and 374, 4 x 4 x 600 226 and
+//     237.
+static bool sweep3_pays(const Plan &p, int32_t flags) {
+  if (flags != kCoOptimal && flags != kNearOpt) return true;
+  const int nb1 = p.n[1] / kSwLanes, nb0 = p.n[0] / kSwRows;  // blocks before the last
+  const int64_t steps = (int64_t)p.n[2] + 1 + 66 * (int64_t)nb1 + 14 * (int64_t)nb0 +
+                        p.n[1] % kSwLanes + p.n[0] % kSwRows / kSwRPW;
+  const int most = std::max(p.n[0], p.n[1]);
+  if (most <= (flags == kCoOptimal ? 3 : 7)) return 10 * steps <= 142 * (int64_t)p.nwaves;
+  if (flags == kCoOptimal) return true;
+  return 10 * steps <= (p.n[0] < 12 ? 155 : 142) * (int64_t)p.nwaves;
+}
+
 // The streaming k = 3 fill covers the plain mode and one of the end-gap-free,
 // co-optimal and near-optimal ones.
 bool sweep3_eligible(const Plan &p, int alpha, int32_t flags) {
@@ -266,7 +293,7 @@ bool sweep3_eligible(const Plan &p, int alpha, int32_t flags) {
   const int64_t wmax = (int64_t)p.n[2] * ((int64_t)std::max(p.n[0], p.n[1]) + 1);
   const bool mode =
       flags == 0 || flags == kEndGapsFree || flags == kCoOptimal || flags == kNearOpt;
-  return p.k == 3 && mode && alpha >= 1 && alpha <= kSwSubMax &&
+  return p.k == 3 && mode && sweep3_pays(p, flags) && alpha >= 1 && alpha <= kSwSubMax &&
          p.n[2] <= kSwSeqMax && wmax < ((int64_t)1 << 31);
 }
 
