@@ -948,13 +948,24 @@ int launch_coopt_trace(const JobDev &jd, Ctrl *ctrl, int32_t max_paths, uint8_t 
 // walk leaves the box.  The list below a cell depends on the cell and on the
 // score so far alone, and its first entry is what a walk that comes to both
 // again goes on with; so new cells are recorded with that score (k <= 5), and
-// a walk that meets such a record copies the columns below it.  16 alignments
+// a walk that meets such a record copies the columns below it.  A record is found
+// by a hash of cell and score.  16 alignments
 // of 300 x 257 x 281: 1.54 ms with global loads for everything at every step,
 // 1.38 with the box alone.
 // ---------------------------------------------------------------------------
 constexpr int kNoThreads = 1024;
 constexpr int kNoPool = 3072;    // recorded cells
 constexpr int kNoWalks = 512;    // recorded walks
+constexpr int kNoHash = 4096;    // chains of records
+
+// Chain of a cell (its packed coordinates) and a score so far: multiplicative
+// hashing (Knuth, The Art of Computer Programming, vol. 3, section 6.4) with
+// odd multipliers near 2^32 divided by the golden ratio, top 12 bits.
+__device__ __forceinline__ int no_hash(uint64_t cell, int32_t score) {
+  const uint32_t x = (uint32_t)cell * 0x9E3779B1u + (uint32_t)(cell >> 32) * 0x9E377955u +
+                     (uint32_t)score;
+  return (int)((x * 0x9E3779B1u) >> 20);
+}
 
 template <int K>
 struct NoSmem {
@@ -963,7 +974,7 @@ struct NoSmem {
   static constexpr int NP = K * (K - 1) / 2;
   static constexpr bool Memo = K <= 5;  // a cell fits the record (13 bits a coordinate)
   static constexpr int Pool = Memo ? kNoPool : 1;
-  uint64_t cell[Pool];             // recorded cell (v_0 .. v_{k-2}), by record
+  uint64_t cell[Pool];             // recorded cell (v_0 .. v_{k-2} and the sum), by record
   uint64_t pass[kNoMaxTotal + 1];  // masks that passed at a column's cell
   int32_t sofar[kNoMaxTotal + 1];  // score of the columns above it
   int32_t box[N];                  // xi(top - x) at sum x_i * E^(K-1-i)
@@ -972,8 +983,8 @@ struct NoSmem {
   uint32_t set[Pool];              // its cell's passing masks
   uint8_t mask[Pool];              // and the one taken (the lowest)
   uint16_t walk[Pool];             // its walk
-  uint16_t link[Pool];             // another record of the same coordinate sum
-  uint16_t head[Memo ? kNoMaxTotal + 1 : 1];  // by coordinate sum (0xFFFF: none)
+  uint16_t link[Pool];             // another record of the same hash
+  uint16_t head[Memo ? kNoHash : 1];  // by hash of cell and score (0xFFFF: none)
   uint16_t wend[kNoWalks];         // a walk's records end before this one
   int16_t wnext[kNoWalks];         // and go on with this one (-1: the origin,
   int32_t wlast[kNoWalks];         // with this score)
@@ -1009,7 +1020,7 @@ __global__ __launch_bounds__(kNoThreads) void nearopt_kernel(JobDev jd, Ctrl *ct
   const int total = (int)jd.total_len;
   for (int x = tid; x < total; x += kNoThreads) sm.seq[x] = jd.seqs[x];
   if constexpr (Sm::Memo)
-    for (int x = tid; x <= total; x += kNoThreads) sm.head[x] = 0xFFFF;
+    for (int x = tid; x < kNoHash; x += kNoThreads) sm.head[x] = 0xFFFF;
   if (tid == 0) {
     sm.sofar[0] = 0;
     sm.status = status;
@@ -1135,9 +1146,11 @@ __global__ __launch_bounds__(kNoThreads) void nearopt_kernel(JobDev jd, Ctrl *ct
         if constexpr (Sm::Memo) {
 #pragma unroll
           for (int i = 0; i < K - 1; ++i) cell |= (uint64_t)(uint32_t)v[i] << (13 * i);
+          cell |= (uint64_t)(uint32_t)h << 52;  // (for the last coordinate; kNoMaxTotal itself, the
+                                                // end cell's, is looked up by no walk)
           if (fresh && np > 0) {
             // met a record of this cell and score?  (one lookup per new cell)
-            int x = __builtin_amdgcn_readfirstlane((int)sm.head[h]);
+            int x = __builtin_amdgcn_readfirstlane((int)sm.head[no_hash(cell, sf)]);
             while (x != 0xFFFF) {
               const bool same = sm.cell[x] == cell && sm.score[x] == sf;
               if (__builtin_amdgcn_readfirstlane((int)same)) break;
@@ -1234,8 +1247,9 @@ __global__ __launch_bounds__(kNoThreads) void nearopt_kernel(JobDev jd, Ctrl *ct
             sm.set[nrec] = (uint32_t)set;
             sm.mask[nrec] = (uint8_t)b;
             sm.walk[nrec] = (uint16_t)nwalk;
-            sm.link[nrec] = sm.head[h];
-            sm.head[h] = (uint16_t)nrec;
+            const int at = no_hash(cell, sf);
+            sm.link[nrec] = sm.head[at];
+            sm.head[at] = (uint16_t)nrec;
             ++nrec;
           }
         }

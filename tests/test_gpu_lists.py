@@ -69,3 +69,21 @@ def test_coopt_list(lens, paths):
         s1, got = dev.result_coopt()
         assert s1 == s0 and len(got) == len(want)
         assert all(np.array_equal(a, b) for a, b in zip(got, want))
+
+
+@pytest.mark.parametrize("lens,paths", [([12, 9], 1200), ([8, 7, 9], 1200), ([6, 7, 5, 6], 900),
+                                        ([4, 5, 4, 3, 5], 700), ([9, 2, 3, 2, 2, 8], 300)], ids=str)
+def test_nearopt_list_of_short_sequences_wide_margin(lens, paths):
+    """Many cells of one coordinate sum, many scores at each, and more of them
+    than are recorded; cells that differ in the last coordinate alone."""
+    for sub, gap in (protein_scoring(), dna_scoring()):
+        seqs = draw(sum(lens), lens, 4)
+        say("nearopt wide", lens, paths)
+        s0, want = oracle_nearopt(seqs, sub, gap, 60, paths)
+        dev = msa.DeviceAligner(lens, sub, gap, nearopt=True)
+        dev.set_sequences(seqs)
+        dev.run_nearopt(60, paths)
+        s1, got = dev.result_nearopt()
+        assert s1 == s0 and len(got) == len(want)
+        for (sa, ra), (sb, rb) in zip(got, want):
+            assert sa == sb and np.array_equal(ra, rb)
