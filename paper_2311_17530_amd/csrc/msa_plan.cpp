@@ -103,8 +103,13 @@ int make_plan(const int32_t *lens, int32_t k, Plan *p, bool streams) {
     // Shapes whose exchange region would be far larger than the face planes
     // keep the tile fill; the kernel forms offsets in the region in 32 bits.
     const int64_t bytes = sweep5_x_words(q) * 4;
+    // Nor do shapes of many tile waves whose blocks are hardly longer than
+    // their skew: each wave waits for a block's start (tile and streaming fill, us:
+    // 100 x 100 x 3 x 3 x 3, 54 waves, 497 and 547; 4 x 100 x 100 x 4 x 4 524 and 542; 60 x 60 x
+    // 8 x 8 x 2, 36 waves, 367 and 363; 40 x 40 x 12 x 12 x 3, 28 waves, 306 and 256; 120 x
+    // 60 x 4 x 4 x 8, 50 waves, 525 and 477).
     q.s5 = bytes <= std::max<int64_t>(2 * q.face_elems * 4, kS4SmallX) &&
-           bytes < ((int64_t)1 << 32);
+           bytes < ((int64_t)1 << 32) && !(q.n[4] <= 4 && q.nwaves > 40);
   }
   // workspace layout
   int64_t o = 0;

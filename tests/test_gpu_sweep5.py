@@ -125,3 +125,24 @@ def test_sweep5_batched_jobs_match_oracle():
         for (seqs, sub, gap), (st, s1, r1) in zip(jobs, msa.align_batch(jobs)):
             s0, r0 = oracle_align(seqs, sub, gap)[:2]
             assert st == msa.MSA_OK and s1 == s0 and np.array_equal(r1, r0)
+
+
+# both sides of the rule on short fifth sequences beside many tile waves
+@pytest.mark.parametrize("lens", [[64, 64, 3, 3, 4], [68, 72, 3, 4, 4], [68, 72, 3, 4, 5],
+                                  [1, 72, 72, 0, 0]], ids=lambda s: "x".join(map(str, s)))
+def test_sweep5_many_waves_of_short_blocks(lens):
+    sub, gap = protein_scoring()
+    dev = msa.DeviceAligner(lens, sub, gap)
+    seqs = draw(sum(lens), lens, 20)
+    say("sweep5", lens)
+    dev.set_sequences(seqs)
+    dev.run()
+    s0, r0, d0 = oracle_align(seqs, sub, gap, want_dir=True)
+    s1, r1 = dev.result()
+    assert s1 == s0 and np.array_equal(r1, r0)
+    assert np.array_equal(dev.export_dirs(), d0)
+    # in a batch, beside a shape of the other kind
+    jobs = [(seqs, sub, gap), (draw(1, [5, 6, 7, 8, 9], 20), sub, gap)]
+    for (sq, _, _), (st, s1, r1) in zip(jobs, msa.align_batch(jobs)):
+        s0, r0 = oracle_align(sq, sub, gap)[:2]
+        assert st == msa.MSA_OK and s1 == s0 and np.array_equal(r1, r0)
