@@ -13,6 +13,18 @@ static int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 
 static bool mul_ok(int64_t a, int64_t b, int64_t lim) { return a == 0 || b <= lim / a; }
 
+// Whether a streaming fill's exchange regions, which share the face planes'
+// memory, are small enough beside them: at most twice as large, or 64 MB; and no
+// larger where the workspace is a large part of the card's memory, so that every
+// shape that the tile fill's workspace lets on the card still fits it (509 x 1506
+// x 1153 x 34: 109 GB, 143 with the exchange regions).
+static bool exchange_fits(const Plan &p, int64_t bytes) {
+  const int64_t faces = p.face_elems * 4;
+  if (bytes <= faces) return true;
+  return bytes <= std::max<int64_t>(2 * faces, kS4SmallX) &&
+         bytes + p.ntiles * p.dbs <= kStreamWsMax;
+}
+
 int make_plan(const int32_t *lens, int32_t k, Plan *p, bool streams) {
   if (!lens || !p || k < 2 || k > kMaxK) return MSA_EINVAL;
   Plan q;
@@ -93,7 +105,7 @@ int make_plan(const int32_t *lens, int32_t k, Plan *p, bool streams) {
     // (short second and third sequences leave most lanes of a block idle) keep
     // the tile fill; the kernel forms a line's offset in the direction blocks
     // of one tile row along dimension 0 in 32 bits.
-    q.s4 = sweep4_x_words(q) * 4 <= std::max<int64_t>(2 * q.face_elems * 4, kS4SmallX) &&
+    q.s4 = exchange_fits(q, sweep4_x_words(q) * 4) &&
            (int64_t)q.tstride[0] * q.dbs < ((int64_t)1 << 32);
   }
   if (streams && k == 5 && q.n[4] <= kS5SeqMax) {
@@ -108,8 +120,8 @@ int make_plan(const int32_t *lens, int32_t k, Plan *p, bool streams) {
     // 100 x 100 x 3 x 3 x 3, 54 waves, 497 and 547; 4 x 100 x 100 x 4 x 4 524 and 542; 60 x 60 x
     // 8 x 8 x 2, 36 waves, 367 and 363; 40 x 40 x 12 x 12 x 3, 28 waves, 306 and 256; 120 x
     // 60 x 4 x 4 x 8, 50 waves, 525 and 477).
-    q.s5 = bytes <= std::max<int64_t>(2 * q.face_elems * 4, kS4SmallX) &&
-           bytes < ((int64_t)1 << 32) && !(q.n[4] <= 4 && q.nwaves > 40);
+    q.s5 = exchange_fits(q, bytes) && bytes < ((int64_t)1 << 32) &&
+           !(q.n[4] <= 4 && q.nwaves > 40);
   }
   // workspace layout
   int64_t o = 0;

@@ -80,6 +80,10 @@ void make_sweep4_order(const Plan &p, std::vector<int32_t> *order);
 // fit its LDS tables, in every mode but the pruned one.
 bool sweep3_eligible(const Plan &p, int alpha, int32_t flags);
 
+// Workspaces up to this size may be larger for a streaming fill than for the
+// tile fill (a quarter of the card's memory, bytes).
+constexpr int64_t kStreamWsMax = (int64_t)72 << 30;
+
 constexpr int64_t kSubBytes = 255 * 255;
 constexpr int64_t kMaxTiles = (int64_t)1 << 30;
 
