@@ -59,7 +59,14 @@ struct JobSizes {
 
 // cap: bytes of the arena the job has to fit.  A k = 4 or 5 job takes the streaming
 // fill where that is possible; where only the tile fill's smaller layout fits
-// the arena, it keeps that.
+// the arena, it keeps that.  So do all k = 5 jobs in an arena below kSmallArena: there, fewer
+// launches give more than the faster fill, and jobs of both kinds in a launch wait for
+// each other (512 jobs of
+// 5..12 residues, tile and streaming fill, ms: 32 MB 10.3 and 16.6, 64 MB 9.0 and 11.6,
+// 128 MB 8.3 and 9.0, 256 MB 7.9 and 8.0, 512 MB 7.8 and 7.6; 256 of 12..20 64 MB 25.2
+// and 32.4, 128 MB 19.4 and 18.6, 256 MB 16.7 and 13.6; k = 4, whose layouts grow by less,
+// 512 jobs of 16..40 in 64 MB 15.6 and 13.3).
+constexpr int64_t kSmallArena = (int64_t)96 << 20;
 int sizes_of(const msa_job &j, int64_t cap, JobSizes *s) {
   int rc = make_plan(j.lens, j.k, &s->p);
   if (rc) return rc;
@@ -81,7 +88,9 @@ int sizes_of(const msa_job &j, int64_t cap, JobSizes *s) {
     t.x = a256((p.k == 5 ? sweep5_x_words(p) : sweep4_x_words(p)) * 4);
     t.small = a256(std::max<int64_t>(p.total_len, 1)) + a256((int64_t)t.keys.size() * 4) + 256;
     t.big = a256(std::max<int64_t>(p.total_len, 1)) + a256(p.ntiles * p.dbs);
-    if (t.total(p.ntiles) + Launch::overhead_bytes(1, p.ntiles) <= cap) *s = t;
+    if (t.total(p.ntiles) + Launch::overhead_bytes(1, p.ntiles) <= cap &&
+        (p.k == 4 || cap >= kSmallArena))
+      *s = t;
   }
   return MSA_OK;
 }
