@@ -89,3 +89,30 @@ def test_fill_kernel_occupancy(usage, kernel):
 def test_no_kernel_uses_scratch(usage):
     used = {d: sc for d, (v, o, sc) in usage.items() if sc}
     assert not used, used
+
+
+# the same for the streaming fills (two workgroups of 8 waves a compute unit for
+# k = 4, four of 5 waves for k = 5, one of 9 waves for k = 3) and the walkers' kernels
+# (one workgroup of 16 waves a compute unit, 4 a SIMD)
+STREAM_FLOORS = {
+    "msa::sweep4_kernel": 4,
+    "msa::batch_sweep4_kernel": 4,
+    "msa::sweep5_kernel": 5,
+    "msa::batch_sweep5_kernel": 5,
+    "void msa::trace_kernel<2>": 4,
+    "void msa::trace_kernel<3>": 4,
+    "void msa::trace_kernel<4>": 4,
+    "void msa::trace_kernel<5>": 4,
+    "void msa::batch_trace_kernel<2, 4>": 4,
+    "void msa::batch_trace_kernel<5, 5>": 4,
+    "void msa::nearopt_kernel<3>": 4,
+}
+
+
+@pytest.mark.parametrize("kernel", sorted(STREAM_FLOORS))
+def test_streaming_and_walker_kernel_occupancy(usage, kernel):
+    hits = [(d, vo) for d, vo in usage.items() if d.startswith(kernel + "(")]
+    assert len(hits) == 1, (kernel, [d for d in usage if "sweep" in d or "trace" in d])
+    d, (v, o, sc) = hits[0]
+    assert o >= STREAM_FLOORS[kernel], f"{d}: {v} VGPRs, {o} waves/SIMD"
+    assert sc == 0, f"{d}: {sc} bytes of scratch per lane"
