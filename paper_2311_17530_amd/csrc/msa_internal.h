@@ -92,6 +92,10 @@ struct Ctrl {
   int32_t alpha;    // scoring fixed at set-up (plain path)
   int32_t gap;
   int32_t flags;    // kEndGapsFree / kCoOptimal (plain path, set at set-up)
+  int32_t sweeps;   // streaming fills finished on this workspace (see
+                    // next_sweep): their exchange values carry its tag
+  int32_t swept;    // 1 once the current fill is a streaming one; the kernel
+                    // that ends the alignment then counts it
   int64_t best;     // end-gap-free: max of (score << 32 | row-major cell index)
                     // over the far faces; INT64_MIN between launches
   // pruned mode (tile bounds): U = sum of pairwise optima, the threshold of
@@ -112,11 +116,7 @@ struct Ctrl {
                       // (batched launches report it)
   int64_t wait_limit;  // batched launches: dependency-wait time-out in 100 MHz
                        // ticks (0: 2 s)
-  int32_t sweeps;   // streaming fills finished on this workspace (see
-                    // next_sweep): their exchange values carry its tag
   int32_t s4head;   // next slot of a batched launch's queue of streaming blocks
-  int32_t swept;    // 1 once the current fill is a streaming one; the kernel
-                    // that ends the alignment then counts it
   int32_t pad[23];
 };
 static_assert(sizeof(Ctrl) == 256, "control block is one 256-byte slot");

@@ -96,13 +96,13 @@ def test_repeated_tracebacks_between_streaming_fills():
 @pytest.mark.parametrize("lens", [[30, 70, 20], [9, 20, 18, 11], [6, 5, 9, 7, 8]],
                          ids=lambda s: "k%d" % len(s))
 def test_count_of_streaming_fills_stays_small(lens):
-    """The count behind the tags is word 38 of the control block, which a
+    """The count behind the tags is word 6 of the control block, which a
     workspace starts with.  It starts again after 105 fills and, set to the
     largest integer, goes on with valid tags."""
     import torch
     sub, gap = protein_scoring()
     dev = msa.DeviceAligner(lens, sub, gap)
-    off = dev.ws_ptr - dev.ws.data_ptr() + 4 * 38
+    off = dev.ws_ptr - dev.ws.data_ptr() + 4 * 6
     count = dev.ws[off: off + 4].view(torch.int32)
 
     def one(seed):
