@@ -113,7 +113,9 @@ struct Ctrl {
                       // the tile, the mask of the predecessor dimensions
                       // still missing, the first missing predecessor tile,
                       // the value its flag held, and the queue head then
-                      // (batched launches report it)
+                      // (batched launches report it); of a streaming fill -2 -
+                      // the job's place among the streaming ones, the block, 0,
+                      // 0, 0 and the head of the block queue
   int64_t wait_limit;  // batched launches: dependency-wait time-out in 100 MHz
                        // ticks (0: 2 s)
   int32_t s4head;   // next slot of a batched launch's queue of streaming blocks
@@ -164,6 +166,23 @@ __host__ __device__ inline int32_t next_sweep(int32_t sweeps, int32_t more) {
 }
 __host__ __device__ inline int sweep_tag(int32_t sweeps, int tags) {
   return (int)((uint32_t)sweeps % (uint32_t)tags) + 1;
+}
+
+// Reports a streaming fill's wait that timed out; the launch's first one also
+// leaves its job and block (one lane, or all of a wave with the same values).  (The
+// constants are formed here, not kept in registers across a persistent loop.)
+__device__ __forceinline__ void sweep_timed_out(Ctrl *ctrl, int job, int block) {
+  int none = 0, code = -4;
+  asm volatile("" : "+v"(none), "+v"(code));
+  if (atomicCAS(&ctrl->status, none, code) == none) {
+    int32_t *const wd = reinterpret_cast<int32_t *>(ctrl->wd);  // (low words first)
+    wd[none] = -2 - job;
+    wd[none + 1] = -1;
+    wd[none + 2] = block;
+    for (int x = none + 3; x < 12; ++x) wd[x] = none;
+    wd[none + 10] =
+        __hip_atomic_load(&ctrl->s4head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
 }
 
 // Readies the control block for the next launch on this workspace (one lane

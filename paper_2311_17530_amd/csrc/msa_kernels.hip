@@ -1650,7 +1650,7 @@ __global__ void batch_finish_kernel(const BatchArgs *__restrict__ a, Ctrl *ctrl)
       g64[1 + q] = ctrl->wd[q];
       ctrl->wd[q] = 0;
     }
-    g64[7] = a->cols;
+    g64[7] = g64[1] <= -2 ? a->s4total : a->cols;  // the queue that the wait stood in
     ctrl->max_pause = 0;
     ctrl->head = 0;
     ctrl->status = ST_OK;

@@ -478,7 +478,7 @@ int Launch::start(const std::vector<const msa_job *> &jobs,
     meta_[i].k = j.k;
     meta_[i].cap = sz[i].cap;
     meta_[i].aln_off = job_out[i] - off_out;
-    meta_[i].qbase = s4 ? -2 : jt[i];
+    meta_[i].qbase = s4 ? -1 - (int64_t)s4base.size() : jt[i];  // (-2 - n of streaming job n)
   }
 
   // The queue holds tile columns along dimension 0 (a workgroup computes a

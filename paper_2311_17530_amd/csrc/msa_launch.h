@@ -81,7 +81,8 @@ class Launch {
   // staged ones (-1 if not found), its tile and the mask of the predecessor
   // dimensions it still missed; `more` (if not null) receives the first
   // missing predecessor tile, the value its flag held, the queue head then and
-  // the queue length.  False when the launch did not time out.
+  // the queue length.  (A streaming fill's: the block, no mask, 0, 0, the head and
+  // the length of the block queue.)  False when the launch did not time out.
   bool device_timeout(int *job, int64_t *tile, int64_t *missing,
                       int64_t more[4] = nullptr) const;
   int njobs() const { return (int)meta_.size(); }
@@ -100,7 +101,8 @@ class Launch {
     int k = 0;
     int64_t cap = 0;
     int64_t aln_off = 0;  // offset of the rows in the host output image
-    int64_t qbase = 0;    // first tile of the job in the launch's numbering
+    int64_t qbase = 0;    // first tile of the job in the launch's numbering (streaming: -2 - its
+                          // place among the streaming jobs)
   };
   int device_ = -1;
   hipStream_t stream_ = nullptr;

@@ -207,11 +207,13 @@ void msa_server::collect(Slot &s) {
         for (int d = 0; d < j.k; ++d) fprintf(stderr, " %lld", (long long)j.lens[d]);
         fprintf(stderr, ")");
       }
-      fprintf(stderr,
-              ", tile %lld, missing predecessor dimensions 0x%llx (tile %lld, flag %lld), "
-              "queue head %lld of %lld\n",
-              (long long)tile, (unsigned long long)missing, (long long)more[0],
-              (long long)more[1], (long long)more[2], (long long)more[3]);
+      if (missing != 0)
+        fprintf(stderr, ", tile %lld, missing predecessor dimensions 0x%llx (tile %lld, flag %lld)",
+                (long long)tile, (unsigned long long)missing, (long long)more[0],
+                (long long)more[1]);
+      else
+        fprintf(stderr, ", block %lld", (long long)tile);
+      fprintf(stderr, ", queue head %lld of %lld\n", (long long)more[2], (long long)more[3]);
     }
   }
   // A launch whose dependency wait timed out is re-run once: its jobs go back

@@ -101,7 +101,7 @@ struct S4Smem {
   int32_t sub16[kS4SubMax * kS4SubRow];      // substitution matrix << 4
   uint8_t s3[kS4Front + kS4SeqMax + 64];
   int32_t late, pause;  // the loader's watchdog fired; longest pause it saw (ticks)
-  int32_t item;
+  int32_t item, job;
 };
 static_assert(kS4Front > kS4Skew, "cells t < 0 read residue codes of the padding");
 
@@ -646,7 +646,7 @@ __device__ __forceinline__ void s4_block(const Sweep4Dev &sd, S4Smem &sm, int it
     s4_barrier();
     s4_sweep(sd, sm, B0, B1, B2, tid, gap, total);
     if (tid == 0) {
-      if (sm.late) atomicCAS(&ctrl->status, 0, -4);
+      if (sm.late) sweep_timed_out(ctrl, sm.job, item);
       if (sm.pause > 0)
         __hip_atomic_fetch_max(&ctrl->max_pause, (int64_t)sm.pause, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
@@ -659,7 +659,10 @@ __device__ __forceinline__ void s4_block(const Sweep4Dev &sd, S4Smem &sm, int it
 __global__ __launch_bounds__(kS4Threads) __attribute__((amdgpu_waves_per_eu(4)))
 void sweep4_kernel(Sweep4Dev sd, Ctrl *ctrl) {
   __shared__ S4Smem sm;
-  if (threadIdx.x == 0) sm.item = atomicAdd(&ctrl->head, 1);
+  if (threadIdx.x == 0) {
+    sm.item = atomicAdd(&ctrl->head, 1);
+    sm.job = 0;
+  }
   const int alpha = ctrl->alpha;
   const int gap = ctrl->gap;
   const int tag = sweep_tag(ctrl->sweeps, kSweepTags);
@@ -729,6 +732,7 @@ void batch_sweep4_kernel(const BatchArgs *__restrict__ a, Ctrl *ctrl) {
     if (it >= total) break;
     const int job = __builtin_amdgcn_readfirstlane(q[2 * it]);
     const int blk = __builtin_amdgcn_readfirstlane(q[2 * it + 1]);
+    if (threadIdx.x == 0) sm.job = job;  // (read by the same thread)
     // the job's descriptor, kept in scalar registers
     Sweep4Dev sd;
     {

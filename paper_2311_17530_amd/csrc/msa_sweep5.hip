@@ -253,9 +253,7 @@ struct S5Aux {
           last = now;
           if (d < most) waited += d;
           else pause = d > pause ? d : pause;
-          const bool late = waited > (uint32_t)wlim;
-          if (late) s5_report(&ctrl->status, -4);
-          if (late || st == -4) {  // (or another workgroup timed out)
+          if (waited > (uint32_t)wlim || st == -4) {  // (or another workgroup timed out)
             dead = true;           // the rest of the block waits for nothing
             break;
           }
@@ -312,6 +310,7 @@ struct S5Aux {
       }
     }
     pass_on(kS5Ring - 1, tag);
+    if (dead) sweep_timed_out(ctrl, sm.job, sm.item);  // (here, where few registers are in use)
     next(ticket);
   }
 };
@@ -550,6 +549,7 @@ void sweep5_kernel(Sweep5Dev sd, Ctrl *ctrl) {
   const int total = sd.nb[0] * sd.nb[1] * sd.nb[2] * sd.nb[3];
   const bool more = total > (int)gridDim.x;
   auto next = [&](int ticket) {
+    sm.job = 0;
     sm.item = ticket >= 0 && ticket < total ? sd.order[ticket] : -1;
   };
   s5_tables(sm);
