@@ -71,10 +71,11 @@ enum {
  * keys by k and ceil(log2(longest length + 1)); the batched path by k class
  * (k = 2..4, 5, 6, 7..8).  Thread-safe; the table lives for the process.
  *   kind    : MSA_TUNE_PLAIN or MSA_TUNE_BATCH
- *   variant : plain path: 0 the built-in rule, 1 the streaming k = 3 fill
- *             (used only where it applies), 2 the tile fill; batched: 0
+ *   variant : plain path: 0 the built-in rule, 1 the streaming fill of k = 3,
+ *             4 or 5 (used only where it applies), 2 the tile fill; batched: 0
  *   wpc     : workgroups per compute unit of the tile fill or the batched
- *             fill (capped at what fits); 0 the built-in rule
+ *             tile fill (capped at what fits; the streaming fills of batched
+ *             k = 4 and 5 jobs have no such choice); 0 the built-in rule
  * msa_dp_tune_set stores a choice, msa_dp_tune_get reads it ((0, 0) when
  * none is stored) into choice_out[2], msa_dp_tune_clear empties the table.
  * msa_dp_tune_candidates writes up to cap / 2 (variant, wpc) pairs the tuner
@@ -85,9 +86,10 @@ enum {
  * (and its time in *best_ms_out when not NULL).  It allocates a workspace of
  * msa_dp_workspace_bytes(lens, k) bytes for the duration of the call.
  * msa_dp_autotune_batch runs msa_dp_align_batch on the jobs of each k class
- * present with every candidate workgroup count (`reps` timed runs each,
- * median wall time) and stores the fastest; wpc_out[4] receives the choice
- * per k class (0 for classes not present).
+ * present that take the tile fill with every candidate workgroup count (`reps`
+ * timed runs each, median wall time) and stores the fastest; wpc_out[4]
+ * receives the choice per k class (0 for classes not present, the built-in
+ * rule's count for classes whose jobs all take a streaming fill).
  * Errors: MSA_EINVAL for bad arguments, the errors of msa_dp_align /
  * msa_dp_align_batch, MSA_EDEVICE.
  * ---------------------------------------------------------------------- */

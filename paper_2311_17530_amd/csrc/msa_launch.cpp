@@ -102,6 +102,11 @@ int64_t job_arena_bytes(const msa_job &j, int64_t cap) {
   return s.total(s.p.ntiles);
 }
 
+bool job_streams(const msa_job &j, int64_t cap) {
+  JobSizes s;
+  return sizes_of(j, cap, &s) == MSA_OK && s.s4;
+}
+
 int64_t Launch::overhead_bytes(int njobs, int64_t ntiles_total) {
   int64_t tables = 0;
   for (int k = 2; k <= kMaxK; ++k) {

@@ -22,8 +22,15 @@ int validate_job(const msa_job &j, int64_t aln_cap_needed_check = -1);
 // instead of 1 beside k = 8).
 inline int kclass_of(int k) { return k <= 4 ? 0 : k == 5 ? 1 : k == 6 ? 2 : 3; }
 
+// Bytes of a batch's arena where the caller sets no budget (msa_batch.cpp).
+int64_t default_budget();
+
 // Device bytes one job needs inside a launch arena of `cap` bytes.
 int64_t job_arena_bytes(const msa_job &j, int64_t cap);
+
+// Whether the job takes a streaming fill in an arena of `cap` bytes (else the tile
+// fill).
+bool job_streams(const msa_job &j, int64_t cap);
 
 struct LaunchResult {
   int32_t status = MSA_OK;

@@ -29,9 +29,6 @@
 #include "../../include/msa_dp.h"
 #include "msa_launch.h"
 
-namespace msa {
-int64_t default_budget();
-}
 using namespace msa;
 
 namespace {

@@ -235,10 +235,21 @@ extern "C" int msa_dp_autotune_batch(const msa_job *jobs, int32_t njobs, int32_t
     if (validate_job(jobs[i]) != MSA_OK) return MSA_EINVAL;
   for (int c = 0; c < 4; ++c) wpc_out[c] = 0;
   for (int kc = 0; kc < 4; ++kc) {
+    // the count is the tile fill's: only jobs that take it are timed
     std::vector<msa_job> cls;
+    int present = 0;
     for (int i = 0; i < njobs; ++i)
-      if (kclass_of(jobs[i].k) == kc) cls.push_back(jobs[i]);
-    if (cls.empty()) continue;
+      if (kclass_of(jobs[i].k) == kc) {
+        present = jobs[i].k;
+        if (!job_streams(jobs[i], default_budget())) cls.push_back(jobs[i]);
+      }
+    if (!present) continue;
+    if (cls.empty()) {  // none does: the built-in rule's count
+      const int occ = std::max(batch_occupancy(kc), 1);
+      tune_set(kTuneBatch, kc, 0, TuneChoice{0, occ});
+      wpc_out[kc] = occ;
+      continue;
+    }
     std::vector<std::vector<uint8_t>> bufs(cls.size());
     std::vector<msa_result> res(cls.size());
     for (size_t i = 0; i < cls.size(); ++i) {

@@ -86,3 +86,23 @@ def test_every_batched_candidate_gives_the_same_bytes():
     res = msa.align_batch(jobs)
     for (st, score, rows), (s0, r0) in zip(res, plain):
         assert st == msa.MSA_OK and score == s0 and np.array_equal(rows, r0)
+
+
+def test_batched_choice_without_jobs_of_the_tile_fill():
+    """Jobs that all take a streaming fill have no workgroup count to choose:
+    the class keeps the built-in rule's, the most that fit, every time."""
+    rng = np.random.Generator(np.random.PCG64(9800))
+    sub, gap = protein_scoring()
+    jobs = [([rng.integers(0, 20, size=n).astype(np.uint8) for n in lens], sub, gap)
+            for lens in ([9, 12, 7, 10], [16, 15, 9, 8], [5, 6, 7, 4, 6], [7, 5, 6, 5, 4])]
+    try:
+        for _ in range(2):
+            say("autotune_batch, streaming jobs")
+            choice = msa.autotune_batch(jobs, reps=1)
+            for kc, k in ((0, 4), (1, 5)):
+                assert choice[kc] == max(w for _, w in msa.tune_candidates(msa.MSA_TUNE_BATCH, k, 0))
+        for (seqs, _, _), (st, score, rows) in zip(jobs, msa.align_batch(jobs)):
+            s0, r0 = oracle_align(seqs, sub, gap)[:2]
+            assert st == msa.MSA_OK and score == s0 and np.array_equal(rows, r0)
+    finally:
+        msa.tune_clear()
