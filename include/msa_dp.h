@@ -307,8 +307,10 @@ int msa_dp_align_dev(void *d_workspace, int64_t ws_bytes,
  * inputs come by value, so the call only enqueues kernels on hip_stream
  * (asynchronous).  Arguments as msa_dp_align_dev, plus the scoring of
  * msa_dp_prepare (submat is a host pointer read during the call).
- * Limits: alpha <= 32 and a workspace (msa_dp_workspace_bytes) of at most
- * 32 MiB -- MSA_EINVAL / MSA_ENOMEM otherwise, returned at once with nothing
+ * Limits: alpha <= 32 and a workspace of at most 32 MiB (for k = 4 and 5 the
+ * tile fill's, which msa_dp_workspace_bytes may exceed by about 64 MiB: it
+ * includes the streaming fill's exchange memory, which this call does not
+ * use) -- MSA_EINVAL / MSA_ENOMEM otherwise, returned at once with nothing
  * enqueued; the other errors as msa_dp_align_dev.  Plain mode only.
  * Every call on a device shares that device's array, which keeps the last
  * call's contents (the set-up rewrites what must start cleared): calls that
