@@ -88,7 +88,7 @@ constexpr int64_t kSubBytes = 255 * 255;
 constexpr int64_t kMaxTiles = (int64_t)1 << 30;
 
 // Fills geometry and layout; returns 0 or a negative status.  Without
-// `streams`, the layout of the tile fill alone (k = 4).
+// `streams`, the layout of the tile fill alone (k = 4 and 5).
 int make_plan(const int32_t *lens, int32_t k, Plan *p, bool streams = true);
 
 // Tiles ordered by computation wave (sum of tile coordinates).

@@ -139,7 +139,7 @@ extern "C" int msa_dp_align_static(const uint8_t *d_seqs, const int32_t *lens, i
     if (lens[i] < 0) return MSA_EINVAL;
   if (alpha < 1 || alpha > kStaticSubMax) return MSA_EINVAL;
   Plan p;
-  int rc = make_plan(lens, k, &p, false);  // (k = 4: the tile fill)
+  int rc = make_plan(lens, k, &p, false);  // (k = 4 and 5: the tile fill)
   if (rc) return rc;
   if (aln_cap < p.total_len || (p.total_len > 0 && (!d_aln || !d_seqs))) return MSA_EINVAL;
   rc = check_scoring_mode(lens, k, submat, alpha, gap, 0u);

@@ -31,9 +31,15 @@
 //     follows the blocks before it in each dimension, so a workgroup only
 //     waits for workgroups that are already running.
 //
-// What bounds it: vector issue.  A step is about 150 vector instructions a
-// compute wave (37 lane slots a cell; the tile kernel's took 129), 0.39 us for
-// a workgroup alone on its compute unit and 0.67 for two of them side by side.
+// What bounds it: vector issue for a little more than half of the time, and the
+// chain of a step (ring write, barrier, ring reads) where two workgroups do not
+// cover each other.  A step is about 150 vector instructions a compute wave (37 lane
+// slots a cell; the tile kernel's took 129), 0.39 us for a workgroup alone on its
+// compute unit and 0.67 for two of them side by side, of which issue is 0.46; in
+// all 129^4 takes 247 M vector instructions, 0.40 of 0.75 ms, and moves 2.25 GB of
+// exchange words and directions (3 TB/s).  Of the cell slots 60% are cells: all
+// lanes wait for the last one's skew, and a last block along dimension 1 or 2 may
+// hold few lanes.
 // Measured (129^4): fill 0.76 ms against 1.61 with the tile kernel; 46 x 34 x 62
 // x 39: 0.11 against 0.30.  On the way there: one workgroup of 8 rows, four
 // compute waves and one loader, all LDS reads after the barrier 1.03 ms (the
@@ -126,9 +132,9 @@ __device__ __forceinline__ void s4_store4(int32_t *base, uint32_t off, i32x4 v) 
                : "memory");
 }
 
-// Steps a block runs: lane (q1, q2) computes its last stored cell, the end of the last 4-cell run, at step 4 * ceil(n3 / 4) + q1 + q2; a
-// ragged block (the last along dimension 1 or 2) stops after its last valid
-// lane.
+// Steps a block runs: lane (q1, q2) computes its last stored cell, the end of the
+// last 4-cell run, at step 4 * ceil(n3 / 4) + q1 + q2; a ragged block (the last
+// along dimension 1 or 2) stops after its last valid lane.
 __device__ __forceinline__ int s4_steps(const Sweep4Dev &sd, int B1, int B2) {
   const int j1 = min(15, sd.n[1] - B1 * 16);
   const int j2 = min(15, sd.n[2] - B2 * 16);

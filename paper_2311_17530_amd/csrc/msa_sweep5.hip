@@ -26,8 +26,9 @@
 //     workgroup only waits for workgroups that are already running.
 //
 // What bounds it: a step's latency and issue together.  A step takes 0.5 us for a
-// workgroup alone on its compute unit and 0.7 for four of them, of which its 90
-// vector instructions a compute wave take 0.6 at most.  Measured: 40^5 2.50 ms with
+// workgroup alone on its compute unit and 0.7 for four of them; its vector
+// instructions are about half of the fill's time (279 M for 41^5 cells, 0.45 of
+// 0.92 ms), beside 3.42 GB of exchange words and directions (3.7 TB/s).  Measured: 40^5 2.50 ms with
 // the tile kernel, 0.92 now; 28^5 0.66 and 0.32.  On the way there: halo words
 // loaded by the compute waves 1.47 ms (every step waited for memory); one
 // workgroup a block 1.47; waiting several steps ahead after a stall, 1.78 against
