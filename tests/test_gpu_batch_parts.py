@@ -93,3 +93,31 @@ def test_traceback_of_few_and_of_many_jobs(k, njobs):
     jobs = [([rng.integers(0, 20, n).astype(np.uint8) for n in lens], sub, gap) for lens in shapes]
     say("batch of", njobs, "jobs, k =", k)
     check(jobs, msa.align_batch(jobs, hbm_budget_bytes=4 << 30))
+
+
+def test_threads_capture_sequences_beside_each_other():
+    """Three threads, each with an arena of its own, meet every composition for
+    the first time while the others and a server run theirs."""
+    import threading
+    errors = []
+
+    def work(n):
+        try:
+            for b, shapes in enumerate(BATCHES[n:] + BATCHES[:n]):
+                jobs = jobs_of(shapes, 200 + 30 * n + b)
+                check(jobs, msa.align_batch(jobs, hbm_budget_bytes=256 << 20))
+        except BaseException as e:  # noqa: BLE001 - reported by the main thread
+            errors.append((n, e))
+
+    say("threads")
+    with msa.Server(hbm_budget_bytes=1 << 30, max_inflight=2) as srv:
+        threads = [threading.Thread(target=work, args=(n,)) for n in (0, 7, 14)]
+        for t in threads:
+            t.start()
+        for b, shapes in enumerate(BATCHES):
+            jobs = jobs_of(shapes, 400 + b)
+            tickets = [srv.submit(*j) for j in jobs]
+            check(jobs, [srv.wait(t, 30_000_000) for t in tickets])
+        for t in threads:
+            t.join()
+    assert not errors, errors

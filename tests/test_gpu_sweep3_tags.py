@@ -125,3 +125,58 @@ def test_count_of_streaming_fills_stays_small(lens):
     for n in range(4):
         one(6000 + n)
         assert 0 <= int(count.item()) < 105
+
+
+@pytest.mark.parametrize("lens,mode", [(LENS, "plain"), (LENS, "egf"), (LENS, "coopt"),
+                                       (LENS, "nearopt"), ([9, 20, 18, 11], "plain"),
+                                       ([6, 5, 9, 7, 8], "plain")],
+                         ids=lambda x: x if isinstance(x, str) else "k%d" % len(x))
+def test_captured_calls_replay_with_new_sequences(lens, mode):
+    """The tag is read on the device, so a captured call replays with a tag of
+    its own each time, also with eager calls and synchronisations in between."""
+    import torch
+    sub, gap = protein_scoring()
+    dev = msa.DeviceAligner(lens, sub, gap, end_gaps_free=mode == "egf",
+                            cooptimal=mode == "coopt", nearopt=mode == "nearopt")
+
+    def sequences(seed):
+        rng = np.random.Generator(np.random.PCG64(seed))
+        return [rng.integers(0, 20, size=n).astype(np.uint8) for n in lens]
+
+    def call():
+        if mode == "coopt":
+            dev.run_coopt(PATHS)
+        elif mode == "nearopt":
+            dev.run_nearopt(DELTA, PATHS)
+        else:
+            dev.run()
+
+    def result():
+        if mode == "coopt":
+            return dev.result_coopt()[1]
+        return [r for _, r in dev.result_nearopt()[1]] if mode == "nearopt" else [dev.result()[1]]
+
+    say("captured", lens, mode)
+    dev.set_sequences(sequences(1))
+    call()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call()
+    for it in range(20):
+        seqs = sequences(10 + it)
+        if it % 5 == 3:  # an eager call between the replays
+            dev.set_sequences(sequences(100 + it))
+            call()
+        dev.set_sequences(seqs)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        if mode == "coopt":
+            want = oracle_coopt(seqs, sub, gap, PATHS)[1]
+        elif mode == "nearopt":
+            want = [r for _, r in oracle_nearopt(seqs, sub, gap, DELTA, PATHS)[1]]
+        else:
+            want = [(oracle_align_egf if mode == "egf" else oracle_align)(seqs, sub, gap)[1]]
+        got = result()
+        assert len(got) == len(want) and all(np.array_equal(a, b) for a, b in zip(got, want)), it
